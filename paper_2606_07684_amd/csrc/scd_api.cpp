@@ -446,7 +446,7 @@ scd_status_t enqueue_reuse_decode(const scd_model_t* model, const scd_batch_t* b
   for (const auto& grp : group_by(jobs, [](const scd::GemmJob& j) {
          return j.k * 2 + ((j.flags & scd::kRopeOut) != 0 ? 1 : 0);
        })) {
-    const int nhg = scd::decode_channel_groups(grp[0].k, w);
+    const int nhg = scd::decode_channel_groups(grp[0].k, w, T * g, static_cast<int64_t>(grp.size()));
     scd::GemmParams gp = base;
     JobPacker jp(gp, scd::decode_tile_rows(nhg, grp[0].k), 128 * nhg);
     for (const auto& j : grp) jp.add(j);
@@ -624,7 +624,8 @@ scd_status_t enqueue_align_first(const scd_model_t* model, const scd_batch_t* ba
   for (const auto& j : jobs)
     (decode_ok && j.k % 32 == 0 && j.k <= 256 ? on_decode : rest).push_back(j);
   for (const auto& grp : group_by(on_decode, [](const scd::GemmJob& j) { return j.k; })) {
-    const int nhg = scd::decode_channel_groups(grp[0].k, hidden);
+    const int nhg = scd::decode_channel_groups(grp[0].k, hidden, batch->n_tokens,
+                                               static_cast<int64_t>(grp.size()));
     JobPacker jp(base, scd::decode_tile_rows(nhg, grp[0].k), 128 * nhg);
     for (const auto& j : grp) jp.add(j);
     for (const auto& lp : jp.build()) {
@@ -637,12 +638,12 @@ scd_status_t enqueue_align_first(const scd_model_t* model, const scd_batch_t* ba
   bool gemm_ok = fast;
   for (const auto& j : rest)
     if (j.k % 64 != 0) gemm_ok = false;
-  JobPacker jp(base, gemm_ok ? scd::kPatchBM : scd::kGenericBM,
-               gemm_ok ? scd::kPatchBN : scd::kGenericBN);
+  const int tile = scd::patch_tile(batch->n_tokens, hidden, static_cast<int64_t>(rest.size()));
+  JobPacker jp(base, gemm_ok ? tile : scd::kGenericBM, gemm_ok ? tile : scd::kGenericBN);
   for (const auto& j : rest) jp.add(j);
   if (!gemm_ok) return run(scd::Op::kPatchAlign, jp.build(), model->dtype, stream);
   for (const auto& p : jp.build()) {
-    const hipError_t e = scd::launch_align_bf16(p, stream);
+    const hipError_t e = scd::launch_align_bf16(tile, p, stream);
     if (e != hipSuccess) return fail(SCD_ERR_HIP, "aligner launch failed: %s", hipGetErrorString(e));
   }
   return ok();
@@ -680,8 +681,11 @@ scd_status_t scd_patch_kv(const scd_model_t* model, const scd_batch_t* batch,
   const int D = static_cast<int>(kv_width(model));
   const bool fast = model->dtype == SCD_BF16 && model->d_model % 64 == 0 &&
                     (model->head_dim == 64 || model->head_dim == 128) && D % 128 == 0;
+  int64_t n_patch = 0;
+  for (int l = 0; l < model->n_layers; ++l) n_patch += model->is_patch[l] ? 1 : 0;
+  const int tile = scd::patch_tile(T, D, 2 * n_patch);
   JobPacker jp(base_params(model, batch, T, 1, rope_table, max_position),
-               fast ? scd::kPatchBM : scd::kGenericBM, fast ? scd::kPatchBN : scd::kGenericBN);
+               fast ? tile : scd::kGenericBM, fast ? tile : scd::kGenericBN);
   for (int l = 0; l < model->n_layers; ++l) {
     if (!model->is_patch[l]) continue;
     const void* bk = b_k ? b_k[l] : nullptr;
@@ -691,7 +695,7 @@ scd_status_t scd_patch_kv(const scd_model_t* model, const scd_batch_t* batch,
   }
   if (!fast) return run(scd::Op::kPatchKV, jp.build(), model->dtype, stream);
   for (const auto& p : jp.build()) {
-    const hipError_t e = scd::launch_patch_bf16(p, stream);
+    const hipError_t e = scd::launch_patch_bf16(tile, p, stream);
     if (e != hipSuccess) return fail(SCD_ERR_HIP, "patch launch failed: %s", hipGetErrorString(e));
   }
   return ok();
@@ -742,8 +746,10 @@ scd_status_t scd_patch_align(const scd_model_t* model, const scd_batch_t* batch,
   const scd::GemmParams base = base_params(model, batch, T, 1, nullptr, 0);
   // act = SiLU(z_h w1^T + b1) for every Patch layer, then h_hat = act w2^T + b2
   std::vector<scd::GemmJob> first_jobs;
-  JobPacker second(base, fast2 ? scd::kPatchBM : scd::kGenericBM,
-                   fast2 ? scd::kPatchBN : scd::kGenericBN);
+  int64_t n_patch = 0;
+  for (int l = 0; l < model->n_layers; ++l) n_patch += model->is_patch[l] ? 1 : 0;
+  const int tile = scd::patch_tile(T, d, n_patch);
+  JobPacker second(base, fast2 ? tile : scd::kGenericBM, fast2 ? tile : scd::kGenericBN);
   for (int l = 0; l < model->n_layers; ++l) {
     if (!model->is_patch[l]) continue;
     first_jobs.push_back({z_h[l], w1[l], act[l], b1 ? b1[l] : nullptr, hidden, model->rank_h[l],
@@ -754,7 +760,7 @@ scd_status_t scd_patch_align(const scd_model_t* model, const scd_batch_t* batch,
                               model->dtype == SCD_BF16 && hidden % 128 == 0, stream));
   if (!fast2) return run(scd::Op::kPatchAlign, second.build(), model->dtype, stream);
   for (const auto& p : second.build()) {
-    const hipError_t e = scd::launch_align_bf16(p, stream);
+    const hipError_t e = scd::launch_align_bf16(tile, p, stream);
     if (e != hipSuccess)
       return fail(SCD_ERR_HIP, "aligner launch failed: %s", hipGetErrorString(e));
   }
@@ -809,14 +815,30 @@ scd_status_t scd_patch_fold(const scd_model_t* model, int32_t hidden,
     jobs.push_back({w_k[l], w2[l], b2 ? b2[l] : nullptr, b_k ? b_k[l] : nullptr, w_fold_k[l], c_k[l]});
     jobs.push_back({w_v[l], w2[l], b2 ? b2[l] : nullptr, b_v ? b_v[l] : nullptr, w_fold_v[l], c_v[l]});
   }
+  // bf16 products on the matrix cores where the contraction is whole 64-wide steps (d_model % 64 ==
+  // 0) and a layer's w2 is within a buffer's 2 GiB; the fp32 path and other widths on the vector units
+  const int D = static_cast<int>(kv_width(model));
+  const bool fast = model->dtype == SCD_BF16 && model->d_model % 64 == 0 &&
+                    static_cast<int64_t>(model->d_model) * hidden < (int64_t{1} << 30);
+  if (fast) {
+    scd_batch_t none{};
+    none.n_seqs = 1;
+    const int tile = scd::patch_tile(D, hidden, static_cast<int64_t>(jobs.size()));
+    JobPacker jp(base_params(model, &none, D, 1, nullptr, 0), tile, tile);
+    for (const auto& j : jobs) jp.add({j.wp, j.w2, j.wf, nullptr, hidden, model->d_model, 0, 0});
+    for (const auto& p : jp.build()) {
+      const hipError_t e = scd::launch_fold_bf16(tile, p, stream);
+      if (e != hipSuccess) return fail(SCD_ERR_HIP, "fold launch failed: %s", hipGetErrorString(e));
+    }
+  }
   for (size_t done = 0; done < jobs.size(); done += scd::kMaxJobs) {
     scd::FoldParams p{};
     p.n_jobs = 0;
     for (size_t i = done; i < jobs.size() && i < done + scd::kMaxJobs; ++i) p.jobs[p.n_jobs++] = jobs[i];
-    p.n = static_cast<int32_t>(kv_width(model));
+    p.n = D;
     p.d_model = model->d_model;
     p.hidden = hidden;
-    const hipError_t e = scd::launch_patch_fold(model->dtype == SCD_BF16, p, stream);
+    const hipError_t e = scd::launch_patch_fold(model->dtype == SCD_BF16, !fast, p, stream);
     if (e != hipSuccess) return fail(SCD_ERR_HIP, "fold launch failed: %s", hipGetErrorString(e));
   }
   return ok();
@@ -877,7 +899,8 @@ scd_status_t scd_patch_kv_from_codes(const scd_model_t* model, const scd_batch_t
   }
   for (const auto& grp : groups) {
     std::vector<scd::GemmJob> first;
-    JobPacker jp(base, fast ? scd::kPatchBM : scd::kGenericBM, fast ? scd::kPatchBN : scd::kGenericBN);
+    const int tile = scd::patch_tile(T, D, 2 * static_cast<int64_t>(grp.size()));
+    JobPacker jp(base, fast ? tile : scd::kGenericBM, fast ? tile : scd::kGenericBN);
     for (int l : grp) {
       first.push_back({z_h[l], w1[l], act[l], b1 ? b1[l] : nullptr, hidden, model->rank_h[l],
                        scd::kVecOut | scd::kSiluOut, 0});
@@ -891,7 +914,7 @@ scd_status_t scd_patch_kv_from_codes(const scd_model_t* model, const scd_batch_t
       continue;
     }
     for (const auto& p : jp.build()) {
-      const hipError_t e = scd::launch_patch_bf16(p, stream);
+      const hipError_t e = scd::launch_patch_bf16(tile, p, stream);
       if (e != hipSuccess) return fail(SCD_ERR_HIP, "patch launch failed: %s", hipGetErrorString(e));
     }
   }

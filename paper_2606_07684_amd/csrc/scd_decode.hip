@@ -34,10 +34,18 @@ namespace {
 using namespace dev;
 
 // Waves per workgroup: 8 when the basis chunk (128 nhg channels x rank) takes more than half the
-// LDS, so one workgroup holds the CU (512 channels up to rank 128, 256 channels above); 4 when
-// two workgroups share a CU.  A tile is 32 rows per wave.
+// LDS (512 channels from rank 96 to 128, 256 channels above); else 4.  A tile is 32 rows per wave.
 constexpr int waves_for(int nhg, int kch) {
   return 128 * nhg * (32 * kch + 8) * 2 > 80 * 1024 ? 8 : 4;
+}
+// Workgroups per CU: two of 4 waves, one of 8, and one of 4 waves for the short contractions of a
+// 512-channel chunk (ranks up to 64).  Those are bound by their stores alone, and fewer waves keep the
+// stores in flight closer together: rank 32 at 16,384 tokens x 28 layers (keys and values, 1.88 GB
+// written) takes 420 us with one such workgroup per CU and 545 us with two; rank 64, 442 us with 4
+// waves and 530 us with 8.  Longer contractions need the second wave of each SIMD (rank 128 at 8192
+// tokens: 289 us with 8 waves, 315 us with 4).
+constexpr int wgs_per_cu(int nhg, int kch) {
+  return waves_for(nhg, kch) == 8 || (nhg == 4 && kch <= 2) ? 1 : 2;
 }
 constexpr int kDRows = kRopeMinRows;  // in-half offsets d = 0..15
 
@@ -350,9 +358,34 @@ hipError_t launch_kch(int kch, const GemmParams& p, int grid_size, size_t lds,
 
 }  // namespace
 
-int decode_channel_groups(int rank, int basis_width) {
-  if (rank > 128) return basis_width % 256 == 0 ? 2 : 1;
-  return basis_width % 512 == 0 ? 4 : (basis_width % 256 == 0 ? 2 : 1);
+// Channels per workgroup (128 nhg) for a launch of n_jobs products of `rows` rows.  The widest chunk
+// that fits the LDS reads the codes least often and keeps each row's stores together, but its tiles
+// are large: a launch with few of them ends in a round that leaves CUs idle.  So the chunk with the
+// least rounds x (elements a CU takes per round) wins, each halving of the chunk counted as 1.25
+// times the work.  Keys and values at the 8B shape (28 layers, rank 128), 512 / 256 / 128 channels,
+// us: 40 tokens 27 / 19 / 15, 333 tokens 37 / 29 / 29, 700 tokens 38 / 40 / 40, 1100 tokens
+// 60 / 44 / 50, 2000 tokens 76 / 95 / 103, 8192 tokens 286 / 329 / 366.  Ranks up to 64 hold only one
+// workgroup of 4 waves per CU at 512 channels, which pays once the stores go to HBM: while both
+// branches' output fits the 256 MB memory-side cache they start at 256 (rank 64, 512 / 256 channels,
+// us: 333 tokens 26 / 24, 1000 tokens 41 / 36, 2000 tokens 63 / 58, 8192 tokens 239 / 284).
+int decode_channel_groups(int rank, int basis_width, int64_t rows, int64_t n_jobs) {
+  int nhg = basis_width % 512 == 0 ? 4 : (basis_width % 256 == 0 ? 2 : 1);
+  const bool cached = rows * n_jobs * basis_width * 2 <= int64_t{128} << 20;
+  if (nhg == 4 && (rank > 128 || (rank <= 64 && cached))) nhg = 2;
+  constexpr int64_t kCus = 256;
+  double best_cost = 0.0, weight = 1.0;
+  int best = nhg;
+  for (int g = nhg; g >= 1; g /= 2, weight *= 1.25) {
+    const int64_t tr = decode_tile_rows(g, rank), per_cu = wgs_per_cu(g, (rank + 31) / 32);
+    const int64_t tiles = (rows + tr - 1) / tr * n_jobs * (basis_width / (128 * g));
+    const int64_t rounds = (tiles + kCus * per_cu - 1) / (kCus * per_cu);
+    const double cost = weight * static_cast<double>(rounds * per_cu * tr * g);
+    if (g == nhg || cost < best_cost) {
+      best_cost = cost;
+      best = g;
+    }
+  }
+  return best;
 }
 
 int decode_tile_rows(int nhg, int rank) { return 32 * waves_for(nhg, (rank + 31) / 32); }
@@ -376,7 +409,7 @@ static hipError_t compute_units(int* out) {
   return hipSuccess;
 }
 
-size_t decode_bf16_lds_bytes(int nhg, int rank, int head_dim) {
+static size_t decode_bf16_lds_bytes(int nhg, int rank, int head_dim) {
   const size_t cn = 128 * static_cast<size_t>(nhg);
   return cn * (rank + 8) * 2 + cn * 2 + static_cast<size_t>(kDRows) * (head_dim / 2 + 2) * 8;
 }
@@ -404,10 +437,7 @@ hipError_t launch_decode_bf16(int nhg, const GemmParams& p, hipStream_t stream, 
   const hipError_t e = compute_units(&cus);
   if (e != hipSuccess) return e;
   const int waves = waves_for(nhg, kch);
-  const size_t lds_per_wg = lds + sizeof(LdsBatch);
-  int per_cu = static_cast<int>((160 * 1024) / lds_per_wg);
-  per_cu = per_cu < 8 / waves ? per_cu : 8 / waves;
-  per_cu = per_cu < 1 ? 1 : per_cu;
+  const int per_cu = wgs_per_cu(nhg, kch);
   const int n_nc = p.jobs[0].n / cn;
   const int64_t tile_rows = 32 * waves;
   const int64_t row_tiles = (p.m + tile_rows - 1) / tile_rows * p.n_jobs;

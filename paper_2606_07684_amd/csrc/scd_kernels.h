@@ -59,14 +59,17 @@ enum class Op : int { kReuseDecode = 0, kPatchKV = 1, kEncodeKV = 2, kEncodeH = 
 // Launchers (return the hipError_t of the launch).
 hipError_t launch_gemm(Op op, bool bf16, const GemmParams& p, hipStream_t stream);
 
-// Patch on the bf16 path: 256 x 256 tiles (tokens x channels), d_model % 64 == 0, head_dim 64 or
-// 128, D % 128 == 0.
-constexpr int kPatchBM = 256;
-constexpr int kPatchBN = 256;
-hipError_t launch_patch_bf16(const GemmParams& p, hipStream_t stream);
+// Patch on the bf16 path: square tiles (tokens x channels) of 256 or 128, d_model % 64 == 0,
+// head_dim 64 or 128, D % 128 == 0.  patch_tile picks the tile for a launch of n_jobs products
+// [m, n].
+int patch_tile(int64_t m, int n, int64_t n_jobs);
+hipError_t launch_patch_bf16(int tile, const GemmParams& p, hipStream_t stream);
 // The aligner's two products on the same kernel (its own symbol): C = act(A B^T + vec), with
 // act = SiLU on jobs flagged kSiluOut; no RoPE.
-hipError_t launch_align_bf16(const GemmParams& p, hipStream_t stream);
+hipError_t launch_align_bf16(int tile, const GemmParams& p, hipStream_t stream);
+// The fold's product on the same kernel, the weights stored [k, n]: C[m, n] = A[m, k] B[k, n];
+// k % 64 == 0, n % 16 == 0, k * n * 2 < 2^31.
+hipError_t launch_fold_bf16(int tile, const GemmParams& p, hipStream_t stream);
 
 // Fold of the aligner's output layer into a projection (one-time, weights only):
 // wf = wp w2 [n, hidden] and c = wp b2 + bp [n], fp32 accumulation, one rounding.
@@ -86,12 +89,13 @@ struct FoldParams {
   int32_t hidden;   // multiple of 16
 };
 static_assert(sizeof(FoldParams) <= 4096, "kernel argument block");
-hipError_t launch_patch_fold(bool bf16, const FoldParams& p, hipStream_t stream);
+// products: form wf here (else only c: launch_fold_bf16 forms wf)
+hipError_t launch_patch_fold(bool bf16, bool products, const FoldParams& p, hipStream_t stream);
 
 // Reuse decode on the bf16 path: workgroups own a channel chunk of 128 * nhg and a share of the
 // launch's row tiles (decode_tile_rows(nhg) rows each); basis_width % (128 * nhg) == 0, one rank
 // (% 32 == 0, <= 256) and one branch per launch, head_dim 64 or 128.
-int decode_channel_groups(int rank, int basis_width);
+int decode_channel_groups(int rank, int basis_width, int64_t rows, int64_t n_jobs);
 int decode_tile_rows(int nhg, int rank);  // rows per tile of the kernel instance
 // align: run the aligner's first product (jobs flagged kSiluOut, rank <= 128, no RoPE) under its
 // own kernel symbol.

@@ -29,6 +29,18 @@
 // The epilogue first stages the tile's RoPE factors (256 tokens x d_h/2 pairs, fp32) and bias in
 // the then free LDS, so its stores never queue behind global loads (on this part loads and stores
 // share one counter: a load issued after stores can only be waited for together with them).
+//
+// Launches with few 256-wide tiles leave most of the chip idle, and each workgroup then waits on the
+// latency of its own copies; they take 128 x 128 tiles (patch_tile), and where every CU has at most
+// one, a ring of nine slots (copies four steps ahead).  333 tokens at the 8B shape (4 layers, contraction
+// 4096): 64 tiles of 256 take 88 us, 192 tiles of 128 45 us with copies two steps ahead and about 25 us
+// with four.
+//
+// The fold of the aligner's output layer (W_P W2, both row-major) is the same product with the right
+// operand's contraction along its rows; it is read through transposing LDS reads.  Eight products
+// 1024 x 4096 x 4096: 240 us (1.15 PFLOP/s) against 3.3 ms on the vector units.
+#include <numeric>
+
 #include "scd_device.h"
 
 namespace scd {
@@ -36,22 +48,25 @@ namespace {
 
 using namespace dev;
 
-constexpr int kBM = kPatchBM;   // tokens per tile
-constexpr int kBN = kPatchBN;   // channels per tile
 constexpr int kBK = 64;                     // contraction step
 constexpr int kLDK = kBK;                   // LDS row (bf16 elements): 8 16-byte chunks, swizzled
-constexpr int kChunks = kBK / 8;
-constexpr int kSlot = kBN * kLDK;           // elements per ring slot (one operand tile of a step)
-constexpr int kRing = 5;                    // slots
+constexpr int kChunks = kBK / 8;            // 16-byte chunks of an operand row's step
 constexpr int kWaves = 4;                   // one wave per SIMD
 constexpr int kThreads = 64 * kWaves;
-constexpr int kDmaIters = kBN * kChunks / kThreads;  // copy instructions per wave per operand tile
-constexpr int kWaveTok = 128;               // tokens per wave (each wave owns 128 channels)
-constexpr int kUB = kWaveTok / 16;          // 16-token MFMA blocks per wave
-constexpr int kSB = 128 / 16;               // 16-channel MFMA blocks per wave
-static_assert(kBN == kBM, "square tiles: both operand tiles fill one slot");
-static_assert(kRing * kSlot * 2 <= 160 * 1024, "LDS");
-static_assert(kBM * 32 * 16 + kBN * 2 <= kRing * kSlot * 2, "epilogue staging fits the ring");
+
+// Geometry of a square tile of TILE channels x TILE tokens (256 or 128) whose copies run AHEAD steps
+// before their use.
+template <int TILE, int AHEAD>
+struct Geo {
+  static constexpr int kRing = 2 * AHEAD + 1;                    // slots
+  static constexpr int kSlot = TILE * kBK;                       // elements of one operand tile
+  static constexpr int kDmaIters = TILE * kChunks / kThreads;    // copies per wave per operand tile
+  static constexpr int kWaveTok = TILE / 2;                      // tokens per wave
+  static constexpr int kUB = kWaveTok / 16;                      // 16-token MFMA blocks per wave
+  static constexpr int kSB = TILE / 2 / 16;                      // 16-channel MFMA blocks per wave
+  static_assert(kRing * kSlot * 2 <= 160 * 1024, "LDS");
+  static_assert(TILE * 32 * 16 + TILE * 2 <= kRing * kSlot * 2, "epilogue staging fits the ring");
+};
 // Fourth word of a raw buffer resource on gfx9-family parts: 32-bit data format, no swizzle.
 constexpr int kBufferFlags = 0x00020000;
 
@@ -62,12 +77,21 @@ constexpr int kBufferFlags = 0x00020000;
 __device__ __forceinline__ int swz(int r) { return r & 7; }
 
 // Weight row (within the tile) held by LDS row rho.  Element i of a 16 x 16 MFMA accumulator of
-// lane l is output row 4 (l / 16) + i of its block; with this order, blocks 2p and 2p + 1 of a
-// wave's 128 rows give lane l the channels 32p + 8 (l / 16) + (0..7), eight consecutive ones.
+// lane l is output row 4 (l / 16) + i of its block; with this order, blocks 2p and 2p + 1 of the
+// tile give lane l the channels 32p + 8 (l / 16) + (0..7), eight consecutive ones.
 __device__ __forceinline__ int weight_row_of_lds(int rho) {
-  const int s = (rho >> 4) & 7, m = rho & 15;
-  return (rho & 128) | (32 * (s >> 1) + 8 * (m >> 2) + 4 * (s & 1) + (m & 3));
+  const int m = rho & 15;
+  return (rho & ~31) | (8 * (m >> 2) + 4 * ((rho >> 4) & 1) + (m & 3));
 }
+
+// Weights stored with the contraction as rows ([K, N], the fold's right operand) keep that order in
+// LDS: row k of a step holds the tile's TILE channels, and the operand is read with transposing LDS
+// reads (ds_read_b64_tr_b16: 16 lanes read 4 rows x 16 channels and lane i receives channel i of
+// the 4 rows).  Chunk c of row k sits at c ^ kswz(k); the two bits keep apart the rows a read takes
+// from one group of four, the third the groups of neighbouring reads.
+__device__ __forceinline__ int kswz(int k) { return 2 * (k & 3) + ((k >> 3) & 1); }
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) s16x4* lds_s16x4_t;
 
 // s_waitcnt immediates: at most n vector-memory operations outstanding (optionally with every LDS
 // access completed), or every LDS access completed.
@@ -76,36 +100,39 @@ constexpr int vmcnt_imm(int n, bool lds_done = false) {
 }
 constexpr int kLgkmDone = 0xF | (0x3 << 14) | (0x7 << 4);
 
-// Scheduling groups for one slice of 64 MFMAs, in two halves of 32 with a scheduling fence
-// between them (one solver region of all 64 MFMAs, 16 reads and 8 copies is not ordered as asked):
-// in the first half one LDS read (operands of the next slice, which do not feed these MFMAs) after
-// every second MFMA, in the second half one copy after every fourth.  (The compiler cannot tell
-// that the copies and the reads touch different LDS slots, so it keeps them in program order:
-// reads first.)
-template <int I = 0>
-__device__ __forceinline__ void interleave_reads() {
-  if constexpr (I < 16) {
-    __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
-    __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-    interleave_reads<I + 1>();
+// Scheduling groups for one slice of MFMAs, in two halves with a scheduling fence between them (one
+// solver region of all 64 MFMAs, 16 reads and 8 copies of a 256-wide tile is not ordered as asked):
+// in the first half the LDS reads (operands of the next slice, which do not feed these MFMAs)
+// spread over the MFMAs, in the second half the copies.  (The compiler cannot tell that the copies
+// and the reads touch different LDS slots, so it keeps them in program order: reads first.)
+// MASK: what is spread (0x100 LDS reads, 0x020 vector-memory reads); N of them over M MFMAs, in
+// groups of R behind P MFMAs.
+template <int MASK, int P, int R, int G, int I = 0>
+__device__ __forceinline__ void spread() {
+  if constexpr (I < G) {
+    __builtin_amdgcn_sched_group_barrier(0x008, P, 0);
+    __builtin_amdgcn_sched_group_barrier(MASK, R, 0);
+    spread<MASK, P, R, G, I + 1>();
   }
 }
-template <int C, int I = 0>
-__device__ __forceinline__ void interleave_copies() {
-  static_assert(C >= 0 && C <= 8, "at most one copy per four MFMAs");
-  if constexpr (I < C) {
-    __builtin_amdgcn_sched_group_barrier(0x008, 4, 0);
-    __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
-    interleave_copies<C, I + 1>();
-  } else if constexpr (C < 8) {
-    __builtin_amdgcn_sched_group_barrier(0x008, 4 * (8 - C), 0);
-  }
+template <int MASK, int M, int N>
+__device__ __forceinline__ void interleave() {
+  constexpr int G = std::gcd(M, N);  // groups
+  spread<MASK, M / G, N / G, G>();
 }
 
 // The product C = A B^T of one launch (both operands row-major with the contraction contiguous,
-// 256 x 256 tiles), with the epilogue the job flags select.  Two kernels run it: the Patch KV
-// regeneration and the aligner in front of it, so profiles attribute each step to its own symbol.
+// TILE x TILE tiles), with the epilogue the job flags select.  KM: the weights are [K, N] instead
+// (contraction as rows).  Several kernels run it, so profiles attribute each step to its own symbol.
+// A wave owns TILE / 2 channels x TILE / 2 tokens.  Its channels are whole heads (TILE 256) or 32
+// channels of a head's first half with their RoPE partners (TILE 128: 32-channel groups wn and
+// wn + 2 for d_h = 128, 2 wn and 2 wn + 1 for d_h = 64).
+template <int TILE, int AHEAD, bool KM>
 __device__ __forceinline__ void patch_gemm_bf16(const GemmParams& p, uint16_t* smem) {
+#if defined(__HIP_DEVICE_COMPILE__)  // device builtins, which a template's host pass would reject
+  using G = Geo<TILE, AHEAD>;
+  constexpr int kRing = G::kRing, kBM = TILE, kBN = TILE, kSlot = G::kSlot, kDmaIters = G::kDmaIters;
+  constexpr int kWaveTok = G::kWaveTok, kUB = G::kUB, kSB = G::kSB;
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -133,8 +160,9 @@ __device__ __forceinline__ void patch_gemm_bf16(const GemmParams& p, uint16_t* s
   // offsets then fit in 32 bits and the step's offset is one scalar.
   auto records = [](int64_t bytes) { return static_cast<int>(bytes < 0x7fffffff ? bytes : 0x7fffffff); };
   const __amdgpu_buffer_rsrc_t wres = __builtin_amdgcn_make_buffer_rsrc(
-      const_cast<uint16_t*>(W + static_cast<int64_t>(n0) * K), 0,
-      records(static_cast<int64_t>(N - n0) * K * 2), kBufferFlags);
+      const_cast<uint16_t*>(W + (KM ? n0 : static_cast<int64_t>(n0) * K)), 0,
+      records(KM ? (static_cast<int64_t>(K) * N - n0) * 2 : static_cast<int64_t>(N - n0) * K * 2),
+      kBufferFlags);
   const __amdgpu_buffer_rsrc_t hres = __builtin_amdgcn_make_buffer_rsrc(
       const_cast<uint16_t*>(Hh + t0 * K), 0, records((M - t0) * K * 2), kBufferFlags);
   uint32_t woff[kDmaIters], hoff[kDmaIters];
@@ -142,16 +170,24 @@ __device__ __forceinline__ void patch_gemm_bf16(const GemmParams& p, uint16_t* s
   for (int j = 0; j < kDmaIters; ++j) {
     const int slot = (kWaves * j + wave) * 64 + lane;
     const int rho = slot / kChunks, c = (slot % kChunks) ^ swz(slot / kChunks);
-    const int n = weight_row_of_lds(rho) < N - n0 ? weight_row_of_lds(rho) : N - n0 - 1;
     const int t = t0 + rho < M ? rho : static_cast<int>(M - 1 - t0);
-    woff[j] = static_cast<uint32_t>((n * K + 8 * c) * 2);
+    if constexpr (KM) {
+      // row k of the step, channel chunk cn (N is a multiple of 8; chunks past N repeat the last)
+      const int k = slot / (kBN / 8);
+      int cn = (slot % (kBN / 8)) ^ kswz(k);
+      cn = n0 + 8 * cn < N ? cn : (N - n0) / 8 - 1;
+      woff[j] = static_cast<uint32_t>((k * N + 8 * cn) * 2);
+    } else {
+      const int n = weight_row_of_lds(rho) < N - n0 ? weight_row_of_lds(rho) : N - n0 - 1;
+      woff[j] = static_cast<uint32_t>((n * K + 8 * c) * 2);
+    }
     hoff[j] = static_cast<uint32_t>((t * K + 8 * c) * 2);
   }
   constexpr bool kTokens = true, kWeights = false;
   // copies j0 .. j1-1 of an operand tile (the whole tile is 0 .. kDmaIters-1)
   auto copy_part = [&](bool tokens, int kc, int slot, int j0, int j1) {
     uint16_t* dst = smem + slot * kSlot;
-    const int kb = kc * kBK * 2;
+    const int kb = kc * kBK * 2 * (KM && !tokens ? N : 1);
 #pragma unroll
     for (int j = j0; j < j1; ++j)
       __builtin_amdgcn_raw_ptr_buffer_load_lds(tokens ? hres : wres,
@@ -169,47 +205,69 @@ __device__ __forceinline__ void patch_gemm_bf16(const GemmParams& p, uint16_t* s
       for (int e = 0; e < 4; ++e) acc[s][u][e] = 0.f;
 
   const int lr = lane & 15, lq = lane >> 4;
-  // Fragments of k-slice ks (32 wide) of the current stage: 8 weight blocks, 8 token blocks.  Lane
-  // group q = l / 16 reads chunk 4 ks + q of its row; every block starts at a multiple of 16 rows,
-  // so the row's swizzle is swz(lane % 16).
+  // The wave's 32-channel groups (block pairs): group j of the wave is tile group wg0 + j * wgs.
+  const int wgs = TILE == 128 && p.head_dim == 128 ? 2 : 1;
+  const int wg0 = TILE == 256 ? 4 * wn : (wgs == 2 ? wn : 2 * wn);
+  // Fragments of k-slice ks (32 wide) of the current stage: kSB weight blocks, kUB token blocks.
+  // Lane group q = l / 16 reads chunk 4 ks + q of its row; every block starts at a multiple of 16
+  // rows, so the row's swizzle is swz(lane % 16).
   auto frags = [&](const uint16_t* wb, const uint16_t* hb, int ks, bf16x8* af, bf16x8* bfr) {
     const int co = 8 * ((4 * ks + lq) ^ swz(lr));
 #pragma unroll
-    for (int s = 0; s < kSB; ++s)
-      af[s] = *reinterpret_cast<const bf16x8*>(wb + s * 16 * kLDK + co);
+    for (int s = 0; s < kSB; ++s) {
+      const int grp = wg0 + (s >> 1) * wgs;
+      if constexpr (KM) {
+        // lane l takes rows 8q .. 8q + 3 (then + 4) of the slice, channels 32 grp + 8 (l % 4) +
+        // 4 (s & 1) + (0..3) of the row (l % 16) / 4 of the four
+        union { s16x4 h[2]; bf16x8 v; } f;
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+          const int k = 32 * ks + 8 * lq + 4 * b + (lr >> 2);
+          const int c = (4 * grp + (lr & 3)) ^ kswz(k);
+          f.h[b] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+              (lds_s16x4_t)(wb + k * kBN + 8 * c + 4 * (s & 1)));
+        }
+        af[s] = f.v;
+      } else {
+        af[s] = *reinterpret_cast<const bf16x8*>(wb + (grp * 32 + (s & 1) * 16) * kLDK + co);
+      }
+    }
 #pragma unroll
     for (int u = 0; u < kUB; ++u)
       bfr[u] = *reinterpret_cast<const bf16x8*>(hb + u * 16 * kLDK + co);
   };
-  // half h of a slice's MFMAs: weight blocks 4h .. 4h + 3 against every token block
+  constexpr int kReads = kSB * (KM ? 2 : 1) + kUB, kHalf = kSB / 2 * kUB;
+  // half h of a slice's MFMAs: half the weight blocks against every token block
   auto mma = [&](const bf16x8* af, const bf16x8* bfr, int h) {
 #pragma unroll
-    for (int s = 4 * h; s < 4 * h + 4; ++s)
+    for (int s = kSB / 2 * h; s < kSB / 2 * (h + 1); ++s)
 #pragma unroll
       for (int u = 0; u < kUB; ++u)
         acc[s][u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[s], bfr[u], acc[s][u], 0, 0, 0);
   };
 
-  // Copies in issue order: T0 W0 T1 W1 T2 W2 ... (token and weight tiles); the i-th goes to slot
-  // i mod 5.  Step kc reads slots of T(kc) and W(kc); its first slice issues token tile kc + 2 into
-  // the slot of weight tile kc - 1 (released at the previous barrier) and its second slice weight
-  // tile kc + 2 into the slot of token tile kc (released at its own barrier).  At the barrier of
-  // step kc only token tile kc + 2 may still be in flight.  A step index past the end re-copies
-  // the last step into a slot that is never read for data (its reads only feed the discarded
-  // look-ahead of the final step), so every step issues the same copies and one counter
+  // Copies in issue order: T0 W0 T1 W1 T2 W2 ... (token and weight tiles); with A = AHEAD the i-th
+  // goes to slot i mod 2A + 1.  Step kc reads slots of T(kc) and W(kc); its first slice issues token
+  // tile kc + A into the slot of weight tile kc - 1 (released at the previous barrier) and its second
+  // slice weight tile kc + A into the slot of token tile kc (released at its own barrier).  At the
+  // barrier of step kc only the 2A - 3 tiles after W(kc + 1) may still be in flight.  A step index
+  // past the end re-copies the last step into a slot that is never read for data (its reads only feed
+  // the discarded look-ahead of the final step), so every step issues the same copies and one counter
   // threshold holds throughout.
   auto clamp = [&](int kc) { return kc < nk ? kc : nk - 1; };
-  copy_tile(kTokens, 0, 0);
-  copy_tile(kWeights, 0, 1);
-  copy_tile(kTokens, clamp(1), 2);
-  copy_tile(kWeights, clamp(1), 3);
-  // step 0's two tiles have landed once at most the last two copies are pending
-  __builtin_amdgcn_s_waitcnt(vmcnt_imm(2 * kDmaIters, true));
+#pragma unroll
+  for (int i = 0; i < AHEAD; ++i) {
+    copy_tile(kTokens, clamp(i), 2 * i);
+    copy_tile(kWeights, clamp(i), 2 * i + 1);
+  }
+  // step 0's two tiles have landed once at most the later steps' copies are pending
+  static_assert(2 * (AHEAD - 1) * kDmaIters < 64, "counter range");
+  __builtin_amdgcn_s_waitcnt(vmcnt_imm(2 * (AHEAD - 1) * kDmaIters, true));
   lds_barrier();
-  const uint16_t* wrow = smem + (wn * 128 + lr) * kLDK;
+  const uint16_t* wrow = smem + (KM ? 0 : lr * kLDK);
   const uint16_t* hrow = smem + (wt * kWaveTok + lr) * kLDK;
   bf16x8 a0[kSB], b0[kUB], a1[kSB], b1[kUB];
-  int sh = 0, sw = 1, sfree = 4;  // slots of step kc's token and weight tiles; slot for T(kc+2)
+  int sh = 0, sw = 1, sfree = kRing - 1;  // slots of T(kc) and W(kc); slot for T(kc + AHEAD)
   frags(wrow + sw * kSlot, hrow + sh * kSlot, 0, a0, b0);
   for (int kc = 0; kc < nk; ++kc) {
     const int next_h = sh + 2 >= kRing ? sh + 2 - kRing : sh + 2;
@@ -218,23 +276,23 @@ __device__ __forceinline__ void patch_gemm_bf16(const GemmParams& p, uint16_t* s
     __builtin_amdgcn_sched_barrier(0);
     mma(a0, b0, 0);
     frags(wrow + sw * kSlot, hrow + sh * kSlot, 1, a1, b1);
-    interleave_reads();
+    interleave<0x100, kHalf, kReads>();
     __builtin_amdgcn_sched_barrier(0);
     mma(a0, b0, 1);
-    copy_tile(kTokens, clamp(kc + 2), sfree);
-    interleave_copies<kDmaIters>();
+    copy_tile(kTokens, clamp(kc + AHEAD), sfree);
+    interleave<0x020, kHalf, kDmaIters>();
     __builtin_amdgcn_sched_barrier(0);
-    // Step kc + 1's tiles have landed once at most token tile kc + 2's copies are pending.
-    __builtin_amdgcn_s_waitcnt(vmcnt_imm(kDmaIters, true));
+    // Step kc + 1's tiles have landed once at most the tiles after them are pending.
+    __builtin_amdgcn_s_waitcnt(vmcnt_imm((2 * AHEAD - 3) * kDmaIters, true));
     lds_barrier();
     __builtin_amdgcn_sched_barrier(0);
     mma(a1, b1, 0);
     frags(wrow + next_w * kSlot, hrow + next_h * kSlot, 0, a0, b0);
-    interleave_reads();
+    interleave<0x100, kHalf, kReads>();
     __builtin_amdgcn_sched_barrier(0);
     mma(a1, b1, 1);
-    copy_tile(kWeights, clamp(kc + 2), sh);
-    interleave_copies<kDmaIters>();
+    copy_tile(kWeights, clamp(kc + AHEAD), sh);
+    interleave<0x020, kHalf, kDmaIters>();
     __builtin_amdgcn_sched_barrier(0);
     sfree = sw;
     sh = next_h;
@@ -252,9 +310,9 @@ __device__ __forceinline__ void patch_gemm_bf16(const GemmParams& p, uint16_t* s
   const uint16_t* bias = static_cast<const uint16_t*>(job.vec);
   uint16_t* C = static_cast<uint16_t*>(job.c);
   const int dh = p.head_dim, half = dh >> 1;
-  // Block pairs p that hold (i, i + d_h/2): (0,2),(1,3) for d_h = 128; (0,1),(2,3) for 64.
+  // The wave's groups that hold (i, i + d_h/2): TILE 256: (0,2),(1,3) for d_h = 128 and (0,1),(2,3)
+  // for 64; TILE 128: its two groups.
   const int pstride = half >> 5;  // 2 or 1
-  const int nw = n0 + wn * 128;
   const int ql = 8 * lq;
   // The tile's RoPE factors and bias are staged in the (now free) LDS first, so the epilogue's
   // stores never wait behind global loads.  Factors: 16-byte chunk c (pairs 2c, 2c + 1) of token
@@ -310,7 +368,7 @@ __device__ __forceinline__ void patch_gemm_bf16(const GemmParams& p, uint16_t* s
   auto finish_pair = [&](auto p_c, auto ps_c, int u, int64_t t, int rl) {
     constexpr int P = decltype(p_c)::value;
     constexpr int PP = P + decltype(ps_c)::value;
-    const int nb = nw + 32 * P + ql, nbp = nw + 32 * PP + ql;
+    const int nb = n0 + 32 * (wg0 + P * wgs) + ql, nbp = n0 + 32 * (wg0 + PP * wgs) + ql;
     float a[8], b[8];
     load8(nb, a);
     load8(nbp, b);
@@ -329,7 +387,7 @@ __device__ __forceinline__ void patch_gemm_bf16(const GemmParams& p, uint16_t* s
       }
     }
     if (rope) {
-      const int c0 = ((32 * P + ql) & (half - 1)) >> 1;  // chunk of the pair of channel r = 0
+      const int c0 = (nb & (half - 1)) >> 1;  // chunk of the pair of channel r = 0 (n0 % d_h = 0)
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
         const float4 cs = *reinterpret_cast<const float4*>(stage + ((c0 + q) * kBM + rl) * 16);
@@ -349,7 +407,9 @@ __device__ __forceinline__ void patch_gemm_bf16(const GemmParams& p, uint16_t* s
     const int rl = wt * kWaveTok + 16 * u + lr;
     const int64_t t = t0 + rl;
     if (t >= M) continue;
-    if (pstride == 2) {
+    if constexpr (TILE == 128) {
+      finish_pair(IntC<0>{}, IntC<1>{}, u, t, rl);
+    } else if (pstride == 2) {
       finish_pair(IntC<0>{}, IntC<2>{}, u, t, rl);
       finish_pair(IntC<1>{}, IntC<2>{}, u, t, rl);
     } else {
@@ -357,31 +417,71 @@ __device__ __forceinline__ void patch_gemm_bf16(const GemmParams& p, uint16_t* s
       finish_pair(IntC<2>{}, IntC<1>{}, u, t, rl);
     }
   }
+#endif
 }
 
-constexpr int kSmemElems = kRing * kSlot;
-__global__ __launch_bounds__(kThreads, 1) void patch_kv_bf16_kernel(GemmParams p) {
-  __shared__ __attribute__((aligned(16))) uint16_t smem[kSmemElems];
-  patch_gemm_bf16(p, smem);
+// One workgroup per CU (all of its LDS), except the 128-wide tiles with copies two steps ahead (two).
+constexpr int wg_per_cu(int tile, int ahead) { return tile == 128 && ahead == 2 ? 2 : 1; }
+
+template <int TILE, int AHEAD>
+__global__ __launch_bounds__(kThreads, wg_per_cu(TILE, AHEAD)) void patch_kv_bf16_kernel(
+    GemmParams p) {
+  __shared__ __attribute__((aligned(16))) uint16_t smem[Geo<TILE, AHEAD>::kRing * Geo<TILE, AHEAD>::kSlot];
+  patch_gemm_bf16<TILE, AHEAD, false>(p, smem);
 }
 
-__global__ __launch_bounds__(kThreads, 1) void patch_align_bf16_kernel(GemmParams p) {
-  __shared__ __attribute__((aligned(16))) uint16_t smem[kSmemElems];
-  patch_gemm_bf16(p, smem);
+template <int TILE, int AHEAD>
+__global__ __launch_bounds__(kThreads, wg_per_cu(TILE, AHEAD)) void patch_align_bf16_kernel(
+    GemmParams p) {
+  __shared__ __attribute__((aligned(16))) uint16_t smem[Geo<TILE, AHEAD>::kRing * Geo<TILE, AHEAD>::kSlot];
+  patch_gemm_bf16<TILE, AHEAD, false>(p, smem);
 }
+
+template <int TILE, int AHEAD>
+__global__ __launch_bounds__(kThreads, wg_per_cu(TILE, AHEAD)) void patch_fold_bf16_kernel(
+    GemmParams p) {
+  __shared__ __attribute__((aligned(16))) uint16_t smem[Geo<TILE, AHEAD>::kRing * Geo<TILE, AHEAD>::kSlot];
+  patch_gemm_bf16<TILE, AHEAD, true>(p, smem);
+}
+
+// Launches of at most one 128-wide tile per CU take the deep ring.
+constexpr int kCus = 256;
 
 }  // namespace
 
-hipError_t launch_patch_bf16(const GemmParams& p, hipStream_t stream) {
-  if (p.total_tiles <= 0) return hipSuccess;
-  hipLaunchKernelGGL(patch_kv_bf16_kernel, dim3(p.total_tiles), dim3(kThreads), 0, stream, p);
-  return hipGetLastError();
+// A full round of 256-wide tiles (one per CU) does twice the work of a full round of 128-wide ones
+// (two per CU) in 1 / 0.57 to 1 / 0.75 of its time, the more the longer the contraction: 128 pays
+// where it saves a round.  Contraction 4096, 8 products of 1024 channels, 256- / 128-wide tiles, us of
+// the consumer call: 700 tokens 145 / 110, 1100 tokens 171 / 192, 2048 tokens 245 / 260, 3000 tokens
+// 385 / 387, 8192 tokens 821 / 938.
+int patch_tile(int64_t m, int n, int64_t n_jobs) {
+  const int64_t t256 = (m + 255) / 256 * ((n + 255) / 256) * n_jobs;
+  const int64_t t128 = (m + 127) / 128 * ((n + 127) / 128) * n_jobs;
+  const int64_t rounds256 = (t256 + kCus - 1) / kCus, rounds128 = (t128 + 2 * kCus - 1) / (2 * kCus);
+  return 7 * rounds128 < 10 * rounds256 ? 128 : 256;
 }
 
-hipError_t launch_align_bf16(const GemmParams& p, hipStream_t stream) {
-  if (p.total_tiles <= 0) return hipSuccess;
-  hipLaunchKernelGGL(patch_align_bf16_kernel, dim3(p.total_tiles), dim3(kThreads), 0, stream, p);
-  return hipGetLastError();
+#define SCD_PATCH_LAUNCH(KERNEL)                                                                  \
+  if (p.total_tiles <= 0) return hipSuccess;                                                      \
+  if (tile == 256)                                                                                \
+    hipLaunchKernelGGL((KERNEL<256, 2>), dim3(p.total_tiles), dim3(kThreads), 0, stream, p);      \
+  else if (p.total_tiles <= kCus)                                                                 \
+    hipLaunchKernelGGL((KERNEL<128, 4>), dim3(p.total_tiles), dim3(kThreads), 0, stream, p);      \
+  else                                                                                            \
+    hipLaunchKernelGGL((KERNEL<128, 2>), dim3(p.total_tiles), dim3(kThreads), 0, stream, p);      \
+  return hipGetLastError()
+
+hipError_t launch_patch_bf16(int tile, const GemmParams& p, hipStream_t stream) {
+  SCD_PATCH_LAUNCH(patch_kv_bf16_kernel);
 }
+
+hipError_t launch_align_bf16(int tile, const GemmParams& p, hipStream_t stream) {
+  SCD_PATCH_LAUNCH(patch_align_bf16_kernel);
+}
+
+hipError_t launch_fold_bf16(int tile, const GemmParams& p, hipStream_t stream) {
+  SCD_PATCH_LAUNCH(patch_fold_bf16_kernel);
+}
+#undef SCD_PATCH_LAUNCH
 
 }  // namespace scd

@@ -1,0 +1,71 @@
+"""Launch shapes the size rules choose between: the Patch, aligner and fold products on 256- and
+128-wide tiles and on the deep copy ring, and the Reuse decode's channel chunks, at sizes on each side
+of every rule, against the fp64 oracle (bf16 bar)."""
+import pytest
+import torch
+
+import paper_2606_07684_amd as scd
+from synth import workloads as W
+from tests import parity_util as U
+
+pytestmark = pytest.mark.gpu
+BF16_TOL = U.TOL["bf16"]
+
+
+def _patch(name, heads, head_dim, d_model, tokens, layers, **kw):
+    return W.Workload(name, layers, d_model, heads, head_dim, tokens, (32,) * layers,
+                      tuple(range(layers)), 5e5, "bf16", with_bias=True, **kw)
+
+
+# (KV heads, head_dim, d_model, request lengths, Patch layers): contractions of 1 to 9 steps of 64
+# around both rings' depths; 128-wide tiles up to one per CU (deep ring), up to two per CU, and
+# 256-wide tiles; full and ragged last tiles.
+PATCH = [
+    (8, 128, 64, (1, 127), 1),        # deep ring, one step, one full token tile
+    (2, 64, 320, (129,), 2),          # deep ring, 5 steps, one token in the second tile
+    (8, 64, 576, (300, 33), 2),       # deep ring, 9 steps, d_h = 64
+    (8, 128, 256, (333, 267), 4),     # two per CU (5 token tiles x 64), 4 steps
+    (16, 64, 192, (600,), 4),         # two per CU, d_h = 64, 3 steps
+    (8, 128, 128, (700, 380), 4),     # 256-wide (5 token tiles x 32), d_h = 128
+    (16, 64, 448, (1025,), 4),        # 256-wide, one token in the last tile, d_h = 64
+]
+
+
+@pytest.mark.parametrize("heads,head_dim,d_model,tokens,layers", PATCH)
+def test_patch_tiles(heads, head_dim, d_model, tokens, layers):
+    wl = _patch(f"tiles_{heads}_{head_dim}_{d_model}", heads, head_dim, d_model, tokens, layers)
+    dev = torch.device("cuda")
+    inp = W.Inputs(wl, dev, encode=False, decode=False)
+    rope = scd.scd_rope_table(U.model_of(wl), wl.max_position)
+    out = U.run_gpu(wl, inp, rope, which=("patch",), fill=float("nan"))
+    U.assert_within(U.compare_all(wl, inp, out), BF16_TOL, wl.name)
+
+
+# Folds: hidden widths that end inside a tile and inside a 16-byte chunk group, d_model of one and
+# many steps, and a d_model that is not whole steps (the vector-unit product).
+@pytest.mark.parametrize("heads,head_dim,d_model,hidden,layers", [
+    (2, 64, 64, 16, 1), (2, 128, 320, 144, 2), (8, 128, 192, 1040, 4), (8, 128, 128, 4112, 4),
+    (2, 64, 96, 80, 1)])
+def test_fold_tiles(heads, head_dim, d_model, hidden, layers):
+    wl = _patch(f"fold_{d_model}_{hidden}", heads, head_dim, d_model, (70,), layers,
+                aligner_hidden=hidden)
+    pc = U.PatchFromCodes(wl)
+    U.assert_within({**pc.fold_errors(), **pc.cache_errors(list(range(wl.n_tokens)))}, BF16_TOL,
+                    wl.name)
+
+
+# Reuse decode at 8 KV heads of 128 (w = 1024): chunks of 128, 256 and 512 channels for rank 128, of
+# 128 and 256 for rank 256, of 256 and 512 for ranks 32 and 64.
+@pytest.mark.parametrize("rank,tokens,layers", [
+    (128, 40, 2), (128, 1999, 7), (128, 8192, 4), (256, 333, 2), (256, 1100, 2), (64, 500, 3),
+    (32, 31000, 2), (64, 31000, 2)])
+def test_decode_chunks(rank, tokens, layers):
+    wl = W.Workload(f"chunks_{rank}_{tokens}", layers, 256, 8, 128, (tokens - 7, 7),
+                    (rank,) * layers, (), 5e5, "bf16")
+    dev = torch.device("cuda")
+    inp = W.Inputs(wl, dev, encode=False, patch=False)
+    rope = scd.scd_rope_table(U.model_of(wl), wl.max_position)
+    out = U.run_gpu(wl, inp, rope, which=("decode",), fill=float("nan"))
+    errs = U.compare_all(wl, inp, out, U.sample_tokens(wl))
+    assert all(bool(torch.isfinite(t).all()) for l in inp.R for t in (out["k_cache"][l], out["v_cache"][l]))
+    U.assert_within(errs, BF16_TOL, wl.name)
