@@ -158,10 +158,14 @@ scd::GemmParams base_params(const scd_model_t* m, const scd_batch_t* b, int64_t 
   return p;
 }
 
-scd_status_t run(scd::Op op, const std::vector<scd::GemmParams>& launches, int dtype,
-                 hipStream_t stream) {
-  for (const auto& p : launches) {
-    const hipError_t e = scd::launch_gemm(op, dtype == SCD_BF16, p, stream);
+// Jobs on the generic kernel.
+scd_status_t run_generic(scd::Op op, const scd::GemmParams& base,
+                         const std::vector<scd::GemmJob>& jobs, int dtype, hipStream_t stream) {
+  const scd::GenericShape shape = scd::generic_shape(jobs.data(), jobs.size(), base.m);
+  JobPacker jp(base, scd::generic_rows(shape), scd::generic_cols(shape));
+  for (const auto& j : jobs) jp.add(j);
+  for (const auto& p : jp.build()) {
+    const hipError_t e = scd::launch_gemm(op, dtype == SCD_BF16, shape, p, stream);
     if (e != hipSuccess) return fail(SCD_ERR_HIP, "kernel launch failed: %s", hipGetErrorString(e));
   }
   return ok();
@@ -368,15 +372,11 @@ scd_status_t scd_encode(const scd_model_t* model, const scd_batch_t* batch,
     // tiles of 128 code columns: a rank above 128 takes two workgroups per row tile
     SCD_TRY(run_groups(kv_base, scd::kEncodeRows, 128, group_by(kv_jobs, by_kind), enc, "encode"));
   } else {
-    JobPacker jp(kv_base, scd::kGenericBM, scd::kGenericBN);
-    for (const auto& j : kv_jobs) jp.add(j);
-    SCD_TRY(run(scd::Op::kEncodeKV, jp.build(), model->dtype, stream));
+    SCD_TRY(run_generic(scd::Op::kEncodeKV, kv_base, kv_jobs, model->dtype, stream));
   }
   if (fast_h)
     return run_groups(h_base, scd::kEncodeRows, 128, group_by(h_jobs, by_kind), enc, "encode");
-  JobPacker hp(h_base, scd::kGenericBM, scd::kGenericBN);
-  for (const auto& j : h_jobs) hp.add(j);
-  return run(scd::Op::kEncodeH, hp.build(), model->dtype, stream);
+  return run_generic(scd::Op::kEncodeH, h_base, h_jobs, model->dtype, stream);
 }
 
 namespace {
@@ -424,8 +424,8 @@ scd_status_t enqueue_reuse_decode(const scd_model_t* model, const scd_batch_t* b
   const int w = model->basis_width;
   const int g = static_cast<int>(kv_width(model) / w);
   const int64_t T = batch->n_tokens;
-  bool fast = model->dtype == SCD_BF16 && (model->head_dim == 64 || model->head_dim == 128) &&
-              w % 128 == 0 && batch->n_seqs <= scd::kMaxLdsSeqs;
+  const bool fast = model->dtype == SCD_BF16 && (model->head_dim == 64 || model->head_dim == 128) &&
+                    w % 128 == 0 && batch->n_seqs <= scd::kMaxLdsSeqs;
   std::vector<scd::GemmJob> jobs;
   for (int l = 0; l < model->n_layers; ++l) {
     if (model->is_patch[l]) continue;
@@ -434,14 +434,9 @@ scd_status_t enqueue_reuse_decode(const scd_model_t* model, const scd_batch_t* b
     jobs.push_back({z_k[l], w_dec_k[l], k_cache[l], mk, w, model->rank_k[l],
                     scd::kRopeOut | scd::kVecOut, 0});
     jobs.push_back({z_v[l], w_dec_v[l], v_cache[l], mv, w, model->rank_v[l], scd::kVecOut, 0});
-    if (model->rank_k[l] % 32 != 0 || model->rank_v[l] % 32 != 0) fast = false;
   }
   const scd::GemmParams base = base_params(model, batch, T * g, g, rope_table, max_position);
-  if (!fast) {
-    JobPacker jp(base, scd::kGenericBM, scd::kGenericBN);
-    for (const auto& j : jobs) jp.add(j);
-    return run(scd::Op::kReuseDecode, jp.build(), model->dtype, stream);
-  }
+  if (!fast) return run_generic(scd::Op::kReuseDecode, base, jobs, model->dtype, stream);
   // one launch per (rank, branch): key and value jobs run different kernel instances
   for (const auto& grp : group_by(jobs, [](const scd::GemmJob& j) {
          return j.k * 2 + ((j.flags & scd::kRopeOut) != 0 ? 1 : 0);
@@ -610,7 +605,7 @@ namespace {
 
 // The aligner's first product act = SiLU(z_h w1^T + b1) for `jobs` (one per Patch layer, K = r_H).
 // It is a short contraction whose time is writing act: the shape of a Reuse decode (code x basis
-// + offset), so the bf16 decode kernel takes every job it can (r_H % 32 == 0, r_H <= 256), one
+// + offset), so the bf16 decode kernel takes every job it can (r_H <= 256), one
 // launch per rank; the other jobs take the bf16 GEMM body when `fast` (r_H % 64 == 0 and
 // hidden % 128 == 0), else the generic kernel.
 scd_status_t enqueue_align_first(const scd_model_t* model, const scd_batch_t* batch, int hidden,
@@ -622,7 +617,7 @@ scd_status_t enqueue_align_first(const scd_model_t* model, const scd_batch_t* ba
                          batch->n_seqs <= scd::kMaxLdsSeqs;
   std::vector<scd::GemmJob> on_decode, rest;
   for (const auto& j : jobs)
-    (decode_ok && j.k % 32 == 0 && j.k <= 256 ? on_decode : rest).push_back(j);
+    (decode_ok && j.k <= 256 ? on_decode : rest).push_back(j);
   for (const auto& grp : group_by(on_decode, [](const scd::GemmJob& j) { return j.k; })) {
     const int nhg = scd::decode_channel_groups(grp[0].k, hidden, batch->n_tokens,
                                                static_cast<int64_t>(grp.size()));
@@ -638,13 +633,27 @@ scd_status_t enqueue_align_first(const scd_model_t* model, const scd_batch_t* ba
   bool gemm_ok = fast;
   for (const auto& j : rest)
     if (j.k % 64 != 0) gemm_ok = false;
+  if (!gemm_ok) return run_generic(scd::Op::kPatchAlign, base, rest, model->dtype, stream);
   const int tile = scd::patch_tile(batch->n_tokens, hidden, static_cast<int64_t>(rest.size()));
-  JobPacker jp(base, gemm_ok ? tile : scd::kGenericBM, gemm_ok ? tile : scd::kGenericBN);
+  JobPacker jp(base, tile, tile);
   for (const auto& j : rest) jp.add(j);
-  if (!gemm_ok) return run(scd::Op::kPatchAlign, jp.build(), model->dtype, stream);
   for (const auto& p : jp.build()) {
     const hipError_t e = scd::launch_align_bf16(tile, p, stream);
     if (e != hipSuccess) return fail(SCD_ERR_HIP, "aligner launch failed: %s", hipGetErrorString(e));
+  }
+  return ok();
+}
+
+// K/V products of Patch layers, on the bf16 Patch kernel when `fast`.
+scd_status_t enqueue_patch(const scd_model_t* model, const scd::GemmParams& base,
+                           const std::vector<scd::GemmJob>& jobs, bool fast, hipStream_t stream) {
+  if (!fast) return run_generic(scd::Op::kPatchKV, base, jobs, model->dtype, stream);
+  const int tile = scd::patch_tile(base.m, jobs[0].n, static_cast<int64_t>(jobs.size()));
+  JobPacker jp(base, tile, tile);
+  for (const auto& j : jobs) jp.add(j);
+  for (const auto& p : jp.build()) {
+    const hipError_t e = scd::launch_patch_bf16(tile, p, stream);
+    if (e != hipSuccess) return fail(SCD_ERR_HIP, "patch launch failed: %s", hipGetErrorString(e));
   }
   return ok();
 }
@@ -681,24 +690,16 @@ scd_status_t scd_patch_kv(const scd_model_t* model, const scd_batch_t* batch,
   const int D = static_cast<int>(kv_width(model));
   const bool fast = model->dtype == SCD_BF16 && model->d_model % 64 == 0 &&
                     (model->head_dim == 64 || model->head_dim == 128) && D % 128 == 0;
-  int64_t n_patch = 0;
-  for (int l = 0; l < model->n_layers; ++l) n_patch += model->is_patch[l] ? 1 : 0;
-  const int tile = scd::patch_tile(T, D, 2 * n_patch);
-  JobPacker jp(base_params(model, batch, T, 1, rope_table, max_position),
-               fast ? tile : scd::kGenericBM, fast ? tile : scd::kGenericBN);
+  const scd::GemmParams base = base_params(model, batch, T, 1, rope_table, max_position);
+  std::vector<scd::GemmJob> jobs;
   for (int l = 0; l < model->n_layers; ++l) {
     if (!model->is_patch[l]) continue;
     const void* bk = b_k ? b_k[l] : nullptr;
     const void* bv = b_v ? b_v[l] : nullptr;
-    jp.add({h_hat[l], w_k[l], k_cache[l], bk, D, model->d_model, scd::kRopeOut | scd::kVecOut, 0});
-    jp.add({h_hat[l], w_v[l], v_cache[l], bv, D, model->d_model, scd::kVecOut, 0});
+    jobs.push_back({h_hat[l], w_k[l], k_cache[l], bk, D, model->d_model, scd::kRopeOut | scd::kVecOut, 0});
+    jobs.push_back({h_hat[l], w_v[l], v_cache[l], bv, D, model->d_model, scd::kVecOut, 0});
   }
-  if (!fast) return run(scd::Op::kPatchKV, jp.build(), model->dtype, stream);
-  for (const auto& p : jp.build()) {
-    const hipError_t e = scd::launch_patch_bf16(tile, p, stream);
-    if (e != hipSuccess) return fail(SCD_ERR_HIP, "patch launch failed: %s", hipGetErrorString(e));
-  }
-  return ok();
+  return enqueue_patch(model, base, jobs, fast, stream);
 }
 
 scd_status_t scd_patch_align(const scd_model_t* model, const scd_batch_t* batch, int32_t hidden,
@@ -746,20 +747,20 @@ scd_status_t scd_patch_align(const scd_model_t* model, const scd_batch_t* batch,
   const scd::GemmParams base = base_params(model, batch, T, 1, nullptr, 0);
   // act = SiLU(z_h w1^T + b1) for every Patch layer, then h_hat = act w2^T + b2
   std::vector<scd::GemmJob> first_jobs;
-  int64_t n_patch = 0;
-  for (int l = 0; l < model->n_layers; ++l) n_patch += model->is_patch[l] ? 1 : 0;
-  const int tile = scd::patch_tile(T, d, n_patch);
-  JobPacker second(base, fast2 ? tile : scd::kGenericBM, fast2 ? tile : scd::kGenericBN);
+  std::vector<scd::GemmJob> second;
   for (int l = 0; l < model->n_layers; ++l) {
     if (!model->is_patch[l]) continue;
     first_jobs.push_back({z_h[l], w1[l], act[l], b1 ? b1[l] : nullptr, hidden, model->rank_h[l],
                           scd::kVecOut | scd::kSiluOut, 0});
-    second.add({act[l], w2[l], h_hat[l], b2 ? b2[l] : nullptr, d, hidden, scd::kVecOut, 0});
+    second.push_back({act[l], w2[l], h_hat[l], b2 ? b2[l] : nullptr, d, hidden, scd::kVecOut, 0});
   }
   SCD_TRY(enqueue_align_first(model, batch, hidden, first_jobs,
                               model->dtype == SCD_BF16 && hidden % 128 == 0, stream));
-  if (!fast2) return run(scd::Op::kPatchAlign, second.build(), model->dtype, stream);
-  for (const auto& p : second.build()) {
+  if (!fast2) return run_generic(scd::Op::kPatchAlign, base, second, model->dtype, stream);
+  const int tile = scd::patch_tile(T, d, static_cast<int64_t>(second.size()));
+  JobPacker jp(base, tile, tile);
+  for (const auto& j : second) jp.add(j);
+  for (const auto& p : jp.build()) {
     const hipError_t e = scd::launch_align_bf16(tile, p, stream);
     if (e != hipSuccess)
       return fail(SCD_ERR_HIP, "aligner launch failed: %s", hipGetErrorString(e));
@@ -899,24 +900,17 @@ scd_status_t scd_patch_kv_from_codes(const scd_model_t* model, const scd_batch_t
   }
   for (const auto& grp : groups) {
     std::vector<scd::GemmJob> first;
-    const int tile = scd::patch_tile(T, D, 2 * static_cast<int64_t>(grp.size()));
-    JobPacker jp(base, fast ? tile : scd::kGenericBM, fast ? tile : scd::kGenericBN);
+    std::vector<scd::GemmJob> product;
     for (int l : grp) {
       first.push_back({z_h[l], w1[l], act[l], b1 ? b1[l] : nullptr, hidden, model->rank_h[l],
                        scd::kVecOut | scd::kSiluOut, 0});
-      jp.add({act[l], w_fold_k[l], k_cache[l], c_k ? c_k[l] : nullptr, D, hidden,
-              scd::kRopeOut | scd::kVecOut, 0});
-      jp.add({act[l], w_fold_v[l], v_cache[l], c_v ? c_v[l] : nullptr, D, hidden, scd::kVecOut, 0});
+      product.push_back({act[l], w_fold_k[l], k_cache[l], c_k ? c_k[l] : nullptr, D, hidden,
+                         scd::kRopeOut | scd::kVecOut, 0});
+      product.push_back({act[l], w_fold_v[l], v_cache[l], c_v ? c_v[l] : nullptr, D, hidden,
+                         scd::kVecOut, 0});
     }
     SCD_TRY(enqueue_align_first(model, batch, hidden, first, fast_first, stream));
-    if (!fast) {
-      SCD_TRY(run(scd::Op::kPatchKV, jp.build(), model->dtype, stream));
-      continue;
-    }
-    for (const auto& p : jp.build()) {
-      const hipError_t e = scd::launch_patch_bf16(tile, p, stream);
-      if (e != hipSuccess) return fail(SCD_ERR_HIP, "patch launch failed: %s", hipGetErrorString(e));
-    }
+    SCD_TRY(enqueue_patch(model, base, product, fast, stream));
   }
   return ok();
 }

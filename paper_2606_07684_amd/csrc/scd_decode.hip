@@ -26,6 +26,10 @@
 // from table rows 0..15 staged once per workgroup in LDS.  Both factors are fp64-evaluated table
 // entries; the product in fp32 is within a few ulp of cos/sin(p w).  Codes and factors are reused
 // for every channel group.
+//
+// Ranks are multiples of 16, one MFMA step; a rank of 32 KCH - 16 runs its instance's last step on zeros
+// (zeroed code registers, zeroed LDS columns).  Rank 48 at 8192 tokens x 28 layers: 230 us, 712 us on
+// the generic kernel that took such ranks before.
 #include "scd_device.h"
 
 namespace scd {
@@ -55,19 +59,19 @@ struct DecodeCtx {
   uint16_t* C;           // output rows [M, N]
   int64_t M;
   int N, n0;             // row width, first channel of the chunk
+  int K;                 // rank: 32 KCH, or 32 KCH - 16
   bool silu;             // SiLU after the offset (the aligner's first product; never with RoPE)
 };
 
 // One tile: the TT rows from row t0 of the current layer-branch, channels [n0, n0 + 128 NHG).
-// KCH = rank / 32, NHG = channel groups of 128, DH = head_dim, ROPE = key jobs, FULL = all TT
+// KCH = rank / 32 rounded up, NHG = channel groups of 128, DH = head_dim, ROPE = key jobs, FULL = all TT
 // rows exist (only the last tile of a layer-branch can be partial).
 template <int KCH, int NHG, int DH, bool ROPE, bool FULL, int TT = 32 * waves_for(NHG, KCH)>
 __device__ __forceinline__ void decode_tile(const GemmParams& p, const LdsBatch& lb,
                                             const DecodeCtx& c, int64_t t0, const uint16_t* Fs,
                                             const uint16_t* mus, const float2* dtab, int lane,
                                             int wave) {
-  constexpr int K = 32 * KCH;
-  constexpr int LDK = K + 8;
+  constexpr int LDK = 32 * KCH + 8;
   constexpr int HALF = DH / 2;
   constexpr int PS = HALF / 32;  // blocks between RoPE partners: 2 (d_h 128) or 1 (d_h 64)
   constexpr int DSTRIDE = HALF + 2;  // padded LDS row of the in-half factor table (float2)
@@ -82,9 +86,13 @@ __device__ __forceinline__ void decode_tile(const GemmParams& p, const LdsBatch&
     // never stored)
     uint4 z[2 * KCH];
     {
-      const uint16_t* zr = c.Z + (row < c.M ? row : 0) * K + 8 * h;
+      const uint16_t* zr = c.Z + (row < c.M ? row : 0) * c.K + 8 * h;
 #pragma unroll
-      for (int i = 0; i < 2 * KCH; ++i) z[i] = *reinterpret_cast<const uint4*>(zr + 16 * i);
+      for (int i = 0; i < 2 * KCH - 1; ++i) z[i] = *reinterpret_cast<const uint4*>(zr + 16 * i);
+      // a rank of 32 KCH - 16 ends one step early: zero codes (against a zeroed basis)
+      constexpr int kLast = 2 * KCH - 1;
+      z[kLast] = make_uint4(0, 0, 0, 0);
+      if (c.K == 32 * KCH) z[kLast] = *reinterpret_cast<const uint4*>(zr + 16 * kLast);
     }
 
     // RoPE factors of this row for its pair indices i0(q) + r, q = 0, 1
@@ -206,10 +214,10 @@ __device__ __forceinline__ void decode_body(const GemmParams& p, uint16_t* lds,
   constexpr int kThreads = 64 * kWaves;
   constexpr int kTT = 32 * kWaves;
   constexpr int CN = 128 * NHG;
-  constexpr int K = 32 * KCH;
-  constexpr int LDK = K + 8;
+  constexpr int LDK = 32 * KCH + 8;
   constexpr int HALF = DH / 2;
   constexpr int DSTRIDE = HALF + 2;
+  const int K = p.jobs[0].k;  // every job of a launch has the same rank
   uint16_t* Fs = lds;                                                   // [CN][LDK]
   uint16_t* mus = Fs + CN * LDK;                                        // [CN]
   float2* dtab = reinterpret_cast<float2*>(mus + CN);                   // [kDRows][DSTRIDE]
@@ -242,6 +250,7 @@ __device__ __forceinline__ void decode_body(const GemmParams& p, uint16_t* lds,
   c.M = M;
   c.N = N;
   c.n0 = nc * CN;
+  c.K = K;
   int cur = -1;
 #pragma unroll 1
   for (int64_t gt = first; gt < last; ++gt) {
@@ -262,6 +271,10 @@ __device__ __forceinline__ void decode_body(const GemmParams& p, uint16_t* lds,
       c.silu = (job.flags & kSiluOut) != 0;
       dma_rows(Fs, CN, K / 8, LDK / 8, wave, kWaves, lane,
                [&](int rho) { return F + static_cast<int64_t>(c.n0 + row_of_lds(rho)) * K; });
+      if (K != 32 * KCH) {  // columns K .. K + 15 of every LDS row: the step past an odd multiple of 16
+        for (int i = tid; i < 2 * CN; i += kThreads)
+          *reinterpret_cast<uint4*>(Fs + (i >> 1) * LDK + K + 8 * (i & 1)) = make_uint4(0, 0, 0, 0);
+      }
       if (tid < CN / 8) {
         const uint4 v = add_mu ? *reinterpret_cast<const uint4*>(mu + c.n0 + 8 * tid)
                                : make_uint4(0, 0, 0, 0);
@@ -423,13 +436,13 @@ hipError_t launch_decode_bf16(int nhg, const GemmParams& p, hipStream_t stream, 
     if (p.jobs[i].k != rank || ((p.jobs[i].flags & kRopeOut) != 0) != rope)
       return hipErrorInvalidValue;
   const int cn = 128 * nhg;
-  if (rank % 32 != 0 || rank < 32 || rank > 256 || p.n_seqs > kMaxLdsSeqs || p.n_jobs < 1 ||
+  if (rank % 16 != 0 || rank < 16 || rank > 256 || p.n_seqs > kMaxLdsSeqs || p.n_jobs < 1 ||
       p.jobs[0].n % cn != 0)
     return hipErrorInvalidValue;
   for (int i = 1; i < p.n_jobs; ++i)
     if (p.jobs[i].n != p.jobs[0].n) return hipErrorInvalidValue;
-  const size_t lds = decode_bf16_lds_bytes(nhg, rank, p.head_dim);
-  const int kch = rank / 32;
+  const int kch = (rank + 31) / 32;
+  const size_t lds = decode_bf16_lds_bytes(nhg, 32 * kch, p.head_dim);
   // one round of workgroups: as many as the compute units hold at once (LDS and the two waves per
   // SIMD the kernel is built for), in whole sets of channel-chunk siblings, at most one set per
   // row tile

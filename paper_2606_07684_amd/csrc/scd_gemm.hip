@@ -7,13 +7,21 @@
 //   patch   A = H_hat [T, d_model]  B = W_K|W_V [D, d]   epilogue + bias, RoPE on keys
 //   encode  A = K|V  [T*g, w]       B = W_enc [r, w]     prologue deRoPE on keys, - mu
 //
-// Workgroup: 256 threads (2 x 2 waves), a 128 x 128 tile of C, K consumed 32 at a time through
-// double-buffered LDS.  bf16 uses v_mfma_f32_16x16x32_bf16, fp32 uses v_mfma_f32_16x16x4_f32,
-// both accumulating in fp32.  Each 32-wide K chunk is two 16-wide pieces; when A needs deRoPE
-// the second piece is the first one's RoPE partner (columns i and i + d_h/2 of one head), so a
-// thread holds both members of every pair it rotates.  Both operands use the same piece order,
-// so the contraction is unchanged.  The epilogue goes through LDS so that RoPE pairs meet in one
-// thread and every global store is a 16-byte vector.
+// A wave computes 32 x 64 or 32 x 32 outputs with both operands read straight from the caches into
+// registers, one step ahead of use: no LDS staging and no barriers, so waves never wait for each
+// other.  bf16 uses v_mfma_f32_16x16x32_bf16, fp32 v_mfma_f32_16x16x4_f32, both accumulating in fp32.
+// The B rows (output columns) are the MFMA's first operand, so a lane ends with four consecutive
+// outputs of one row (eight over two blocks) and stores them as one vector.  A lane holds 16 bytes of
+// a row per block, so a load covers 16 rows x 64 bytes.  When the input needs deRoPE a step's two
+// blocks are columns i and i + d_h/2 of one head; when the output is rotated a wave's column blocks are
+// heads' first halves and their partners: every RoPE pair meets in one lane's registers.
+//
+// The shape follows the launch (generic_shape): four waves along the rows when there are enough of
+// them to fill the chip; else one tile per workgroup whose waves split the contraction (their sums meet
+// in LDS, added in wave order), so that short prefixes and thin codes do not wait on one wave's chain
+// of loads.  fp32 is bound by the MFMA rate (32 cycles per 16 x 16 x 4), small launches by latency:
+// the smallest model's codec (512 tokens, 4 layers) takes 32 us in four launches; on 128 x 128 tiles
+// through LDS it took 193 us, three quarters of each 32-code tile computed for nothing.
 #include <type_traits>
 
 #include "scd_kernels.h"
@@ -58,9 +66,9 @@ __device__ inline int64_t table_row(const GemmParams& p, int64_t pos) {
 template <bool BF16> struct Elem;
 template <> struct Elem<true> {
   using T = uint16_t;
-  static constexpr int kVecs = 1;  // 16-byte vectors per 8 elements
-  __device__ static inline void unpack(const uint4* v, float* f) {
-    const uint32_t w[4] = {v[0].x, v[0].y, v[0].z, v[0].w};
+  static constexpr int kLane = 8;  // elements of a 16-byte vector
+  __device__ static inline void unpack(const uint4& v, float* f) {
+    const uint32_t w[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       f[2 * i] = __uint_as_float(w[i] << 16);
@@ -70,11 +78,9 @@ template <> struct Elem<true> {
   __device__ static inline uint32_t bits(float f) {
     return static_cast<uint32_t>(__builtin_bit_cast(uint16_t, static_cast<__bf16>(f)));
   }
-  __device__ static inline void pack(const float* f, uint4* v) {
-    v[0].x = bits(f[0]) | (bits(f[1]) << 16);
-    v[0].y = bits(f[2]) | (bits(f[3]) << 16);
-    v[0].z = bits(f[4]) | (bits(f[5]) << 16);
-    v[0].w = bits(f[6]) | (bits(f[7]) << 16);
+  __device__ static inline uint4 pack(const float* f) {
+    return make_uint4(bits(f[0]) | (bits(f[1]) << 16), bits(f[2]) | (bits(f[3]) << 16),
+                      bits(f[4]) | (bits(f[5]) << 16), bits(f[6]) | (bits(f[7]) << 16));
   }
   __device__ static inline float load1(const void* p, int64_t i) {
     return __uint_as_float(static_cast<uint32_t>(static_cast<const uint16_t*>(p)[i]) << 16);
@@ -82,24 +88,16 @@ template <> struct Elem<true> {
 };
 template <> struct Elem<false> {
   using T = float;
-  static constexpr int kVecs = 2;
-  __device__ static inline void unpack(const uint4* v, float* f) {
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      f[4 * i] = __uint_as_float(v[i].x);
-      f[4 * i + 1] = __uint_as_float(v[i].y);
-      f[4 * i + 2] = __uint_as_float(v[i].z);
-      f[4 * i + 3] = __uint_as_float(v[i].w);
-    }
+  static constexpr int kLane = 4;
+  __device__ static inline void unpack(const uint4& v, float* f) {
+    f[0] = __uint_as_float(v.x);
+    f[1] = __uint_as_float(v.y);
+    f[2] = __uint_as_float(v.z);
+    f[3] = __uint_as_float(v.w);
   }
-  __device__ static inline void pack(const float* f, uint4* v) {
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      v[i].x = __float_as_uint(f[4 * i]);
-      v[i].y = __float_as_uint(f[4 * i + 1]);
-      v[i].z = __float_as_uint(f[4 * i + 2]);
-      v[i].w = __float_as_uint(f[4 * i + 3]);
-    }
+  __device__ static inline uint4 pack(const float* f) {
+    return make_uint4(__float_as_uint(f[0]), __float_as_uint(f[1]), __float_as_uint(f[2]),
+                      __float_as_uint(f[3]));
   }
   __device__ static inline float load1(const void* p, int64_t i) {
     return static_cast<const float*>(p)[i];
@@ -113,161 +111,138 @@ struct EncodeKV {};
 struct EncodeH {};
 struct PatchAlign {};
 
-template <typename OP, bool BF16, int BM, int BN, int WM, int WN>
-__global__ __launch_bounds__(WM * WN * 64) void gemm_nt_kernel(GemmParams p) {
+// Four consecutive outputs of one row.
+template <bool BF16>
+__device__ inline void store4(void* base, int64_t i, const float* f) {
+  if constexpr (BF16) {
+    uint2 v;
+    v.x = Elem<true>::bits(f[0]) | (Elem<true>::bits(f[1]) << 16);
+    v.y = Elem<true>::bits(f[2]) | (Elem<true>::bits(f[3]) << 16);
+    *reinterpret_cast<uint2*>(static_cast<uint16_t*>(base) + i) = v;
+  } else {
+    *reinterpret_cast<float4*>(static_cast<float*>(base) + i) = make_float4(f[0], f[1], f[2], f[3]);
+  }
+}
+
+// Eight consecutive outputs of one row.
+template <bool BF16>
+__device__ inline void store8(void* base, int64_t i, const float* f, const float* g) {
+  if constexpr (BF16) {
+    const float y[8] = {f[0], f[1], f[2], f[3], g[0], g[1], g[2], g[3]};
+    *reinterpret_cast<uint4*>(static_cast<uint16_t*>(base) + i) = Elem<true>::pack(y);
+  } else {
+    store4<false>(base, i, f);
+    store4<false>(base, i + 4, g);
+  }
+}
+
+template <typename OP, bool BF16, int FM, int FN, int WM, int WK>
+__global__ __launch_bounds__(WM * WK * 64, 2) void gemm_nt_kernel(GemmParams p) {
   using EL = Elem<BF16>;
   using T = typename EL::T;
-  constexpr int BK = 32;
-  constexpr int NT = WM * WN * 64;
-  constexpr int NV = EL::kVecs;
-  constexpr int LDK = BK + 16 / static_cast<int>(sizeof(T));  // LDS row, padded by 16 bytes
-  constexpr int WTM = BM / WM, WTN = BN / WN;
-  constexpr int FM = WTM / 16, FN = WTN / 16;
-  constexpr int LDC = BN + 4;
-  constexpr int TPA = (BM * 2) / NT, TPB = (BN * 2) / NT;
-  static_assert(TPA * NT == BM * 2 && TPB * NT == BN * 2, "loader split");
-  constexpr size_t kAB = 2u * (BM + BN) * LDK * sizeof(T);
-  constexpr size_t kC = static_cast<size_t>(BM) * LDC * sizeof(float);
-  constexpr size_t kSmem = kAB > kC ? kAB : kC;
+  constexpr int VL = EL::kLane;  // contraction elements a lane holds of a block (16 bytes)
+  constexpr int KB = 4 * VL;     // contraction of a block
+  constexpr int BM = 16 * FM * WM, BN = 16 * FN, FP = FN / 2;
+  constexpr bool kEnc = std::is_same<OP, EncodeKV>::value;  // the only step with an input prologue
+  static_assert(FN % 2 == 0 && (WK == 1 || (WM == 1 && FM <= WK)), "block split");
+  extern __shared__ __attribute__((aligned(16))) float4 red[];  // [WK][FM][FN][64] when WK > 1
 
-  __shared__ __attribute__((aligned(16))) unsigned char smem[kSmem];
-  __shared__ int s_pos[BM];
-  T* As = reinterpret_cast<T*>(smem);
-  T* Bs = As + 2 * BM * LDK;
-  float* Cs = reinterpret_cast<float*>(smem);
-
-  const int tid = threadIdx.x;
-  const int lane = tid & 63;
-  const int wave = tid >> 6;
-  const int wm = wave / WN, wn = wave % WN;
+  const int lane = threadIdx.x & 63, lr = lane & 15, lq = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wk = WK > 1 ? wave : 0, wm = WK > 1 ? 0 : wave;
 
   const int bid = xcd_remap(blockIdx.x, gridDim.x);
   int j = 0;
   while (j + 1 < p.n_jobs && bid >= p.jobs[j + 1].tile_begin) ++j;
   const GemmJob job = p.jobs[j];
   const int local = bid - job.tile_begin;
-  const int ntn = (job.n + BN - 1) / BN;
-  const int64_t m0 = static_cast<int64_t>(local / ntn) * BM;
+  const int K = job.k, N = job.n;
+  const int64_t M = p.m;
+  const int ntn = (N + BN - 1) / BN;
+  const int64_t m0 = static_cast<int64_t>(local / ntn) * BM + wm * 16 * FM;
   const int n0 = (local % ntn) * BN;
-  const bool derope = (job.flags & kDeropeIn) != 0;
+  const bool derope = kEnc && (job.flags & kDeropeIn) != 0;
+  const bool vec_in = kEnc && (job.flags & kVecIn) != 0 && job.vec != nullptr;
   const bool rope_out = (job.flags & kRopeOut) != 0;
-  const bool vec_in = (job.flags & kVecIn) != 0 && job.vec != nullptr;
   const bool vec_out = (job.flags & kVecOut) != 0 && job.vec != nullptr;
   const bool silu_out = (job.flags & kSiluOut) != 0;
   const int dh = p.head_dim, half = dh / 2;
-  const int K = job.k, N = job.n;
-  const int64_t M = p.m;
-  const int nk = (K + BK - 1) / BK;
-  const int heads_in_row = K / dh;
-  const T* A = static_cast<const T*>(job.a);
-  const T* B = static_cast<const T*>(job.b);
 
-  if (derope || rope_out) {
-    for (int r = tid; r < BM; r += NT) s_pos[r] = static_cast<int>(row_position(p, m0 + r));
+  // Output columns: a lane's outputs of blocks 2q and 2q + 1 are the eight columns 8 (l / 16) + (0..7)
+  // of a 32-column group (first column of the group: group_of), so that a bf16 store is 16 bytes.
+  // When the output is rotated the first FN / 4 groups are columns of heads' first halves and the rest
+  // their partners.  Two blocks, or heads of 32: single 16-column blocks instead (first column:
+  // block_of).  -1: past the last column.
+  const bool wide = FN == 4 && (!rope_out || half >= 32);
+  auto group_of = [&](int q) {
+    if (!rope_out) return n0 + 32 * q;
+    const int per = half / 32, b = n0 / 64 + q % (FN / 4 > 0 ? FN / 4 : 1);
+    return (b / per) * dh + (b % per) * 32 + (q / (FN / 4 > 0 ? FN / 4 : 1)) * half;
+  };
+  auto block_of = [&](int b) {
+    if (!rope_out) return n0 + 16 * b;
+    const int q = n0 / 32 + b % FP, per = half / 16;  // pair block, pair blocks per head
+    return (q / per) * dh + (q % per) * 16 + (b / FP) * half;
+  };
+  // first of this lane's four columns of block b
+  auto col_of = [&](int b) {
+    const int c = wide ? group_of(b >> 1) + 8 * lq + 4 * (b & 1) : block_of(b) + 4 * lq;
+    return c < N ? c : -1;
+  };
+  // rows past the ends read the last one (their results are never stored)
+  const T* xrow[FM];
+  const T* wrow[FN];
+  const float2* csrow[FM];
+#pragma unroll
+  for (int a = 0; a < FM; ++a) {
+    const int64_t m = m0 + 16 * a + lr < M ? m0 + 16 * a + lr : M - 1;
+    xrow[a] = static_cast<const T*>(job.a) + m * K;
+    if constexpr (kEnc) csrow[a] = derope ? p.rope + table_row(p, row_position(p, m)) * half : nullptr;
   }
-  __syncthreads();
+#pragma unroll
+  for (int b = 0; b < FN; ++b) {
+    const int c = wide ? group_of(b >> 1) + 8 * (lr >> 2) + 4 * (b & 1) + (lr & 3) : block_of(b) + lr;
+    wrow[b] = static_cast<const T*>(job.b) + static_cast<int64_t>(c < N ? c : 0) * K;
+  }
 
-  auto bases = [&](int kc, int& b0, int& b1) {
+  struct Step {
+    uint4 x[FM][2], w[FN][2];
+    float4 cs[kEnc ? FM : 1][kEnc ? VL / 2 : 1];
+  };
+  // This lane's contraction columns of step i: two blocks, or with deRoPE a block of first halves and
+  // their partners.  Both operands take the same columns, so the order does not matter.
+  const int hmask = half - 1;  // d_h is a power of two
+  auto cols = [&](int i, int& c0, int& c1) {
+    const int t = i * KB + VL * lq;
     if (derope) {
-      const int o = kc / heads_in_row, h = kc % heads_in_row;
-      b0 = h * dh + o * 16;
-      b1 = b0 + half;
+      c0 = 2 * (t & ~hmask) + (t & hmask);
+      c1 = c0 + half;
     } else {
-      b0 = kc * BK;
-      b1 = b0 + 16;
+      c0 = t + i * KB;
+      c1 = c0 + KB;
     }
   };
-
-  uint4 ra[TPA][2][NV], rb[TPB][2][NV];
-  const uint4 zero = make_uint4(0, 0, 0, 0);
-
-  auto gload = [&](int kc) {
-    int b0, b1;
-    bases(kc, b0, b1);
+  auto load = [&](int i, Step& s) {
+    int c0, c1;
+    cols(i, c0, c1);
+    // columns past the end read the row's first ones and are replaced by zero when used
+    const int d0 = c0 < K ? c0 : 0, d1 = c1 < K ? c1 : 0;
 #pragma unroll
-    for (int t = 0; t < TPA; ++t) {
-      const int task = tid + t * NT, row = task >> 1, q = task & 1;
-      const int64_t gr = m0 + row;
-#pragma unroll
-      for (int pc = 0; pc < 2; ++pc) {
-        const int col = (pc ? b1 : b0) + 8 * q;
-        const bool ok = gr < M && col < K;
-        // out-of-range pieces read an in-bounds address and are replaced by zero
-        const uint4* src = reinterpret_cast<const uint4*>(A + (ok ? gr * K + col : 0));
-#pragma unroll
-        for (int v = 0; v < NV; ++v) {
-          const uint4 x = src[v];
-          ra[t][pc][v] = ok ? x : zero;
-        }
-      }
-    }
-#pragma unroll
-    for (int t = 0; t < TPB; ++t) {
-      const int task = tid + t * NT, row = task >> 1, q = task & 1;
-      const int gn = n0 + row;
-#pragma unroll
-      for (int pc = 0; pc < 2; ++pc) {
-        const int col = (pc ? b1 : b0) + 8 * q;
-        const bool ok = gn < N && col < K;
-        const uint4* src =
-            reinterpret_cast<const uint4*>(B + (ok ? static_cast<int64_t>(gn) * K + col : 0));
-#pragma unroll
-        for (int v = 0; v < NV; ++v) {
-          const uint4 x = src[v];
-          rb[t][pc][v] = ok ? x : zero;
-        }
-      }
-    }
-  };
-
-  auto sstore = [&](int kc, int buf) {
-    int b0, b1;
-    bases(kc, b0, b1);
-#pragma unroll
-    for (int t = 0; t < TPA; ++t) {
-      const int task = tid + t * NT, row = task >> 1, q = task & 1;
-      uint4* d0 = reinterpret_cast<uint4*>(As + (buf * BM + row) * LDK + 8 * q);
-      uint4* d1 = reinterpret_cast<uint4*>(As + (buf * BM + row) * LDK + 16 + 8 * q);
-      if (derope || vec_in) {
-        float u[8], v[8];
-        EL::unpack(ra[t][0], u);
-        EL::unpack(ra[t][1], v);
+    for (int a = 0; a < FM; ++a) {
+      s.x[a][0] = *reinterpret_cast<const uint4*>(xrow[a] + d0);
+      s.x[a][1] = *reinterpret_cast<const uint4*>(xrow[a] + d1);
+      if constexpr (kEnc) {
         if (derope) {
-          const int i0 = (b0 % dh) + 8 * q;
-          const float2* cs = p.rope + table_row(p, s_pos[row]) * half + i0;
+          const float4* cs = reinterpret_cast<const float4*>(csrow[a] + (d0 & hmask));
 #pragma unroll
-          for (int e = 0; e < 8; ++e) {
-            const float2 c = cs[e];
-            const float uu = u[e], vv = v[e];
-            u[e] = uu * c.x + vv * c.y;
-            v[e] = vv * c.x - uu * c.y;
-          }
+          for (int e = 0; e < VL / 2; ++e) s.cs[a][e] = cs[e];
         }
-        if (vec_in) {
-#pragma unroll
-          for (int e = 0; e < 8; ++e) {
-            const int c0 = b0 + 8 * q + e, c1 = b1 + 8 * q + e;
-            if (c0 < K) u[e] -= EL::load1(job.vec, c0);
-            if (c1 < K) v[e] -= EL::load1(job.vec, c1);
-          }
-        }
-        uint4 o0[NV], o1[NV];
-        EL::pack(u, o0);
-        EL::pack(v, o1);
-#pragma unroll
-        for (int w = 0; w < NV; ++w) { d0[w] = o0[w]; d1[w] = o1[w]; }
-      } else {
-#pragma unroll
-        for (int w = 0; w < NV; ++w) { d0[w] = ra[t][0][w]; d1[w] = ra[t][1][w]; }
       }
     }
 #pragma unroll
-    for (int t = 0; t < TPB; ++t) {
-      const int task = tid + t * NT, row = task >> 1, q = task & 1;
-      uint4* d0 = reinterpret_cast<uint4*>(Bs + (buf * BN + row) * LDK + 8 * q);
-      uint4* d1 = reinterpret_cast<uint4*>(Bs + (buf * BN + row) * LDK + 16 + 8 * q);
-#pragma unroll
-      for (int w = 0; w < NV; ++w) { d0[w] = rb[t][0][w]; d1[w] = rb[t][1][w]; }
+    for (int b = 0; b < FN; ++b) {
+      s.w[b][0] = *reinterpret_cast<const uint4*>(wrow[b] + d0);
+      s.w[b][1] = *reinterpret_cast<const uint4*>(wrow[b] + d1);
     }
   };
 
@@ -277,136 +252,163 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_nt_kernel(GemmParams p) {
 #pragma unroll
     for (int b = 0; b < FN; ++b) acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-  const int lr = lane & 15, lk = (lane >> 4) * 8;
-  auto compute = [&](int buf) {
-    const T* Ab = As + buf * BM * LDK;
-    const T* Bb = Bs + buf * BN * LDK;
-    if constexpr (BF16) {
-      bf16x8 af[FM], bfr[FN];
+  auto compute = [&](int i, Step& s) {
+    int c[2];
+    cols(i, c[0], c[1]);
+    if constexpr (kEnc) {
+      if (derope || vec_in) {
+        float mu[2][VL];
 #pragma unroll
-      for (int a = 0; a < FM; ++a)
-        af[a] = *reinterpret_cast<const bf16x8*>(Ab + (wm * WTM + a * 16 + lr) * LDK + lk);
+        for (int h = 0; h < 2; ++h)
 #pragma unroll
-      for (int b = 0; b < FN; ++b)
-        bfr[b] = *reinterpret_cast<const bf16x8*>(Bb + (wn * WTN + b * 16 + lr) * LDK + lk);
+          for (int e = 0; e < VL; ++e) mu[h][e] = 0.f;
+        if (vec_in) {
 #pragma unroll
-      for (int a = 0; a < FM; ++a)
+          for (int h = 0; h < 2; ++h) {
+            const uint4 v = *reinterpret_cast<const uint4*>(static_cast<const T*>(job.vec) +
+                                                            (c[h] < K ? c[h] : 0));
+            EL::unpack(v, mu[h]);
+          }
+        }
 #pragma unroll
-        for (int b = 0; b < FN; ++b)
-          acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[a], bfr[b], acc[a][b], 0, 0, 0);
-    } else {
-      float af[FM][8], bfr[FN][8];
+        for (int a = 0; a < FM; ++a) {
+          float u[VL], v[VL];
+          EL::unpack(s.x[a][0], u);
+          EL::unpack(s.x[a][1], v);
+          if (derope) {
+            const float* cs = reinterpret_cast<const float*>(s.cs[a]);
 #pragma unroll
-      for (int a = 0; a < FM; ++a) {
-        const float4* s = reinterpret_cast<const float4*>(Ab + (wm * WTM + a * 16 + lr) * LDK + lk);
-        const float4 x0 = s[0], x1 = s[1];
-        af[a][0] = x0.x; af[a][1] = x0.y; af[a][2] = x0.z; af[a][3] = x0.w;
-        af[a][4] = x1.x; af[a][5] = x1.y; af[a][6] = x1.z; af[a][7] = x1.w;
+            for (int e = 0; e < VL; ++e) {
+              const float uu = u[e], vv = v[e];
+              u[e] = uu * cs[2 * e] + vv * cs[2 * e + 1];
+              v[e] = vv * cs[2 * e] - uu * cs[2 * e + 1];
+            }
+          }
+#pragma unroll
+          for (int e = 0; e < VL; ++e) {
+            u[e] -= mu[0][e];
+            v[e] -= mu[1][e];
+          }
+          s.x[a][0] = EL::pack(u);
+          s.x[a][1] = EL::pack(v);
+        }
       }
+    }
 #pragma unroll
-      for (int b = 0; b < FN; ++b) {
-        const float4* s = reinterpret_cast<const float4*>(Bb + (wn * WTN + b * 16 + lr) * LDK + lk);
-        const float4 x0 = s[0], x1 = s[1];
-        bfr[b][0] = x0.x; bfr[b][1] = x0.y; bfr[b][2] = x0.z; bfr[b][3] = x0.w;
-        bfr[b][4] = x1.x; bfr[b][5] = x1.y; bfr[b][6] = x1.z; bfr[b][7] = x1.w;
-      }
+    for (int h = 0; h < 2; ++h) {
+      const bool ok = c[h] < K;
+      const uint4 zero = make_uint4(0, 0, 0, 0);
+      uint4 x[FM], w[FN];
 #pragma unroll
-      for (int e = 0; e < 8; ++e)
+      for (int a = 0; a < FM; ++a) x[a] = ok ? s.x[a][h] : zero;
+#pragma unroll
+      for (int b = 0; b < FN; ++b) w[b] = ok ? s.w[b][h] : zero;
+      if constexpr (BF16) {
 #pragma unroll
         for (int a = 0; a < FM; ++a)
 #pragma unroll
           for (int b = 0; b < FN; ++b)
-            acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x4f32(af[a][e], bfr[b][e], acc[a][b], 0, 0, 0);
+            acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                __builtin_bit_cast(bf16x8, w[b]), __builtin_bit_cast(bf16x8, x[a]), acc[a][b], 0, 0, 0);
+      } else {
+#pragma unroll
+        for (int e = 0; e < VL; ++e)
+#pragma unroll
+          for (int a = 0; a < FM; ++a)
+#pragma unroll
+            for (int b = 0; b < FN; ++b)
+              acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x4f32(
+                  __builtin_bit_cast(f32x4, w[b])[e], __builtin_bit_cast(f32x4, x[a])[e], acc[a][b],
+                  0, 0, 0);
+      }
     }
   };
 
-  if (nk > 0) {
-    gload(0);
-    sstore(0, 0);
-    __syncthreads();
-    for (int kc = 0; kc < nk; ++kc) {
-      const int cur = kc & 1;
-      if (kc + 1 < nk) gload(kc + 1);
-      compute(cur);
-      if (kc + 1 < nk) sstore(kc + 1, cur ^ 1);
-      __syncthreads();
+  // steps wk, wk + WK, ...; each step's operands are loaded during the one before
+  const int steps = (K + 2 * KB - 1) / (2 * KB);
+  {
+    Step s0, s1;
+    int i = wk;
+    if (i < steps) load(i, s0);
+    for (; i < steps; i += 2 * WK) {
+      if (i + WK < steps) load(i + WK, s1);
+      compute(i, s0);
+      if (i + WK >= steps) break;
+      if (i + 2 * WK < steps) load(i + 2 * WK, s0);
+      compute(i + WK, s1);
     }
   }
 
-  // Accumulators -> LDS (fp32).  MFMA output: lane holds column lane%16, rows 4*(lane/16)+e.
+  // Lane holds, for blocks (a, b), row 16 a + lane % 16 and columns col_of(b) + (0..3).
+  auto finish = [&](int a, const f32x4* y) {
+    const int64_t m = m0 + 16 * a + lr;
+    if (m >= M) return;
+    float f[FN][4];
 #pragma unroll
-  for (int a = 0; a < FM; ++a)
-#pragma unroll
-    for (int b = 0; b < FN; ++b)
+    for (int b = 0; b < FN; ++b) {
+      const int c = col_of(b);
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        const int row = wm * WTM + a * 16 + 4 * (lane >> 4) + e;
-        const int col = wn * WTN + b * 16 + (lane & 15);
-        Cs[row * LDC + col] = acc[a][b][e];
+        f[b][e] = y[b][e];
+        if (vec_out && c >= 0) f[b][e] += EL::load1(job.vec, c + e);
       }
-  __syncthreads();
-
-  T* C = static_cast<T*>(job.c);
-  if (rope_out) {
-    const int gph = dh / 16;          // 8-wide groups in half a head
-    constexpr int GPR = BN / 16;      // pair groups per tile row
-    for (int task = tid; task < BM * GPR; task += NT) {
-      const int row = task / GPR, cg = task % GPR;
-      const int o = (cg % gph) * 8;
-      const int c0 = (cg / gph) * dh + o, c1 = c0 + half;
-      const int64_t gm = m0 + row;
-      const int gc0 = n0 + c0, gc1 = n0 + c1;
-      if (gm >= M || gc0 >= N) continue;
-      float u[8], v[8];
+    }
+    if (rope_out) {
+      const float2* cs = p.rope + table_row(p, row_position(p, m)) * half;
 #pragma unroll
-      for (int e = 0; e < 8; ++e) { u[e] = Cs[row * LDC + c0 + e]; v[e] = Cs[row * LDC + c1 + e]; }
-      if (vec_out) {
+      for (int b = 0; b < FP; ++b) {
+        const int c = col_of(b);
+        if (c < 0) continue;
+        const float4* q = reinterpret_cast<const float4*>(cs + (c & hmask));
+        const float4 q0 = q[0], q1 = q[1];
+        const float co[4] = {q0.x, q0.z, q1.x, q1.z}, si[4] = {q0.y, q0.w, q1.y, q1.w};
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          u[e] += EL::load1(job.vec, gc0 + e);
-          v[e] += EL::load1(job.vec, gc1 + e);
+        for (int e = 0; e < 4; ++e) {
+          const float u = f[b][e], v = f[b + FP][e];
+          f[b][e] = u * co[e] - v * si[e];
+          f[b + FP][e] = v * co[e] + u * si[e];
         }
       }
-      const float2* cs = p.rope + table_row(p, s_pos[row]) * half + o;
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        const float2 c = cs[e];
-        const float uu = u[e], vv = v[e];
-        u[e] = uu * c.x - vv * c.y;
-        v[e] = vv * c.x + uu * c.y;
-      }
-      uint4 o0[NV], o1[NV];
-      EL::pack(u, o0);
-      EL::pack(v, o1);
-      uint4* d0 = reinterpret_cast<uint4*>(C + gm * N + gc0);
-      uint4* d1 = reinterpret_cast<uint4*>(C + gm * N + gc1);
-#pragma unroll
-      for (int w = 0; w < NV; ++w) { d0[w] = o0[w]; d1[w] = o1[w]; }
     }
-  } else {
-    constexpr int GPR = BN / 8;
-    for (int task = tid; task < BM * GPR; task += NT) {
-      const int row = task / GPR, c0 = (task % GPR) * 8;
-      const int64_t gm = m0 + row;
-      const int gc0 = n0 + c0;
-      if (gm >= M || gc0 >= N) continue;
-      float u[8];
 #pragma unroll
-      for (int e = 0; e < 8; ++e) u[e] = Cs[row * LDC + c0 + e];
-      if (vec_out) {
-#pragma unroll
-        for (int e = 0; e < 8; ++e) u[e] += EL::load1(job.vec, gc0 + e);
-      }
+    for (int b = 0; b < FN; ++b) {
+      const int c = col_of(b);
+      if (c < 0) continue;
       if (silu_out) {
 #pragma unroll
-        for (int e = 0; e < 8; ++e) u[e] = u[e] / (1.f + expf(-u[e]));
+        for (int e = 0; e < 4; ++e) f[b][e] = f[b][e] / (1.f + expf(-f[b][e]));
       }
-      uint4 o0[NV];
-      EL::pack(u, o0);
-      uint4* d0 = reinterpret_cast<uint4*>(C + gm * N + gc0);
-#pragma unroll
-      for (int w = 0; w < NV; ++w) d0[w] = o0[w];
+      if constexpr (FN == 4) {
+        if (wide && (b & 1) == 0) continue;  // stored with the next block's
+        if (wide) {
+          store8<BF16>(job.c, m * N + c - 4, f[b - (b & 1)], f[b]);
+          continue;
+        }
+      }
+      store4<BF16>(job.c, m * N + c, f[b]);
     }
+  };
+  if constexpr (WK == 1) {
+#pragma unroll
+    for (int a = 0; a < FM; ++a) finish(a, acc[a]);
+  } else {
+    // the waves' partial sums, added in wave order; wave a finishes row block a
+#pragma unroll
+    for (int a = 0; a < FM; ++a)
+#pragma unroll
+      for (int b = 0; b < FN; ++b)
+        red[((wk * FM + a) * FN + b) * 64 + lane] = __builtin_bit_cast(float4, acc[a][b]);
+    __syncthreads();
+    if (wk >= FM) return;
+    f32x4 y[FN];
+#pragma unroll
+    for (int b = 0; b < FN; ++b) {
+      y[b] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int w = 0; w < WK; ++w)
+        y[b] += __builtin_bit_cast(f32x4, red[((w * FM + wk) * FN + b) * 64 + lane]);
+    }
+    finish(wk, y);
   }
 }
 
@@ -443,26 +445,68 @@ __global__ void positions_kernel(int32_t* out, int64_t n_tokens, int32_t n_seqs,
 
 }  // namespace
 
-template <typename OP, bool BF16>
+// Short contractions (the decode, thin head-shared encodes) are a load, a few MFMAs and a store per
+// wave: 32 x 32 waves, more of them in flight (bf16 decode of 64-wide heads' shared basis, 8192 tokens
+// x 14 layers: 254 us, 310 us as 32 x 64).  Longer ones take 32 x 64 waves, four to a workgroup once
+// they give every SIMD one; below that the contraction is split so that the chip still has waves to
+// run.  fp32, us on 128x64 / 32x64 split by 4 / 32x32 split by 8: encode of 4099 tokens x 8 layers
+// (w = 512, 64 codes) 122 / 93 / 141; encode and Patch of 512 tokens x 4 layers 90 / 36 / 24; codec of
+// 12,000 tokens x 24 layers 2140 / 3700 / 5400 (128 x 128 tiles through LDS took 3490).
+GenericShape generic_shape(const GemmJob* jobs, size_t n_jobs, int64_t m) {
+  int64_t waves = 0;  // of 32 x 64 outputs
+  int k = 0;
+  for (size_t i = 0; i < n_jobs; ++i) {
+    waves += (m + 31) / 32 * ((jobs[i].n + 63) / 64);
+    k = jobs[i].k > k ? jobs[i].k : k;
+  }
+  if (k <= 128) return GenericShape::k128x32;
+  if (waves >= 1024) return GenericShape::k128x64;
+  return waves >= 256 ? GenericShape::k32x64 : GenericShape::k32x32;
+}
+
+int generic_rows(GenericShape s) {
+  constexpr int rows[] = {128, 128, 32, 32};
+  return rows[static_cast<int>(s)];
+}
+
+int generic_cols(GenericShape s) {
+  constexpr int cols[] = {64, 32, 64, 32};
+  return cols[static_cast<int>(s)];
+}
+
+template <typename OP, bool BF16, int FM, int FN, int WM, int WK>
 hipError_t launch_one(const GemmParams& p, hipStream_t stream) {
-  hipLaunchKernelGGL((gemm_nt_kernel<OP, BF16, kGenericBM, kGenericBN, 2, 2>),
-                     dim3(p.total_tiles), dim3(256), 0, stream, p);
+  const size_t lds = WK > 1 ? static_cast<size_t>(WK) * FM * FN * 64 * sizeof(float4) : 0;
+  hipLaunchKernelGGL((gemm_nt_kernel<OP, BF16, FM, FN, WM, WK>), dim3(p.total_tiles),
+                     dim3(64 * WM * WK), lds, stream, p);
   return hipGetLastError();
 }
 
-template <typename OP>
-hipError_t launch_op(bool bf16, const GemmParams& p, hipStream_t stream) {
-  return bf16 ? launch_one<OP, true>(p, stream) : launch_one<OP, false>(p, stream);
+template <typename OP, bool BF16>
+hipError_t launch_shape(GenericShape shape, const GemmParams& p, hipStream_t stream) {
+  switch (shape) {
+    case GenericShape::k128x64: return launch_one<OP, BF16, 2, 4, 4, 1>(p, stream);
+    case GenericShape::k128x32: return launch_one<OP, BF16, 2, 2, 4, 1>(p, stream);
+    case GenericShape::k32x64: return launch_one<OP, BF16, 2, 4, 1, 4>(p, stream);
+    case GenericShape::k32x32: return launch_one<OP, BF16, 2, 2, 1, 8>(p, stream);
+  }
+  return hipErrorInvalidValue;
 }
 
-hipError_t launch_gemm(Op op, bool bf16, const GemmParams& p, hipStream_t stream) {
+template <typename OP>
+hipError_t launch_op(bool bf16, GenericShape shape, const GemmParams& p, hipStream_t stream) {
+  return bf16 ? launch_shape<OP, true>(shape, p, stream) : launch_shape<OP, false>(shape, p, stream);
+}
+
+hipError_t launch_gemm(Op op, bool bf16, GenericShape shape, const GemmParams& p,
+                       hipStream_t stream) {
   if (p.total_tiles <= 0) return hipSuccess;
   switch (op) {
-    case Op::kReuseDecode: return launch_op<ReuseDecode>(bf16, p, stream);
-    case Op::kPatchKV: return launch_op<PatchKV>(bf16, p, stream);
-    case Op::kEncodeKV: return launch_op<EncodeKV>(bf16, p, stream);
-    case Op::kEncodeH: return launch_op<EncodeH>(bf16, p, stream);
-    case Op::kPatchAlign: return launch_op<PatchAlign>(bf16, p, stream);
+    case Op::kReuseDecode: return launch_op<ReuseDecode>(bf16, shape, p, stream);
+    case Op::kPatchKV: return launch_op<PatchKV>(bf16, shape, p, stream);
+    case Op::kEncodeKV: return launch_op<EncodeKV>(bf16, shape, p, stream);
+    case Op::kEncodeH: return launch_op<EncodeH>(bf16, shape, p, stream);
+    case Op::kPatchAlign: return launch_op<PatchAlign>(bf16, shape, p, stream);
   }
   return hipErrorInvalidValue;
 }

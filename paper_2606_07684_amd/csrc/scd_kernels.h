@@ -48,16 +48,20 @@ struct GemmParams {
 };
 static_assert(sizeof(GemmParams) <= 4096, "kernel argument block");
 
-// Tile shape of the generic launcher (rows x columns of C per workgroup).
-constexpr int kGenericBM = 128;
-constexpr int kGenericBN = 128;
+// Workgroup shape of a generic launch, by the rows x columns of C it computes: 4 waves of 32 x 64 or
+// 32 x 32 along the rows, or one tile whose 4 or 8 waves split the contraction.
+enum class GenericShape : int { k128x64 = 0, k128x32 = 1, k32x64 = 2, k32x32 = 3 };
+GenericShape generic_shape(const GemmJob* jobs, size_t n_jobs, int64_t m);
+int generic_rows(GenericShape s);
+int generic_cols(GenericShape s);
 
 // The codec step a launch performs; each step is its own kernel symbol so profiles attribute time
 // per step.
 enum class Op : int { kReuseDecode = 0, kPatchKV = 1, kEncodeKV = 2, kEncodeH = 3, kPatchAlign = 4 };
 
 // Launchers (return the hipError_t of the launch).
-hipError_t launch_gemm(Op op, bool bf16, const GemmParams& p, hipStream_t stream);
+hipError_t launch_gemm(Op op, bool bf16, GenericShape shape, const GemmParams& p,
+                       hipStream_t stream);
 
 // Patch on the bf16 path: square tiles (tokens x channels) of 256 or 128, d_model % 64 == 0,
 // head_dim 64 or 128, D % 128 == 0.  patch_tile picks the tile for a launch of n_jobs products
@@ -94,7 +98,7 @@ hipError_t launch_patch_fold(bool bf16, bool products, const FoldParams& p, hipS
 
 // Reuse decode on the bf16 path: workgroups own a channel chunk of 128 * nhg and a share of the
 // launch's row tiles (decode_tile_rows(nhg) rows each); basis_width % (128 * nhg) == 0, one rank
-// (% 32 == 0, <= 256) and one branch per launch, head_dim 64 or 128.
+// (% 16 == 0, <= 256) and one branch per launch, head_dim 64 or 128.
 int decode_channel_groups(int rank, int basis_width, int64_t rows, int64_t n_jobs);
 int decode_tile_rows(int nhg, int rank);  // rows per tile of the kernel instance
 // align: run the aligner's first product (jobs flagged kSiluOut, rank <= 128, no RoPE) under its

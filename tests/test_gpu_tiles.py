@@ -69,3 +69,31 @@ def test_decode_chunks(rank, tokens, layers):
     errs = U.compare_all(wl, inp, out, U.sample_tokens(wl))
     assert all(bool(torch.isfinite(t).all()) for l in inp.R for t in (out["k_cache"][l], out["v_cache"][l]))
     U.assert_within(errs, BF16_TOL, wl.name)
+
+
+# The generic kernel's workgroup shapes (fp32, and bf16 with heads of 32): enough rows for four 32 x 64
+# waves per workgroup, fewer (contraction split by 4) and few (split by 8), each with deRoPE, offsets,
+# biases and rotated output; contractions that end inside a step (ranks 16 and 48).
+@pytest.mark.parametrize("dtype,heads,head_dim", [("f32", 8, 64), ("f32", 4, 128), ("bf16", 16, 32)])
+@pytest.mark.parametrize("tokens", [(4000, 101), (970, 30), (33,)])
+def test_generic_shapes(dtype, heads, head_dim, tokens):
+    wl = W.Workload(f"generic_{dtype}_{head_dim}", 5, 160, heads, head_dim, tokens,
+                    (48, 16, 64, 64, 48), (0,), 1e4, dtype, with_bias=True,
+                    pos0=tuple(11 * i + 3 for i in range(len(tokens))), ranks_v=(16, 48, 64, 80, 16))
+    dev = torch.device("cuda")
+    inp = W.Inputs(wl, dev)
+    rope = scd.scd_rope_table(U.model_of(wl), wl.max_position)
+    out = U.run_gpu(wl, inp, rope, fill=float("nan"))
+    U.assert_within(U.compare_all(wl, inp, out), U.TOL[dtype], wl.name)
+
+
+# Ranks that are odd multiples of 16 on the bf16 decode (the contraction's last step zeroed).
+@pytest.mark.parametrize("ranks,ranks_v", [((16, 48, 80), (112, 16, 48)), ((144, 176, 208), (240, 16, 144))])
+def test_decode_odd_ranks(ranks, ranks_v):
+    wl = W.Workload(f"odd_{ranks[0]}", 3, 256, 4, 64, (300, 77), ranks, (), 5e5, "bf16",
+                    ranks_v=ranks_v)
+    dev = torch.device("cuda")
+    inp = W.Inputs(wl, dev, encode=False, patch=False)
+    rope = scd.scd_rope_table(U.model_of(wl), wl.max_position)
+    out = U.run_gpu(wl, inp, rope, which=("decode",), fill=float("nan"))
+    U.assert_within(U.compare_all(wl, inp, out), BF16_TOL, wl.name)
