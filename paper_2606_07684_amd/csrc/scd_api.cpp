@@ -362,19 +362,33 @@ scd_status_t scd_encode(const scd_model_t* model, const scd_batch_t* batch,
   }
   const scd::GemmParams kv_base = base_params(model, batch, T * g, g, rope_table, max_position);
   const scd::GemmParams h_base = base_params(model, batch, T, 1, rope_table, max_position);
-  // one launch per (rank, branch kind, offset present): each is its own kernel instance
+  // one launch per (rank, branch kind, offset present): each is its own kernel instance.  Rows whose
+  // encoder fits the LDS run with it resident, the others stream it (encode_resident).
   auto by_kind = [](const scd::GemmJob& j) {
     const bool mu = (j.flags & scd::kVecIn) != 0 && j.vec != nullptr;
     return j.n * 4 + ((j.flags & scd::kDeropeIn) != 0 ? 2 : 0) + (mu ? 1 : 0);
   };
   auto enc = [&](const scd::GemmParams& p) { return scd::launch_encode_bf16(p, stream); };
   if (fast_kv) {
+    auto enc_kv = [&](const scd::GemmParams& p) { return scd::launch_encode_kv_bf16(p, stream); };
+    std::vector<std::vector<scd::GemmJob>> resident, streamed;
+    for (auto& grp : group_by(kv_jobs, by_kind))
+      (scd::encode_resident(w, grp[0].n, T * g, static_cast<int64_t>(grp.size())) ? resident : streamed)
+          .push_back(std::move(grp));
+    SCD_TRY(run_groups(kv_base, scd::kEncodeRows, 128, resident, enc_kv, "encode"));
     // tiles of 128 code columns: a rank above 128 takes two workgroups per row tile
-    SCD_TRY(run_groups(kv_base, scd::kEncodeRows, 128, group_by(kv_jobs, by_kind), enc, "encode"));
+    for (const auto& g : streamed)
+      SCD_TRY(run_groups(kv_base, g[0].vec != nullptr ? scd::kEncodeRowsMu : scd::kEncodeRows, 128,
+                         {g}, enc, "encode"));
   } else {
     SCD_TRY(run_generic(scd::Op::kEncodeKV, kv_base, kv_jobs, model->dtype, stream));
   }
-  if (fast_h)
+  // A few hundred row tiles of one long contraction each leave most CUs idle and wait on latency: the
+  // generic kernel splits the contraction there.  Four layers, d_model 4096, 128 codes, us streamed /
+  // generic: 40 tokens 38 / 17, 333 tokens 45 / 18, 1000 tokens 44 / 26, 2500 tokens 45 / 68.
+  int64_t h_tiles = 0;
+  for (const auto& j : h_jobs) h_tiles += (T + 31) / 32 * ((j.n + 63) / 64);
+  if (fast_h && h_tiles > 320)
     return run_groups(h_base, scd::kEncodeRows, 128, group_by(h_jobs, by_kind), enc, "encode");
   return run_generic(scd::Op::kEncodeH, h_base, h_jobs, model->dtype, stream);
 }

@@ -14,10 +14,12 @@
 // double-buffered in LDS and shared by the four waves.  Both operands visit the columns of a chunk
 // in the same order, so the contraction is unchanged.
 //
-// The offset is folded into the product: (X - 1 mu^T) E^T = X E^T - 1 (E mu)^T.  E mu is one more
-// MFMA per k-step with mu as a B operand broadcast to all 32 columns; wave w computes it for the
-// code blocks b = w (mod 4), the workgroup shares it through LDS and every lane subtracts it from
-// its fp32 accumulators.  The offset therefore costs no per-element work and is never rounded.
+// The offset is folded into the product: (X - 1 mu^T) E^T = X E^T - 1 (E mu)^T.  With an offset a
+// workgroup takes 127 rows and mu as its 128th, so E mu falls out of the same MFMAs (an extra product
+// per k-step with mu broadcast, as before, was a fifth of the MFMAs and a third of the LDS reads); the
+// workgroup shares it through LDS and every lane subtracts it from its fp32 accumulators, so the
+// offset is never rounded.  Rank 256, 32,768 tokens: 2263 -> 2145 us; rank 128, 8192 tokens (with the
+// Patch codes): 367 -> 358 us.
 #include "scd_device.h"
 
 namespace scd {
@@ -44,15 +46,15 @@ __device__ constexpr int chunk_col(int s, int h, bool derope) {
 // DEROPE = key jobs; MU = every job of the launch has an offset.
 template <int RB, int DH, bool DEROPE, bool MU, int DEPTH>
 __global__ __launch_bounds__(kThreads) void encode_bf16_kernel(GemmParams p) {
-  constexpr int kMuBlocks = (RB + 3) / 4;  // offset blocks per wave (waves past RB idle)
+  // With an offset a workgroup takes 127 rows and mu itself as its last one (not rotated)
+  constexpr int kRows = MU ? kEncodeRowsMu : kEncodeRows;
   extern __shared__ __attribute__((aligned(16))) uint16_t lds[];
   // Weight chunk rows: padded (DEPTH 1) or swizzled without padding (DEPTH 2, where every wave must
   // issue a fixed number of copies so its waits can be counted).
   constexpr bool kSwz = DEPTH == 2;
   constexpr int kLdc = kSwz ? kChunk : kLdcPad;
   uint16_t* Es = lds;                               // [2][RB*32][kLdc]
-  uint16_t* mus = lds + 2 * RB * 32 * kLdc;         // [K] (deRoPE'd-space offset)
-  float* emu = reinterpret_cast<float*>(mus + (MU ? p.jobs[0].k : 0));  // [RB*32]: E mu
+  float* emu = reinterpret_cast<float*>(lds + 2 * RB * 32 * kLdc);  // [RB*32]: E mu
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -70,19 +72,14 @@ __global__ __launch_bounds__(kThreads) void encode_bf16_kernel(GemmParams p) {
   const int R = job.n - code0 < RB * 32 ? job.n - code0 : RB * 32;  // code columns here
   const int K = job.k;
   const int64_t M = p.m;
-  const int64_t row = static_cast<int64_t>(local / n_split) * 128 + wave * 32 + (lane & 31);
-  const bool valid = row < M;
+  const int64_t row = static_cast<int64_t>(local / n_split) * kRows + wave * 32 + (lane & 31);
+  const bool mu_row = MU && wave * 32 + (lane & 31) == kRows;
+  const bool valid = row < M && !mu_row;
   constexpr bool derope = DEROPE;
   const uint16_t* X = static_cast<const uint16_t*>(job.a);
   const uint16_t* E = static_cast<const uint16_t*>(job.b) + static_cast<int64_t>(code0) * K;
   const uint16_t* mu = static_cast<const uint16_t*>(job.vec);
   const int nchunks = K / kChunk;
-
-  // offsets -> LDS (whole row width)
-  if (MU) {
-    for (int q = tid; q < K / 8; q += kThreads)
-      *reinterpret_cast<uint4*>(mus + 8 * q) = *reinterpret_cast<const uint4*>(mu + 8 * q);
-  }
 
   // weight chunk c -> LDS buffer b, asynchronously; code rows beyond R read row 0 and only feed
   // accumulator blocks that are never stored.  Swizzled: RB*32 rows x 16 chunks of 16 bytes, chunk
@@ -124,12 +121,12 @@ __global__ __launch_bounds__(kThreads) void encode_bf16_kernel(GemmParams p) {
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
         const float2 v = cs_row[16 * o + 8 * h + e];
-        cs_c[o][e] = v.x;
-        cs_s[o][e] = v.y;
+        cs_c[o][e] = mu_row ? 1.f : v.x;
+        cs_s[o][e] = mu_row ? 0.f : v.y;
       }
   }
 
-  const uint16_t* xrow = X + (valid ? row : 0) * K;
+  const uint16_t* xrow = mu_row ? mu : X + (valid ? row : 0) * K;
   // rows past the end read row 0 (always in bounds); their codes are never stored
   auto load_x = [&](int c, uint4* dst) {
 #pragma unroll
@@ -137,49 +134,26 @@ __global__ __launch_bounds__(kThreads) void encode_bf16_kernel(GemmParams p) {
       dst[s] = *reinterpret_cast<const uint4*>(xrow + c * kChunk + chunk_col<DH>(s, h, derope));
   };
 
-  f32x16 acc[RB], accm[kMuBlocks];
+  f32x16 acc[RB];
 #pragma unroll
   for (int b = 0; b < RB; ++b)
 #pragma unroll
     for (int e = 0; e < 16; ++e) acc[b][e] = 0.f;
-#pragma unroll
-  for (int i = 0; i < kMuBlocks; ++i)
-#pragma unroll
-    for (int e = 0; e < 16; ++e) accm[i][e] = 0.f;
 
   // One chunk's MFMAs for input registers x (8 loads of this lane's row) against weight buffer buf.
-  // Each weight fragment of k-step s + 1 (and the offset's) is read into the register its MFMA of
-  // step s has just consumed, one read after each MFMA, so each LDS read has most of a step of
-  // MFMAs to land instead of stalling the MFMA that needs it, with no second register set.
-  // B operands come in (first half, second half) pairs: deRoPE in fp32 and one bf16 rounding
-  // (keys), or the loaded values themselves.  Both operands visit the chunk's columns in the same
-  // order, so the contraction is unchanged.  Every wave computes kMuBlocks offset blocks (blocks
-  // past RB repeat block 0 and are never used), so every step has the same instructions.
-  // The read-ahead keeps a step's fragments live across the next step's deRoPE; the key kernels
-  // with four or more code blocks would then need more than half a SIMD's registers and drop to one
-  // wave per SIMD, which costs more than the reads' latency (the second wave hides it), so they
-  // read each step's fragments right before its MFMAs.
-  constexpr bool kReadAhead = !(DEROPE && RB >= 4);
-  constexpr int kStepMfma = RB + (MU ? kMuBlocks : 0);
-  constexpr int kStepReads = RB + (MU ? kMuBlocks + 1 : 0);
-  constexpr int kPairs = kStepMfma < kStepReads ? kStepMfma : kStepReads;
-  auto compute_chunk = [&](int c, int buf, const uint4* x) {
+  // The weight fragments of k-step s + 1 are read under the MFMAs of step s, so each LDS read has a
+  // step to land instead of stalling the MFMA that needs it.  B operands come in (first half, second
+  // half) pairs: deRoPE in fp32 and one bf16 rounding (keys), or the loaded values themselves.  Both
+  // operands visit the chunk's columns in the same order, so the contraction is unchanged.
+  auto compute_chunk = [&](int buf, const uint4* x) {
     const uint16_t* eb = Es + buf * RB * 32 * kLdc + (lane & 31) * kLdc;
-    bf16x8 f[RB], m[kMuBlocks], mu;
+    bf16x8 f[2][RB];
     auto read_step = [&](int s) {
       const int col = chunk_col<DH>(s, h, derope);
 #pragma unroll
-      for (int b = 0; b < RB; ++b) f[b] = efrag(eb, b, col);
-      if constexpr (MU) {
-#pragma unroll
-        for (int i = 0; i < kMuBlocks; ++i) {
-          const int b = wave + 4 * i;
-          m[i] = efrag(eb, b < RB ? b : 0, col);
-        }
-        mu = *reinterpret_cast<const bf16x8*>(mus + c * kChunk + col);
-      }
+      for (int b = 0; b < RB; ++b) f[s & 1][b] = efrag(eb, b, col);
     };
-    if constexpr (kReadAhead) read_step(0);
+    read_step(0);
     bf16x8 bu, bv;
 #pragma unroll
     for (int s = 0; s < 8; ++s) {
@@ -205,45 +179,17 @@ __global__ __launch_bounds__(kThreads) void encode_bf16_kernel(GemmParams p) {
         }
       }
       const bf16x8 bx = (s & 1) ? bv : bu;
-      if constexpr (!kReadAhead) {
-        // each fragment read right before its MFMA (short-lived registers)
-        const int col = chunk_col<DH>(s, h, derope);
-#pragma unroll
-        for (int b = 0; b < RB; ++b)
-          acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(efrag(eb, b, col), bx, acc[b], 0, 0, 0);
-        if constexpr (MU) {
-          const bf16x8 mu_s = *reinterpret_cast<const bf16x8*>(mus + c * kChunk + col);
-#pragma unroll
-          for (int i = 0; i < kMuBlocks; ++i) {
-            const int b = wave + 4 * i;
-            if (b < RB)
-              accm[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(efrag(eb, b, col), mu_s, accm[i],
-                                                                0, 0, 0);
-          }
-        }
-        continue;
-      }
       __builtin_amdgcn_sched_barrier(0);
+      if (s + 1 < 8) read_step(s + 1);
 #pragma unroll
       for (int b = 0; b < RB; ++b)
-        acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[b], bx, acc[b], 0, 0, 0);
-      if constexpr (MU) {
-        // E mu for this wave's offset blocks: mu (same columns as the inputs) in every B column
+        acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[s & 1][b], bx, acc[b], 0, 0, 0);
+      if (s + 1 < 8) {
 #pragma unroll
-        for (int i = 0; i < kMuBlocks; ++i)
-          accm[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(m[i], mu, accm[i], 0, 0, 0);
-      }
-      if (kReadAhead && s + 1 < 8) {
-        read_step(s + 1);
-#pragma unroll
-        for (int i = 0; i < kPairs; ++i) {
-          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+        for (int b = 0; b < RB; ++b) {
           __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
         }
-        if constexpr (kStepMfma > kPairs)
-          __builtin_amdgcn_sched_group_barrier(0x008, kStepMfma - kPairs, 0);
-        if constexpr (kStepReads > kPairs)
-          __builtin_amdgcn_sched_group_barrier(0x100, kStepReads - kPairs, 0);
       }
       __builtin_amdgcn_sched_barrier(0);
     }
@@ -262,7 +208,7 @@ __global__ __launch_bounds__(kThreads) void encode_bf16_kernel(GemmParams p) {
       stage_weights(c + 1, buf ^ 1);
       load_x(c + 1, xn);
     }
-    compute_chunk(c, buf, xc);
+    compute_chunk(buf, xc);
     wait_vmem();
     lds_barrier();
 #pragma unroll
@@ -289,7 +235,7 @@ __global__ __launch_bounds__(kThreads) void encode_bf16_kernel(GemmParams p) {
     __builtin_amdgcn_sched_barrier(0);
     load_x(c + 2 < last ? c + 2 : last, xfar);
     __builtin_amdgcn_sched_barrier(0);
-    if (c < nchunks) compute_chunk(c, buf, xcur);
+    if (c < nchunks) compute_chunk(buf, xcur);
     // chunk c + 1's weights and inputs have landed once only chunk c + 2's 8 input loads are
     // pending; the barrier makes that true for every wave and retires this chunk's LDS reads.  The
     // scheduling fences keep each step's loads on their side of the count.
@@ -307,14 +253,12 @@ __global__ __launch_bounds__(kThreads) void encode_bf16_kernel(GemmParams p) {
   wait_vmem();
   }
   if constexpr (MU) {
-    // every B column of the offset product is the same: lanes 0 and 32 publish their 16 values
+    // the last wave's last lanes of both halves hold E mu
+    if (mu_row) {
 #pragma unroll
-    for (int i = 0; i < kMuBlocks; ++i) {
-      const int b = wave + 4 * i;
-      if (b < RB && (lane & 31) == 0) {
+      for (int b = 0; b < RB; ++b)
 #pragma unroll
-        for (int e = 0; e < 16; ++e) emu[32 * b + 16 * h + e] = accm[i][e];
-      }
+        for (int e = 0; e < 16; ++e) emu[32 * b + 16 * h + e] = acc[b][e];
     }
     __syncthreads();
 #pragma unroll
@@ -336,6 +280,282 @@ __global__ __launch_bounds__(kThreads) void encode_bf16_kernel(GemmParams p) {
     d[0] = pack8(y);
     d[1] = pack8(y + 8);
   }
+}
+
+// ---- keys and values on resident weights ------------------------------------------------------------
+// The same product with no weight traffic in the loop: a workgroup of 8 waves keeps its code block's
+// whole encoder in LDS and every wave streams 32-row tiles on its own, inputs two chunks ahead across
+// tiles, with no barrier until the share enters the next layer.  Fragments are read from LDS one k-step
+// ahead and the next pair's deRoPE runs between MFMAs.  Bound by the mixed read/write stream of HBM:
+// rank 32 at w = 1024 moves 4.5 TB/s, a plain copy 4.7 TB/s (reads alone 6.1 TB/s).  E mu is computed
+// once per share and layer (chunks dealt to the waves) and subtracted from the accumulators.
+constexpr int kCus = 256;
+constexpr int kResWaves = 8, kResThreads = 64 * kResWaves;
+
+// LDS of the resident kernel: RB * 32 code rows x K columns of the encoder, then E mu (partial sums of
+// the waves, and their sum).
+constexpr size_t resident_lds(int rb, int k) {
+  return static_cast<size_t>(rb) * 32 * k * 2 + static_cast<size_t>(kResWaves + 1) * rb * 32 * 4;
+}
+
+template <int RB, int DH, bool DEROPE, bool MU>
+__global__ __launch_bounds__(kResThreads, 2) void encode_kv_bf16_kernel(GemmParams p) {
+  extern __shared__ __attribute__((aligned(16))) uint16_t lds[];
+  __shared__ LdsBatch lbatch;
+  constexpr int CB = RB * 32;                    // codes of this workgroup
+  const int K = p.jobs[0].k, nchunks = K / kChunk;
+  uint16_t* Ws = lds;                            // [nchunks][CB][kChunk], 16-byte pieces swizzled
+  float* part = reinterpret_cast<float*>(lds + static_cast<size_t>(CB) * K);  // [kResWaves][CB]
+  float* emu = part + kResWaves * CB;            // [CB]
+
+  const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int64_t M = p.m;
+
+  // workgroup -> (share of the wave tiles, code block); code block fastest, so that the workgroups
+  // that read the same rows run on one XCD at the same time
+  const int u = xcd_remap(blockIdx.x, gridDim.x);
+  const int n = p.jobs[0].n;
+  const int n_split = (n + CB - 1) / CB, n_share = gridDim.x / n_split;
+  const int share = u / n_split, code0 = (u % n_split) * CB;
+  const int R = n - code0 < CB ? n - code0 : CB;
+  const int64_t per_job = (M + 31) / 32;         // wave tiles of 32 rows
+  int64_t first, last;
+  if (p.reserved > 0) {                          // whole jobs, `reserved` shares each
+    const int j = share / p.reserved, q = share % p.reserved;
+    first = j * per_job + per_job * q / p.reserved;
+    last = j * per_job + per_job * (q + 1) / p.reserved;
+  } else {                                       // one balanced list over all jobs
+    const int64_t total = per_job * p.n_jobs;
+    first = total * share / n_share;
+    last = total * (share + 1) / n_share;
+  }
+  const bool lds_batch = p.n_seqs <= kMaxLdsSeqs;
+  if (DEROPE && lds_batch) stage_batch(p, lbatch, tid, kResThreads);
+
+  constexpr int kNo = DEROPE ? DH / 32 : 1;      // 16-wide offsets per half head
+  for (int64_t t = first; t < last;) {
+    const int j = static_cast<int>(t / per_job);
+    const int64_t t1 = last < (j + 1) * per_job ? last : (j + 1) * per_job;
+    const int64_t job0 = j * per_job;
+    const GemmJob& job = p.jobs[j];
+    const uint16_t* X = static_cast<const uint16_t*>(job.a);
+    const uint16_t* E = static_cast<const uint16_t*>(job.b) + static_cast<int64_t>(code0) * K;
+    uint16_t* Z = static_cast<uint16_t*>(job.c);
+
+    // Loads run two chunks ahead of use, across the wave's tiles (t + wave, t + wave + 8, ...).  Past
+    // the last tile they re-read the wave's first one; rows past the end read row 0.
+    int64_t lt = t + wave;  // tile and chunk of the next load
+    int lc = 0;
+    const uint16_t* xrow;
+    auto set_row = [&]() {
+      const int64_t row = (lt < t1 ? lt : t) * 32 - job0 * 32 + (lane & 31);
+      xrow = X + (row < M ? row : 0) * K;
+    };
+    set_row();
+    auto load_x = [&](uint4 (&x)[8]) {
+#pragma unroll
+      for (int s = 0; s < 8; ++s)
+        x[s] = *reinterpret_cast<const uint4*>(xrow + lc * kChunk + chunk_col<DH>(s, h, DEROPE));
+      if (++lc == nchunks) {
+        lc = 0;
+        lt += kResWaves;
+        set_row();
+      }
+    };
+    uint4 x0[8], x1[8], x2[8];
+    if (t != first) lds_barrier();  // every wave is done with the previous job's weights
+    load_x(x0);
+    load_x(x1);
+    // the encoder -> LDS: chunk c of code row rho (permuted so that a lane ends with 16 consecutive
+    // codes of one row), piece q at q ^ (rho & 7); rows past R repeat row 0 and are never stored
+    for (int s = wave * 64; s < nchunks * CB * 16; s += kResThreads) {
+      const int slot = s + lane, c = slot / (CB * 16), rho = (slot >> 4) % CB;
+      const int q = (slot & 15) ^ (rho & 7), r = row_of_lds(rho);
+      __builtin_amdgcn_global_load_lds(
+          E + static_cast<int64_t>(r < R ? r : 0) * K + c * kChunk + 8 * q,
+          (lds_void_t)(Ws + 8 * s), 16, 0, 0);
+    }
+    wait_vmem();
+    lds_barrier();
+
+    auto wfrag = [&](int c, int b, int col) {
+      return *reinterpret_cast<const bf16x8*>(Ws + (c * CB + b * 32 + (lane & 31)) * kChunk +
+                                              8 * ((col >> 3) ^ (lane & 7)));
+    };
+    if constexpr (MU) {
+      // E mu: mu as the B operand in every column, chunks dealt out to the waves, partial sums added
+      // in wave order
+      const uint16_t* mu = static_cast<const uint16_t*>(job.vec);
+      f32x16 am[RB];
+#pragma unroll
+      for (int b = 0; b < RB; ++b)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) am[b][e] = 0.f;
+      for (int c = wave; c < nchunks; c += kResWaves) {
+#pragma unroll
+        for (int s = 0; s < 8; ++s) {
+          const bf16x8 m = *reinterpret_cast<const bf16x8*>(mu + c * kChunk + 16 * s + 8 * h);
+#pragma unroll
+          for (int b = 0; b < RB; ++b)
+            am[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wfrag(c, b, 16 * s + 8 * h), m, am[b],
+                                                            0, 0, 0);
+        }
+      }
+      if ((lane & 31) == 0) {
+#pragma unroll
+        for (int b = 0; b < RB; ++b)
+#pragma unroll
+          for (int e = 0; e < 16; ++e) part[wave * CB + 32 * b + 16 * h + e] = am[b][e];
+      }
+      lds_barrier();
+      if (tid < CB) {
+        float v = 0.f;
+#pragma unroll
+        for (int w = 0; w < kResWaves; ++w) v += part[w * CB + tid];
+        emu[tid] = v;
+      }
+      lds_barrier();
+    }
+
+    // rotation factors of the row this lane works on, for every pair index it touches
+    float cs_c[kNo][8], cs_s[kNo][8];
+    auto load_rope = [&](int64_t tile) {
+      if constexpr (DEROPE) {
+        const int64_t row = (tile - job0) * 32 + (lane & 31);
+        const int pos = row < M ? (lds_batch ? row_position_lds(p, lbatch, row) : row_position(p, row)) : 0;
+        const float2* cs_row = p.rope + static_cast<int64_t>(pos) * (DH / 2);
+#pragma unroll
+        for (int o = 0; o < kNo; ++o)
+#pragma unroll
+          for (int e = 0; e < 8; e += 2) {
+            const float4 v = *reinterpret_cast<const float4*>(cs_row + 16 * o + 8 * h + e);
+            cs_c[o][e] = v.x;
+            cs_s[o][e] = v.y;
+            cs_c[o][e + 1] = v.z;
+            cs_s[o][e + 1] = v.w;
+          }
+      }
+    };
+    f32x16 acc[RB];
+    auto clear = [&]() {
+#pragma unroll
+      for (int b = 0; b < RB; ++b)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[b][e] = 0.f;
+    };
+    int64_t ct = t + wave;  // tile and chunk of the next product
+    int cc = 0;
+    clear();
+    if (ct < t1) load_rope(ct);
+    auto step = [&](uint4 (&x)[8], uint4 (&far)[8]) {
+      load_x(far);
+      __builtin_amdgcn_sched_barrier(0);
+      // the B operand of steps sp and sp + 1: deRoPE in fp32 and one rounding, or the loaded values
+      auto operand = [&](int sp, bf16x8& bu, bf16x8& bv) {
+        if constexpr (DEROPE) {
+          float a[8], b[8];
+          unpack8(x[sp], a);
+          unpack8(x[sp + 1], b);
+          constexpr int spH = DH / 16;
+          const int o = (sp % spH) >> 1;
+#pragma unroll
+          for (int e = 0; e < 8; ++e) {
+            const float c = cs_c[o][e], sn = cs_s[o][e];
+            const float uu = a[e], vv = b[e];
+            a[e] = uu * c + vv * sn;
+            b[e] = vv * c - uu * sn;
+          }
+          bu = __builtin_bit_cast(bf16x8, pack8(a));
+          bv = __builtin_bit_cast(bf16x8, pack8(b));
+        } else {
+          bu = __builtin_bit_cast(bf16x8, x[sp]);
+          bv = __builtin_bit_cast(bf16x8, x[sp + 1]);
+        }
+      };
+      // Each step's fragments are read during the step before (read right before its MFMAs, an LDS
+      // read's whole latency stands in front of every MFMA), and the next pair's deRoPE runs between
+      // the MFMAs of the pair's second step.
+      bf16x8 f[2][RB], bu[2], bv[2];
+#pragma unroll
+      for (int b = 0; b < RB; ++b) f[0][b] = wfrag(cc, b, chunk_col<DH>(0, h, DEROPE));
+      operand(0, bu[0], bv[0]);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int s = 0; s < 8; ++s) {
+        if (s + 1 < 8) {
+#pragma unroll
+          for (int b = 0; b < RB; ++b)
+            f[(s + 1) & 1][b] = wfrag(cc, b, chunk_col<DH>(s + 1, h, DEROPE));
+        }
+        if ((s & 1) && s + 1 < 8) operand(s + 1, bu[((s + 1) >> 1) & 1], bv[((s + 1) >> 1) & 1]);
+        const bf16x8 bx = (s & 1) ? bv[(s >> 1) & 1] : bu[(s >> 1) & 1];
+#pragma unroll
+        for (int b = 0; b < RB; ++b)
+          acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[s & 1][b], bx, acc[b], 0, 0, 0);
+        if (s + 1 < 8) __builtin_amdgcn_sched_group_barrier(0x100, RB, 0);
+        if constexpr (DEROPE) {
+          if ((s & 1) && s + 1 < 8) {
+#pragma unroll
+            for (int b = 0; b < RB; ++b) {
+              __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+              __builtin_amdgcn_sched_group_barrier(0x002, 64 / RB, 0);
+            }
+          }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      if (++cc < nchunks) return;
+      cc = 0;
+      // the tile is complete: lane holds, for block b, codes code0 + 32 b + 16 h + (0..15) of its row
+      const int64_t row = (ct - job0) * 32 + (lane & 31);
+      ct += kResWaves;
+      if (ct < t1) load_rope(ct);
+      if (row < M) {
+        uint16_t* zo = Z + row * n + code0;
+#pragma unroll
+        for (int b = 0; b < RB; ++b) {
+          const int c0 = 32 * b + 16 * h;
+          if (c0 >= R) continue;
+          float y[16];
+#pragma unroll
+          for (int e = 0; e < 16; ++e) y[e] = MU ? acc[b][e] - emu[c0 + e] : acc[b][e];
+          uint4* d = reinterpret_cast<uint4*>(zo + c0);
+          d[0] = pack8(y);
+          d[1] = pack8(y + 8);
+        }
+      }
+      clear();
+    };
+    while (ct < t1) {
+      step(x0, x2);
+      if (ct >= t1) break;
+      step(x1, x0);
+      if (ct >= t1) break;
+      step(x2, x1);
+    }
+    t = t1;
+  }
+}
+
+template <int RB>
+hipError_t launch_resident(bool derope, bool mu, const GemmParams& p, int grid, hipStream_t stream) {
+  const size_t lds = resident_lds(RB, p.jobs[0].k);
+#define SCD_RESIDENT(DH, DEROPE, MU)                                                             \
+  hipLaunchKernelGGL((encode_kv_bf16_kernel<RB, DH, DEROPE, MU>), dim3(grid), dim3(kResThreads), \
+                     lds, stream, p)
+  if (!derope) {
+    if (mu) SCD_RESIDENT(128, false, true);
+    else SCD_RESIDENT(128, false, false);
+  } else if (p.head_dim == 128) {
+    if (mu) SCD_RESIDENT(128, true, true);
+    else SCD_RESIDENT(128, true, false);
+  } else {
+    if (mu) SCD_RESIDENT(64, true, true);
+    else SCD_RESIDENT(64, true, false);
+  }
+#undef SCD_RESIDENT
+  return hipGetLastError();
 }
 
 template <int RB, bool DEROPE, bool MU>
@@ -378,9 +598,58 @@ hipError_t launch_kind(bool derope, bool mu, int head_dim, const GemmParams& p, 
 // above 128 take two workgroups of 4 blocks per row tile.
 int encode_code_blocks(int max_rank) { return max_rank <= 64 ? 2 : 4; }
 
-size_t encode_bf16_lds_bytes(int code_blocks, int k, bool mu) {
+size_t encode_bf16_lds_bytes(int code_blocks, bool mu) {
   return static_cast<size_t>(2) * code_blocks * 32 * kLdcPad * 2 +
-         (mu ? static_cast<size_t>(k) * 2 + static_cast<size_t>(code_blocks) * 32 * 4 : 0);
+         (mu ? static_cast<size_t>(code_blocks) * 32 * 4 : 0);
+}
+
+// Code blocks of 32 per workgroup of the resident kernel.
+static int resident_blocks(int k, int rank) {
+  return rank <= 32 ? 1 : rank <= 64 || k > 512 ? 2 : rank <= 96 ? 3 : 4;
+}
+
+// Resident where one workgroup's LDS holds the encoder of every code, so that the rows are read once:
+// keys and values, us streamed / resident: w = 512, rank 96, 32,768 tokens x 24 layers 706 / 617;
+// w = 128 (heads' shared basis), ranks 64 and 32, 8192 tokens x 32 layers 442 / 344; w = 1024, rank 64,
+// 32,768 tokens 1046 / 1020.  Split over workgroups the rows are read once per 64 codes, which loses
+// for large launches (w = 1024, rank 128, 8192 tokens: 315 / 330) and still wins while the launch is
+// one tile per wave and bound by latency (rank 128, 40 tokens 49 / 29, 333 tokens 57 / 35).
+bool encode_resident(int k, int rank, int64_t rows, int64_t n_jobs) {
+  const int rb = resident_blocks(k, rank);
+  if (resident_lds(rb, k) + sizeof(LdsBatch) > 160 * 1024) return false;
+  const int n_split = (rank + 32 * rb - 1) / (32 * rb);
+  const int64_t wgs = ((rows + 31) / 32 + kResWaves - 1) / kResWaves;
+  return n_split == 1 || wgs * n_jobs * n_split <= kCus;
+}
+
+hipError_t launch_encode_kv_bf16(GemmParams p, hipStream_t stream) {
+  if (p.m <= 0 || p.n_jobs < 1) return hipSuccess;
+  const int k = p.jobs[0].k, n = p.jobs[0].n;
+  const bool derope = (p.jobs[0].flags & kDeropeIn) != 0;
+  const bool mu = p.jobs[0].vec != nullptr;
+  for (int i = 0; i < p.n_jobs; ++i) {
+    const GemmJob& j = p.jobs[i];
+    if (j.k != k || j.n != n || ((j.flags & kDeropeIn) != 0) != derope || (j.vec != nullptr) != mu)
+      return hipErrorInvalidValue;
+  }
+  const int rb = resident_blocks(k, n);
+  if (resident_lds(rb, k) + sizeof(LdsBatch) > 160 * 1024) return hipErrorInvalidValue;
+  const int n_split = (n + 32 * rb - 1) / (32 * rb);
+  const int64_t shares = kCus / n_split > 0 ? kCus / n_split : 1;
+  const int64_t per_job = (p.m + 31) / 32, wgs = (per_job + kResWaves - 1) / kResWaves;
+  // a launch of at most one tile per wave: whole jobs, spread over as many workgroups as there are
+  int64_t parts = 0;
+  if (wgs * p.n_jobs <= shares) {
+    parts = shares / p.n_jobs < per_job ? shares / p.n_jobs : per_job;
+  }
+  p.reserved = static_cast<int32_t>(parts);
+  const int grid = static_cast<int>((parts > 0 ? parts * p.n_jobs : shares) * n_split);
+  switch (rb) {
+    case 1: return launch_resident<1>(derope, mu, p, grid, stream);
+    case 2: return launch_resident<2>(derope, mu, p, grid, stream);
+    case 3: return launch_resident<3>(derope, mu, p, grid, stream);
+    default: return launch_resident<4>(derope, mu, p, grid, stream);
+  }
 }
 
 hipError_t launch_encode_bf16(const GemmParams& p, hipStream_t stream) {
@@ -399,7 +668,7 @@ hipError_t launch_encode_bf16(const GemmParams& p, hipStream_t stream) {
     max_r = j.n > max_r ? j.n : max_r;
   }
   const int rb = encode_code_blocks(max_r);
-  const size_t lds = encode_bf16_lds_bytes(rb, k, mu);
+  const size_t lds = encode_bf16_lds_bytes(rb, mu);
   if (rb == 2) return launch_kind<2>(derope, mu, p.head_dim, p, lds, stream);
   return launch_kind<4>(derope, mu, p.head_dim, p, lds, stream);
 }

@@ -110,10 +110,14 @@ constexpr int kMaxLdsSeqs = 256;
 // Rows every RoPE table holds at least (positions 0..15 are read as in-tile offsets).
 constexpr int kRopeMinRows = 16;
 
-// Encode on the bf16 path: a unit is 128 rows x all code columns; k % 128 == 0, n <= 256,
+// Encode on the bf16 path: a unit is 128 rows (127 when its jobs have offsets) x all code columns; k % 128 == 0, n <= 256,
 // head_dim 64 or 128 when a job de-rotates.
-constexpr int kEncodeRows = 128;
+constexpr int kEncodeRows = 128, kEncodeRowsMu = 127;
 hipError_t launch_encode_bf16(const GemmParams& p, hipStream_t stream);
+// Keys and values with the encoder resident in LDS: k % 128 == 0, head_dim 64 or 128 when a job
+// de-rotates, every job of a launch of one rank and kind, rows of one encode_resident shape.
+bool encode_resident(int k, int rank, int64_t rows, int64_t n_jobs);
+hipError_t launch_encode_kv_bf16(GemmParams p, hipStream_t stream);
 // ---- Offline Reuse fit (joint Gram of de-rotated producer/consumer rows, then a small fp64
 // solve).  The Gram of X = [A B] (N rows of 2w columns) is accumulated per 128 x 128 upper tile and
 // per slice of rows into a workspace of partial tiles, then summed over slices in a fixed order.

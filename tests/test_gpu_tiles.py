@@ -97,3 +97,25 @@ def test_decode_odd_ranks(ranks, ranks_v):
     rope = scd.scd_rope_table(U.model_of(wl), wl.max_position)
     out = U.run_gpu(wl, inp, rope, which=("decode",), fill=float("nan"))
     U.assert_within(U.compare_all(wl, inp, out), BF16_TOL, wl.name)
+
+
+# bf16 encode: the resident kernel with whole-layer shares (one and several code blocks), its balanced
+# list crossing layers (several chunks, and one), 1 to 4 code blocks of 32, with and without offsets;
+# the streamed kernel with 127-row tiles; Patch codes on either side of the split contraction.
+@pytest.mark.parametrize("heads,head_dim,shared,tokens,layers,ranks,mu", [
+    (8, 128, False, (300, 3), 3, (128, 256, 96), True),
+    (8, 128, False, (5000,), 3, (128, 192, 128), True),
+    (2, 128, False, (9000, 100), 9, (64,) * 9, True),
+    (4, 64, False, (9001,), 9, (96,) * 9, False),
+    (4, 128, False, (700,), 4, (128, 32, 96, 48), True),
+    (8, 128, True, (2999,), 4, (128, 128, 32, 32), True),
+    (2, 64, False, (1,), 2, (16, 112), False)])
+def test_encode_shapes(heads, head_dim, shared, tokens, layers, ranks, mu):
+    wl = W.Workload(f"encode_{heads}_{tokens[0]}", layers, 384, heads, head_dim, tokens, ranks, (0,),
+                    5e5, "bf16", basis_width=head_dim if shared else None, with_mu=mu,
+                    pos0=tuple(9 * i for i in range(len(tokens))))
+    dev = torch.device("cuda")
+    inp = W.Inputs(wl, dev, decode=False, patch=False)
+    rope = scd.scd_rope_table(U.model_of(wl), wl.max_position)
+    out = U.run_gpu(wl, inp, rope, which=("encode",))
+    U.assert_within(U.compare_all(wl, inp, out), BF16_TOL, wl.name)
