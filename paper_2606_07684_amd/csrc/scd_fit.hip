@@ -613,18 +613,19 @@ __global__ __launch_bounds__(256) void fit_gram_reduce_kernel(const FitGramParam
 //             from the updated column and the product p = tau A v that the next launch needs.  Two
 //             matrix copies take turns as source and destination, so no workgroup reads what
 //             another workgroup of the same launch writes.  The last steps (a trailing block of at
-//             most 128 rows) run in one launch with the block in LDS;
-//   bisect    the r largest eigenvalues of T by bisection on Sturm counts;
-//   inverse   their eigenvectors of T by inverse iteration (three solves with T - lambda I under
-//             partial pivoting); eigenvalues closer than 1e-7 ||T|| form a cluster, whose vectors
-//             one thread computes in turn, each orthogonalised against the cluster's earlier ones
-//             (for 2w <= 256 the working vectors live in LDS);
-//   back      V_r = Q Y, each column's largest-magnitude entry then made positive;
+//             most 256 rows) run in one launch with the block in registers;
+//   bisect    the r largest eigenvalues of T by multisection on Sturm counts, one wave each;
+//   inverse   their eigenvectors of T by inverse iteration (three solves with T - lambda I, factored
+//             once under partial pivoting); eigenvalues closer than 1e-7 ||T|| form a cluster, whose
+//             vectors one thread computes in turn, each orthogonalised against the cluster's earlier
+//             ones (the working vectors live in LDS);
+//   back      V_r = Q Y, one wave per column, the column in registers, each column's largest-magnitude
+//             entry then made positive;
 //   project   P = G_c V_r;
 //   normal    Z^T Z + lam I = V_r^T P + lam I and A^T A + lam I;
-//   chol      right-looking Cholesky of both, one launch per column (sizes up to 128: one
-//             launch, the matrix in LDS);
-//   out       the triangular solves for E and F and the outputs, rounded once.
+//   chol      Cholesky of both, 64 columns per panel and update launch;
+//   out       the triangular solves for E and F, one wave per right-hand side in registers, and the
+//             outputs, rounded once.
 // ---------------------------------------------------------------------------------------------
 constexpr int kSolveThreads = 256;
 constexpr int kSolveRows = 16;  // rows per workgroup of the prep and of a tridiagonal step, n <= 512
@@ -632,9 +633,6 @@ constexpr int kSolveRows = 16;  // rows per workgroup of the prep and of a tridi
 // trailing block is then large and one layer's 16-row workgroups would leave most CUs idle, each
 // workgroup bound by its CU's share of the memory bandwidth.
 constexpr int kSolveRowsWide = 4;
-// columns of Y per workgroup of the back-transformation: 8 for n <= 512 (many layers, short
-// chains), 2 above (one layer's few workgroups carry long chains)
-constexpr int kBackColsNarrow = 8, kBackColsWide = 2;
 constexpr int kMaxN = 2 * kFitMaxSolveWidth;
 constexpr int kInverseSolves = 3;
 constexpr double kEps = 2.220446049250313e-16;  // 2^-52
@@ -691,13 +689,13 @@ __device__ inline Slots slots(double* work, int w, int layer) {
   return s;
 }
 
-// Centred Gram entry G[i][j] - s_i s_j / N in fp64; every stage that needs G_c evaluates it with
-// this one expression, so all see the same values.
-__device__ inline double centred(const float* gram, const float* cs, int n, int i, int j, double rows,
-                                 bool center) {
-  double g = static_cast<double>(gram[static_cast<int64_t>(i) * n + j]);
-  if (center) g -= static_cast<double>(cs[i]) * static_cast<double>(cs[j]) / rows;
-  return g;
+// Centred Gram entry G[i][j] - s_i s_j / N in fp64 (inv = 1 / N, or 0 without centring); every stage
+// that needs G_c evaluates it with this one expression, so all see the same values.  (A division per
+// entry cost more than the products it fed.)
+__device__ inline double centred(const float* gram, const float* cs, int n, int i, int j, double inv) {
+  const double g = static_cast<double>(gram[static_cast<int64_t>(i) * n + j]);
+  if (inv == 0.0) return g;
+  return g - static_cast<double>(cs[i]) * static_cast<double>(cs[j]) * inv;
 }
 
 __device__ inline double wave_sum(double v) {
@@ -723,7 +721,7 @@ __global__ __launch_bounds__(kSolveThreads) void fit_prep_kernel(const FitSolveP
   const int i0 = blockIdx.x * kSolveRows;
   for (int e = threadIdx.x; e < kSolveRows * n; e += kSolveThreads) {
     const int i = i0 + e / n, j = e % n;
-    if (i < n) s.z[static_cast<int64_t>(i) * n + j] = centred(jb.gram, jb.colsum, n, i, j, rows, center);
+    if (i < n) s.z[static_cast<int64_t>(i) * n + j] = centred(jb.gram, jb.colsum, n, i, j, center ? 1.0 / rows : 0.0);
   }
   if (blockIdx.x != 0) return;
   if (threadIdx.x == 0)
@@ -871,117 +869,223 @@ __global__ __launch_bounds__(kSolveThreads) void fit_tridiag_kernel(const SolveA
   tridiag_step<0, kSolveRowsWide>(a);
 }
 
+// Wave-wide fp64 sum without LDS: four DPP steps inside rows of 16 lanes, then the rows (halves)
+// swapped against themselves.
+template <int CTRL>
+__device__ inline double dpp_f64(double v) {
+  const int64_t b = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_update_dpp(0, static_cast<int>(b), CTRL, 0xF, 0xF, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, static_cast<int>(b >> 32), CTRL, 0xF, 0xF, true);
+  return __longlong_as_double((static_cast<int64_t>(hi) << 32) | static_cast<uint32_t>(lo));
+}
+__device__ inline double row16_sum(double v) {
+  v += dpp_f64<0xB1>(v);   // quad_perm [1,0,3,2]
+  v += dpp_f64<0x4E>(v);   // quad_perm [2,3,0,1]
+  v += dpp_f64<0x141>(v);  // row_half_mirror
+  v += dpp_f64<0x140>(v);  // row_mirror
+  return v;
+}
+// Sum over the four rows of 16 lanes (every lane keeps its column of the row).
+__device__ inline double rows4_sum(double v) {
+  const int64_t b = __double_as_longlong(v);
+  const uint32_t lo = static_cast<uint32_t>(b), hi = static_cast<uint32_t>(b >> 32);
+  auto join = [](uint32_t l, uint32_t h) {
+    return __longlong_as_double((static_cast<int64_t>(h) << 32) | l);
+  };
+  const auto l16 = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+  const auto h16 = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+  v = join(l16[0], h16[0]) + join(l16[1], h16[1]);
+  const int64_t c = __double_as_longlong(v);
+  const uint32_t lo2 = static_cast<uint32_t>(c), hi2 = static_cast<uint32_t>(c >> 32);
+  const auto l32 = __builtin_amdgcn_permlane32_swap(lo2, lo2, false, false);
+  const auto h32 = __builtin_amdgcn_permlane32_swap(hi2, hi2, false, false);
+  return join(l32[0], h32[0]) + join(l32[1], h32[1]);
+}
+__device__ inline double wave_sum_dpp(double v) { return rows4_sum(row16_sum(v)); }
+
+__device__ inline double readlane_f64(double v, int lane) {
+  const int64_t b = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_readlane(static_cast<int>(b), lane);
+  const int hi = __builtin_amdgcn_readlane(static_cast<int>(b >> 32), lane);
+  return __longlong_as_double((static_cast<int64_t>(hi) << 32) | static_cast<uint32_t>(lo));
+}
+
 // The last steps, from step k0 on (trailing block of at most kTailN rows), in one launch: one
-// workgroup per layer holds the block [k0 + 1, n)^2 of A^(k0) in LDS and applies the same steps as
-// the per-column launches (the same expressions, reflectors and p in the same places), the
-// workgroup barriers standing in for the launch boundaries.  k0 = -1 starts from G_c itself.
-constexpr int kTailN = 128, kTailThreads = 1024;
-__global__ __launch_bounds__(kTailThreads) void fit_tridiag_tail_kernel(const SolveArgs a) {
-  constexpr int LD = kTailN + 1, kWaves = kTailThreads / 64;
-  __shared__ double am[kTailN * LD];
-  __shared__ double vk[kTailN], wk[kTailN], vn[kTailN], pk[kTailN];
-  __shared__ double red[2][kWaves];
+// workgroup per layer keeps the block [k0 + 1, n)^2 of A^(k0) in registers and applies the same steps
+// as the per-column launches, the workgroup barriers standing in for the launch boundaries.
+// k0 = -1 starts from G_c itself.
+//
+// The steps are a chain, so the layout keeps each one short.  The lower triangle (with whole 32 x 32
+// blocks on the diagonal) is spread over 512 threads, thread (ty, tx) holding rows ty + 32 a and
+// columns tx + 16 b; an element serves its row's sum and, below the diagonal blocks, its mirror's.  The
+// threads' partial sums meet in LDS, where two threads add up each entry (lane reductions for 8 rows and
+// 14 column blocks cost twice that).  The vector part of a step (w, the next column, its reflector) is
+// one wave's work with four entries a lane, so it needs no barrier of its own: three barriers per
+// step.  256 rows take 3.3 us a step on average; in LDS
+// with a wave per row and six-step shuffles (128 rows at most) a step took 5.9 us, and the columns
+// before that 9.6 us a launch.
+constexpr int kTailN = 256, kTailThreads = 512;
+__global__ __launch_bounds__(kTailThreads, 2) void fit_tridiag_tail_kernel(const SolveArgs a) {
+  constexpr int kRB = kTailN / 32, kCB = kTailN / 16;
+  // partial sums of A v: by thread row ty for the columns, by thread column tx for the rows (padded so
+  // that the 64 lanes of a store hit distinct banks)
+  constexpr int kRowLd = kTailN + 4;
+  __shared__ double col[kTailN], vs[kTailN], ws[kTailN], ns[kTailN], ps[kTailN];
+  __shared__ double cpart[32][kTailN], rpart[16][kRowLd];
   const int layer = blockIdx.x, n = 2 * a.w, k0 = a.step, tid = threadIdx.x;
-  const int lane = tid & 63, wave = tid >> 6;
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int tx = tid & 15, ty = tid >> 4;
   const Slots s = slots(a.work, a.w, layer);
   const int o = k0 + 1;  // global index of local row / column 0
   const int m0 = n - o;  // rows of the block (<= kTailN)
-  {
-    const double* src = k0 <= 0 ? s.z : ((k0 - 1) & 1 ? s.y : s.x);
-    for (int e = tid; e < m0 * m0; e += kTailThreads) {
-      const int i = e / m0, j = e % m0;
-      am[i * LD + j] = src[static_cast<int64_t>(o + i) * n + o + j];
+  const double* src = k0 <= 0 ? s.z : ((k0 - 1) & 1 ? s.y : s.x);
+  double am[kRB][kCB];  // blocks b <= 2 row + 1
+#pragma unroll
+  for (int r = 0; r < kRB; ++r)
+#pragma unroll
+    for (int b = 0; b < 2 * r + 2; ++b) {
+      const int i = ty + 32 * r, j = tx + 16 * b;
+      am[r][b] = i < m0 && j < m0 ? src[static_cast<int64_t>(o + i) * n + o + j] : 0.0;
     }
-    if (k0 >= 0) {
-      const double* vrow = reflector_rows(s, k0) + static_cast<int64_t>(k0) * n;
-      const double* p_cur = (k0 & 1) ? s.p1 : s.p0;
-      for (int i = tid; i < m0; i += kTailThreads) {
-        vk[i] = vrow[o + i];
-        pk[i] = p_cur[o + i];
+  for (int i = tid; i < kTailN; i += kTailThreads)
+    col[i] = i < m0 ? src[static_cast<int64_t>(o) * n + o + i] : 0.0;
+  for (int i = tid; i < 32 * kTailN; i += kTailThreads) (&cpart[0][0])[i] = 0.0;
+  for (int i = tid; i < 16 * kRowLd; i += kTailThreads) (&rpart[0][0])[i] = 0.0;
+  // wave 0: p_k and v_k, entries lane + 64 q
+  double pq[4] = {0.0, 0.0, 0.0, 0.0}, vq[4] = {0.0, 0.0, 0.0, 0.0}, tau = 0.0;
+  if (wave == 0 && k0 >= 0) {
+    const double* vrow = reflector_rows(s, k0) + static_cast<int64_t>(k0) * n;
+    const double* p_cur = (k0 & 1) ? s.p1 : s.p0;
+    tau = s.tau[k0];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int i = lane + 64 * q;
+      if (i < m0) {
+        vq[q] = vrow[o + i];
+        pq[q] = p_cur[o + i];
       }
-    } else {
-      for (int i = tid; i < m0; i += kTailThreads) vk[i] = pk[i] = 0.0;
     }
   }
   __syncthreads();
-  auto block_sum = [&](double v, int slot) {
-    v = wave_sum(v);
-    if (lane == 0) red[slot][wave] = v;
-    __syncthreads();
-    double t = 0.0;
-    for (int q = 0; q < kWaves; ++q) t += red[slot][q];
-    return t;
+  auto entry = [&](const double (&x)[4], int i) {  // entry i (uniform) of a wave-wide vector
+    const int l = i & 63;
+    const double y0 = readlane_f64(x[0], l), y1 = readlane_f64(x[1], l);
+    const double y2 = readlane_f64(x[2], l), y3 = readlane_f64(x[3], l);
+    return i < 128 ? (i < 64 ? y0 : y1) : (i < 192 ? y2 : y3);
   };
-  double tau_k = k0 >= 0 ? s.tau[k0] : 0.0;
   for (int k = k0; k <= n - 3; ++k) {
-    // local indices: global i is local i - o; the step touches global [k + 1, n)
-    const int b = k + 1 - o;  // local index of global k + 1
-    // w_k = p_k - (tau_k / 2)(p_k . v_k) v_k
-    double kk = 0.0;
-    if (k >= 0) {
+    const int c = k + 1 - o;  // local index of global k + 1
+    if (wave == 0) {
       double dot = 0.0;
-      for (int i = b + tid; i < m0; i += kTailThreads) dot += pk[i] * vk[i];
-      kk = 0.5 * tau_k * block_sum(dot, 0);
-    }
-    const double vk1 = vk[b], wk1 = pk[b] - kk * vk1;
-    double sig = 0.0;
-    for (int i = b + tid; i < m0; i += kTailThreads) {
-      const double wi = pk[i] - kk * vk[i];
-      wk[i] = wi;
-      const double c = am[b * LD + i] - vk1 * wi - wk1 * vk[i];
-      vn[i] = c;
-      if (i >= b + 2) sig += c * c;
-    }
-    const double sigma = block_sum(sig, 1);  // its barrier also publishes wk and vn
-    const double d_next = vn[b], alpha = vn[b + 1];
-    double tau = 0.0, beta = alpha, scale = 0.0;
-    if (!(sigma == 0.0)) {
-      const double norm = sqrt(alpha * alpha + sigma);
-      beta = alpha >= 0.0 ? -norm : norm;
-      tau = (beta - alpha) / beta;
-      scale = 1.0 / (alpha - beta);
-    }
-    __syncthreads();  // every thread has read alpha and used pk
-    for (int i = b + 2 + tid; i < m0; i += kTailThreads) vn[i] *= scale;
-    __syncthreads();
-    // rows k + 2 .. n - 1 of A^(k+1) (in place) and of p_{k+1}
-    for (int i = b + 1 + wave; i < m0; i += kWaves) {
-      const double vi = vk[i], wi = wk[i];
-      double acc = 0.0;
-      for (int j = b + 1 + lane; j < m0; j += 64) {
-        const double v = am[i * LD + j] - vi * wk[j] - wi * vk[j];
-        am[i * LD + j] = v;
-        if (k == n - 3 && tid == 0) s.d[n - 1] = v;  // the last step: i = j = n - 1
-        acc += v * (j == b + 1 ? 1.0 : vn[j]);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int i = lane + 64 * q;
+        if (k > k0) pq[q] = tau * ps[i];
+        if (i < c) pq[q] = vq[q] = 0.0;
+        dot += pq[q] * vq[q];
       }
-      acc = wave_sum(acc);
-      if (lane == 0) pk[i] = tau * acc;
+      const double kk = 0.5 * tau * wave_sum_dpp(dot);
+      double wq[4], cq[4], sig = 0.0;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) wq[q] = pq[q] - kk * vq[q];
+      const double v1 = entry(vq, c), w1 = entry(wq, c);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int i = lane + 64 * q;
+        cq[q] = col[i] - v1 * wq[q] - w1 * vq[q];
+        if (i >= c + 2) sig += cq[q] * cq[q];
+      }
+      const double sigma = wave_sum_dpp(sig);
+      const double d_next = entry(cq, c), alpha = entry(cq, c + 1);
+      double beta = alpha, scale = 0.0;
+      tau = 0.0;
+      if (!(sigma == 0.0)) {
+        // tau = (beta - alpha) / beta and scale = 1 / (alpha - beta) from one division
+        const double norm = sqrt(alpha * alpha + sigma);
+        beta = alpha >= 0.0 ? -norm : norm;
+        const double diff = alpha - beta, inv = 1.0 / (beta * diff);
+        tau = -diff * diff * inv;
+        scale = beta * inv;
+      }
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int i = lane + 64 * q;
+        vs[i] = i > c ? vq[q] : 0.0;
+        ws[i] = i > c ? wq[q] : 0.0;
+        vq[q] = i > c + 1 ? cq[q] * scale : (i == c + 1 ? 1.0 : 0.0);
+        if (i >= m0) vq[q] = 0.0;
+        ns[i] = vq[q];
+      }
+      if (lane == 0) {
+        s.d[k + 1] = d_next;
+        s.e[k + 1] = beta;
+        s.tau[k + 1] = tau;
+      }
     }
-    // reflector k + 1 where the per-column launches keep it, and T's entries
-    double* vrow = ((k + 1) & 1 ? s.x : s.y) + static_cast<int64_t>(k + 1) * n;
-    for (int i = b + 1 + tid; i < m0; i += kTailThreads) vrow[o + i] = i == b + 1 ? 1.0 : vn[i];
-    if (tid == 0) {
-      s.d[k + 1] = d_next;
-      s.e[k + 1] = beta;
-      s.tau[k + 1] = tau;
+    lds_barrier();
+    // reflector k + 1 where the per-column launches keep it
+    if (tid < kTailN && tid > c && tid < m0)
+      (((k + 1) & 1) ? s.x : s.y)[static_cast<int64_t>(k + 1) * n + o + tid] = ns[tid];
+    // A^(k+1) on [c + 1, m0)^2 and the sums of A^(k+1) v_{k+1}; column c + 1 for the next step
+    double vi[kRB], wi[kRB], ni[kRB], rs[kRB];
+#pragma unroll
+    for (int r = 0; r < kRB; ++r) {
+      vi[r] = vs[ty + 32 * r];
+      wi[r] = ws[ty + 32 * r];
+      ni[r] = ns[ty + 32 * r];
+      rs[r] = 0.0;
     }
-    __syncthreads();  // pk and am are the next step's
-    // the next step's reflector: v_{k+1} (first entry 1)
-    for (int i = b + 1 + tid; i < m0; i += kTailThreads) vk[i] = i == b + 1 ? 1.0 : vn[i];
-    tau_k = tau;
-    __syncthreads();
+#pragma unroll
+    for (int b = 0; b < kCB; ++b) {
+      if (16 * b + 15 <= c || 16 * b >= m0) continue;  // columns all done, or past the end
+      const double vj = vs[tx + 16 * b], wj = ws[tx + 16 * b], nj = ns[tx + 16 * b];
+      double cs = 0.0;
+#pragma unroll
+      for (int r = b / 2; r < kRB; ++r) {
+        am[r][b] = am[r][b] - vi[r] * wj - wi[r] * vj;
+        rs[r] += am[r][b] * nj;
+        if (r > b / 2) cs += am[r][b] * ni[r];
+      }
+      if (b / 2 + 1 < kRB) cpart[ty][tx + 16 * b] = cs;
+      if (b == (c + 1) / 16 && tx == ((c + 1) & 15)) {
+#pragma unroll
+        for (int r = b / 2; r < kRB; ++r) col[ty + 32 * r] = am[r][b];
+      }
+    }
+#pragma unroll
+    for (int r = 0; r < kRB; ++r) rpart[tx][ty + 32 * r] = rs[r];
+    lds_barrier();
+    {
+      // two threads per entry: half of its column's and half of its row's partial sums each
+      const int i = tid >> 1, h = tid & 1;
+      double t = 0.0;
+#pragma unroll
+      for (int m = 0; m < 16; ++m) t += cpart[16 * h + m][i];
+#pragma unroll
+      for (int m = 0; m < 8; ++m) t += rpart[8 * h + m][i];
+      t += dpp_f64<0xB1>(t);
+      if (h == 0) ps[i] = t;
+    }
+    lds_barrier();
   }
+  if (tid == 0) s.d[n - 1] = col[m0 - 1];
 }
 
 // ---- bisection -------------------------------------------------------------------------------
 // Number of eigenvalues of T below x (Sturm count of the LDL^T pivots of T - x I); a pivot smaller
-// in magnitude than pivmin counts as -pivmin.
+// in magnitude than pivmin counts as -pivmin.  The pivots are a chain, so the quotient is the hardware
+// reciprocal with two Newton steps (within an ulp; pivmin keeps the pivot normal) instead of an IEEE
+// division, about half its latency.
 __device__ inline int sturm_count(const double* d, const double* e2, int n, double x, double pivmin) {
   double q = d[0] - x;
   if (fabs(q) < pivmin) q = -pivmin;
   int c = q < 0.0 ? 1 : 0;
+#pragma unroll 8
   for (int i = 1; i < n; ++i) {
-    q = (d[i] - x) - e2[i - 1] / q;
+    double r = __builtin_amdgcn_rcp(q);
+    r = fma(fma(-q, r, 1.0), r, r);
+    r = fma(fma(-q, r, 1.0), r, r);
+    q = fma(-e2[i - 1], r, d[i] - x);
     if (fabs(q) < pivmin) q = -pivmin;
     c += q < 0.0 ? 1 : 0;
   }
@@ -1003,14 +1107,14 @@ __device__ inline void gershgorin(const double* d, const double* ae, int n, doub
   }
 }
 
-// One wave per workgroup, four eigenvalues per wave, each by 16 lanes: lam[j] = the (j+1)-th
-// largest.  Every round the 16 lanes take Sturm counts at 16 evenly spaced interior points of the
-// bracket, which then shrinks to the pair of neighbouring points (ends included) between which the
-// count passes j's ascending index: a 17-fold cut per round, until the bracket is below an absolute
-// 2^-52 ||T|| plus a relative 2^-51.
-constexpr int kSectionLanes = 16;
+// One wave per eigenvalue: lam[j] = the (j+1)-th largest.  Every round the 64 lanes take Sturm counts
+// at 64 evenly spaced interior points of the bracket, which then shrinks to the pair of neighbouring
+// points (ends included) between which the count passes j's ascending index: a 65-fold cut per round (9
+// rounds; 16 lanes need 13), until the bracket is below an absolute 2^-52 ||T|| plus a relative 2^-51.
+constexpr int kSectionLanes = 64;
+template <int N>  // n <= N: the LDS decides how many waves a CU holds
 __global__ __launch_bounds__(64) void fit_bisect_kernel(const SolveArgs a) {
-  __shared__ double d[kMaxN], e2[kMaxN], ae[kMaxN];
+  __shared__ double d[N], e2[N], ae[N];
   const int layer = blockIdx.y, n = 2 * a.w;
   const Slots s = slots(a.work, a.w, layer);
   const int r = static_cast<int>(s.job->rank);
@@ -1027,23 +1131,21 @@ __global__ __launch_bounds__(64) void fit_bisect_kernel(const SolveArgs a) {
   const double tnorm = fmax(fmax(fabs(lo0), fabs(hi0)), 1e-280);
   if (blockIdx.x == 0 && threadIdx.x == 0) s.job->tnorm = tnorm;
   const int lane = threadIdx.x & (kSectionLanes - 1);
-  const int j = blockIdx.x * (64 / kSectionLanes) + threadIdx.x / kSectionLanes;
-  // the 16 lanes of an eigenvalue share every branch below; whole groups past r are idle
+  const int j = blockIdx.x;
   const bool live = j < r;
   const double atol = kEps * tnorm, pivmin = kEps * tnorm;
   const int t = n - 1 - j;  // ascending index
   double lo = lo0 - atol, hi = hi0 + atol;
   for (int it = 0; it < 64; ++it) {
     if (hi - lo <= atol + 2.0 * kEps * fmax(fabs(lo), fabs(hi))) break;
-    // point k = 1 .. 16 at lo + k step; the new ends are points (or the old ends), so the counts
+    // point k = 1 .. 64 at lo + k step; the new ends are points (or the old ends), so the counts
     // already taken there hold for them
     const double step = (hi - lo) * (1.0 / (kSectionLanes + 1));
     const double x = lo + step * (lane + 1);
     const bool below = live && sturm_count(d, e2, n, x, pivmin) <= t;
-    // lanes of this group whose point lies below the eigenvalue (a prefix of the group)
+    // lanes whose point lies below the eigenvalue (a prefix)
     const uint64_t m = __ballot(below);
-    const int group = threadIdx.x & ~(kSectionLanes - 1);
-    const int kb = __popcll((m >> group) & ((1ull << kSectionLanes) - 1));
+    const int kb = __popcll(m);
     const double nlo = kb > 0 ? lo + step * kb : lo;
     const double nhi = kb < kSectionLanes ? lo + step * (kb + 1) : hi;
     lo = nlo;
@@ -1075,87 +1177,121 @@ struct Strided {
   __device__ double& operator[](int i) const { return p[i * stride]; }
 };
 
-// The four vectors one eigenvector's inverse iteration works on: the vector and its LU factors.
+// What one eigenvector's inverse iteration works on: the vector, the LU factors of T - sigma I under
+// partial pivoting (inverse diagonal, two superdiagonals, multipliers) and the row swaps.
 struct InverseWork {
-  Strided y, u0, u1, u2;
+  Strided y, u0, u1, u2, mult;
+  uint8_t* swap;
+  int swap_stride;
 };
 
-// Inverse iteration for the cluster of eigenvalues lam[j .. last] (one thread).  Member m works in
-// work(m); every finished vector m is stored at out(m) (Y[i][m] of the layer), which is also where
-// the orthogonalisation reads the earlier members.
-template <typename WorkFn, typename OutFn>
+// Inverse iteration for the cluster of eigenvalues lam[j .. last] (one thread).  Every finished vector m
+// is stored at out(m) (Y[i][m] of the layer), which is also where the orthogonalisation reads the
+// earlier members.  n is a multiple of kInvChunk.  The factors do not change between the solves of one
+// eigenvalue, so they are formed once and no solve divides; the solves read kInvChunk entries ahead of
+// the recurrence (which is one fma a step forward, two back), and the sums of a vector come out of its
+// back substitution.
+constexpr int kInvChunk = 8;
+template <typename OutFn>
 __device__ inline void inverse_cluster(const double* d, const double* e, int n, const double* lam,
-                                       int j, int last, double tnorm, WorkFn work, OutFn out) {
+                                       int j, int last, double tnorm, const InverseWork& wk, OutFn out) {
   const double pert = 10.0 * kEps * tnorm, ptol = kEps * tnorm;
+  const Strided y = wk.y, u0 = wk.u0, u1 = wk.u1, u2 = wk.u2, mult = wk.mult;
   double sigma = 0.0;
   for (int m = j; m <= last; ++m) {
-    const InverseWork wk = work(m);
-    const Strided y = wk.y, u0 = wk.u0, u1 = wk.u1, u2 = wk.u2;
     // shifts inside a cluster step down by at least pert, so the solves stay independent
     sigma = m == j ? lam[m] : fmin(lam[m], sigma - pert);
-    for (int i = 0; i < n; ++i) y[i] = start_entry(i, m);
-    double sc = 2.0;  // the start vector's entries lie in [-1/2, 1/2)
-    for (int it = 0; it < kInverseSolves; ++it) {
-      // forward elimination of (T - sigma I) y = b / max|b| with partial pivoting; rows hold
-      // (c0, c1) on the diagonal and the superdiagonal, the right-hand side rides along
+    {
+      // elimination of T - sigma I; a row holds (c0, c1) on the diagonal and the superdiagonal
       double c0 = d[0] - sigma, c1 = n > 1 ? e[0] : 0.0;
-      double yc = y[0] * sc;
       for (int i = 0; i < n - 1; ++i) {
         const double sub = e[i], a1 = d[i + 1] - sigma, b1 = i + 1 < n - 1 ? e[i + 1] : 0.0;
-        const double nb = y[i + 1] * sc;
-        if (fabs(c0) >= fabs(sub)) {
-          const double piv = guard_pivot(c0, ptol);
-          const double mult = sub / piv;
-          u0[i] = piv;
-          u1[i] = c1;
-          u2[i] = 0.0;
-          y[i] = yc;
-          yc = nb - mult * yc;
-          c0 = a1 - mult * c1;
-          c1 = b1;
-        } else {
-          const double mult = c0 / sub;
-          u0[i] = sub;
-          u1[i] = a1;
-          u2[i] = b1;
-          y[i] = nb;
-          yc = yc - mult * nb;
-          c0 = c1 - mult * a1;
-          c1 = -mult * b1;
-        }
+        const bool keep = fabs(c0) >= fabs(sub);
+        const double piv = keep ? guard_pivot(c0, ptol) : sub;
+        const double inv = 1.0 / piv;
+        const double ml = (keep ? sub : c0) / piv;
+        u0[i] = inv;
+        u1[i] = keep ? c1 : a1;
+        u2[i] = keep ? 0.0 : b1;
+        mult[i] = ml;
+        wk.swap[i * wk.swap_stride] = keep ? 0 : 1;
+        const double n0 = keep ? a1 - ml * c1 : c1 - ml * a1;
+        c1 = keep ? b1 : -ml * b1;
+        c0 = n0;
       }
-      u0[n - 1] = guard_pivot(c0, ptol);
-      y[n - 1] = yc;
+      u0[n - 1] = 1.0 / guard_pivot(c0, ptol);
+      u1[n - 1] = u2[n - 1] = mult[n - 1] = 0.0;
+      wk.swap[(n - 1) * wk.swap_stride] = 0;
+    }
+    for (int i = 0; i < n; ++i) y[i] = start_entry(i, m);
+    double sc = 2.0;  // the start vector's entries lie in [-1/2, 1/2)
+    double ss = 0.0, mx = 0.0;
+    for (int it = 0; it < kInverseSolves; ++it) {
+      // forward: the right-hand side b / max|b| through the elimination
+      double yc = y[0] * sc;
+      for (int i0 = 0; i0 < n; i0 += kInvChunk) {
+        double nb[kInvChunk], ml[kInvChunk], yo[kInvChunk];
+        int sw[kInvChunk];
+#pragma unroll
+        for (int u = 0; u < kInvChunk; ++u) {
+          nb[u] = y[i0 + u + 1 < n ? i0 + u + 1 : n - 1] * sc;
+          ml[u] = mult[i0 + u];
+          sw[u] = wk.swap[(i0 + u) * wk.swap_stride];
+        }
+#pragma unroll
+        for (int u = 0; u < kInvChunk; ++u) {
+          // the last row has nothing below it: its value is the running one
+          yo[u] = sw[u] ? nb[u] : yc;
+          yc = sw[u] ? yc - ml[u] * nb[u] : nb[u] - ml[u] * yc;
+        }
+#pragma unroll
+        for (int u = 0; u < kInvChunk; ++u) y[i0 + u] = yo[u];
+      }
       // back substitution, in place
       double x1 = 0.0, x2 = 0.0;
-      for (int i = n - 1; i >= 0; --i) {
-        double v = y[i];
-        if (i + 1 < n) v -= u1[i] * x1;
-        if (i + 2 < n) v -= u2[i] * x2;
-        v /= u0[i];
-        y[i] = v;
-        x2 = x1;
-        x1 = v;
+      ss = 0.0;
+      mx = 0.0;
+      for (int i0 = n - kInvChunk; i0 >= 0; i0 -= kInvChunk) {
+        double v[kInvChunk], a0[kInvChunk], a1[kInvChunk], a2[kInvChunk];
+#pragma unroll
+        for (int u = 0; u < kInvChunk; ++u) {
+          v[u] = y[i0 + u];
+          a0[u] = u0[i0 + u];
+          a1[u] = u1[i0 + u];
+          a2[u] = u2[i0 + u];
+        }
+#pragma unroll
+        for (int u = kInvChunk - 1; u >= 0; --u) {
+          v[u] = (v[u] - a2[u] * x2 - a1[u] * x1) * a0[u];
+          x2 = x1;
+          x1 = v[u];
+          ss += v[u] * v[u];
+          mx = fmax(mx, fabs(v[u]));
+        }
+#pragma unroll
+        for (int u = 0; u < kInvChunk; ++u) y[i0 + u] = v[u];
       }
-      // orthogonalise against the cluster's earlier vectors, then normalise
-      for (int q = j; q < m; ++q) {
-        const Strided yq = out(q);
-        double dot = 0.0;
-        for (int i = 0; i < n; ++i) dot += yq[i] * y[i];
-        for (int i = 0; i < n; ++i) y[i] -= dot * yq[i];
+      if (m > j) {
+        // orthogonalise the normalised vector against the cluster's earlier ones
+        const double inv = 1.0 / sqrt(ss);
+        for (int i = 0; i < n; ++i) y[i] *= inv;
+        for (int q = j; q < m; ++q) {
+          const Strided yq = out(q);
+          double dot = 0.0;
+          for (int i = 0; i < n; ++i) dot += yq[i] * y[i];
+          for (int i = 0; i < n; ++i) y[i] -= dot * yq[i];
+        }
+        ss = mx = 0.0;
+        for (int i = 0; i < n; ++i) {
+          ss += y[i] * y[i];
+          mx = fmax(mx, fabs(y[i]));
+        }
       }
-      double ss = 0.0, mx = 0.0;
-      for (int i = 0; i < n; ++i) {
-        ss += y[i] * y[i];
-        mx = fmax(mx, fabs(y[i]));
-      }
-      const double inv = 1.0 / sqrt(ss);
-      for (int i = 0; i < n; ++i) y[i] *= inv;
-      sc = mx > 0.0 ? 1.0 / (mx * inv) : 1.0;  // 1 / max|y| of the normalised vector
+      sc = mx > 0.0 ? 1.0 / mx : 1.0;
     }
     const Strided o = out(m);
-    if (o.p != y.p)
-      for (int i = 0; i < n; ++i) o[i] = y[i];
+    const double inv = 1.0 / sqrt(ss);
+    for (int i = 0; i < n; ++i) o[i] = y[i] * inv;
   }
 }
 
@@ -1171,14 +1307,17 @@ __device__ inline bool cluster_of(const double* lam, int r, int j, double ctol, 
 
 // Inverse iteration, one eigenvector per working thread: the thread keeps its vector and the LU
 // factors of T - sigma I in LDS ([i][thread], THREADS interleaved, so the threads' accesses fall in
-// distinct banks) and copies each finished vector to Y[i][m].  Two instances: 16 threads per
-// workgroup for n <= 256, and one thread per workgroup (96 KiB of LDS) for larger n; the chain of
-// dependent accesses would otherwise wait on global memory at each link.
-constexpr int kInverseLdsN = 256, kInverseLdsThreads = 16;
+// distinct banks) and copies each finished vector to Y[i][m].  Two instances: 8 threads per workgroup
+// for n <= 256, and one thread per workgroup (82 KiB of LDS) for larger n; the chain of dependent
+// accesses would otherwise wait on global memory at each link.  28 layers x 64 vectors of 256 150 us, 2
+// layers x 128 vectors of 2048 1.1 ms (a division per row in every solve, and the sums in passes of their
+// own: 362 us and 2.9 ms).
+constexpr int kInverseLdsN = 256, kInverseLdsThreads = 8;
 template <int N, int THREADS>
 __global__ __launch_bounds__(64) void fit_inverse_lds_kernel(const SolveArgs a) {
   __shared__ double d[N], e[N];
-  __shared__ double vec[4 * N * THREADS];
+  __shared__ double vec[5 * N * THREADS];
+  __shared__ uint8_t swap[N * THREADS];
   const int layer = blockIdx.y, n = 2 * a.w;
   const Slots s = slots(a.work, a.w, layer);
   const int r = static_cast<int>(s.job->rank);
@@ -1197,114 +1336,93 @@ __global__ __launch_bounds__(64) void fit_inverse_lds_kernel(const SolveArgs a) 
   auto lds = [&](int q) { return Strided{vec + q * kPlane + t, THREADS}; };
   inverse_cluster(
       d, e, n, s.lam, j, last, tnorm,
-      [&](int) { return InverseWork{lds(0), lds(1), lds(2), lds(3)}; },
+      InverseWork{lds(0), lds(1), lds(2), lds(3), lds(4), swap + t, THREADS},
       [&](int m) { return Strided{s.z + m, r}; });
 }
 
 // ---- back-transformation and sign ---------------------------------------------------------------
-// kBackCols columns of Y per workgroup, held in LDS while the reflectors n-3 .. 0 are applied in
-// turn (Y <- (I - tau_j v_j v_j^T) Y); thread t keeps rows i = t / kBackCols (mod kSolveThreads /
-// kBackCols) of column t % kBackCols.  Then each column's first entry of largest magnitude is made
-// positive.  Each reflector costs every column about 3n LDS accesses, so few columns per
-// workgroup (and more workgroups) shorten the chain.
-template <int kBackCols>
-__global__ __launch_bounds__(kSolveThreads) void fit_back_kernel(const SolveArgs a) {
-  __shared__ double yc[kMaxN * kBackCols];
-  __shared__ double vb[kMaxN];
-  __shared__ double red[kSolveThreads / 64][kBackCols];
-  __shared__ int redi[kSolveThreads / 64][kBackCols];
-  const int layer = blockIdx.y, n = 2 * a.w, tid = threadIdx.x;
+// One wave per column of Y: the column stays in registers (entry lane + 64 q) while the reflectors
+// n-3 .. 0 are applied in turn (y <- y - tau_j (v_j . y) v_j), each loaded while the one before is
+// applied.  The n - 2 reflectors are a chain, and a wave's sum needs no barrier: n = 256, 28 layers x
+// 64 columns 103 us, n = 2048, 2 layers x 128 columns 0.96 ms (8 columns per workgroup in LDS, three barriers
+// per reflector: 330 us and 3.5 ms).  Then the column's first entry of largest magnitude is made
+// positive.  NQ: entries per lane, n <= 64 NQ (MASK: n < 64 NQ).  The
+// reflectors run in groups of 64 kGrp whose first live entry register is a constant, so the loops hold no
+// tests of it.
+template <int NQ, bool MASK, int Q0>
+__device__ __forceinline__ void back_group(const Slots& s, int n, int j1, double (&y)[NQ]) {
+  constexpr int kGrp = NQ >= 16 ? 4 : 1;
+  if constexpr (Q0 >= 0) {
+    // reflectors j1 .. 64 Q0 - 1 (down to 0 in the last group): entries past j, all in registers >= Q0
+    const int j0 = Q0 == 0 ? 0 : 64 * Q0 - 1, lane = threadIdx.x;
+    double cur[NQ], nxt[NQ], tnxt = 0.0;
+    auto fetch = [&](int j) {
+      tnxt = s.tau[j];
+      const double* vrow = reflector_rows(s, j) + static_cast<int64_t>(j) * n;
+#pragma unroll
+      for (int q = Q0; q < NQ; ++q) {
+        const int i = lane + 64 * q;
+        const double v = vrow[MASK && i >= n ? n - 1 : i];
+        nxt[q] = (q < Q0 + kGrp && i <= j) || (MASK && i >= n) ? 0.0 : v;
+      }
+    };
+    if (j1 >= j0) fetch(j1);
+    for (int j = j1; j >= j0; --j) {
+      const double t = tnxt;
+#pragma unroll
+      for (int q = Q0; q < NQ; ++q) cur[q] = nxt[q];
+      fetch(j > j0 ? j - 1 : j0);
+      double dot = 0.0;
+#pragma unroll
+      for (int q = Q0; q < NQ; ++q) dot += cur[q] * y[q];
+      const double f = t * wave_sum_dpp(dot);
+      if (t == 0.0) continue;
+#pragma unroll
+      for (int q = Q0; q < NQ; ++q) y[q] -= f * cur[q];
+    }
+    back_group<NQ, MASK, Q0 - kGrp>(s, n, j0 - 1 < j1 ? j0 - 1 : j1, y);
+  }
+}
+
+template <int NQ, bool MASK>
+__global__ __launch_bounds__(64) void fit_back_kernel(const SolveArgs a) {
+  const int layer = blockIdx.y, n = 2 * a.w, lane = threadIdx.x;
   const Slots s = slots(a.work, a.w, layer);
-  const int r = static_cast<int>(s.job->rank);
-  const int c0 = blockIdx.x * kBackCols;
-  if (c0 >= r) return;
-  constexpr int kGroups = kSolveThreads / kBackCols;  // row groups
-  const int c = tid % kBackCols, g = tid / kBackCols, lane = tid & 63, wave = tid >> 6;
-  const bool live = c0 + c < r;
-  for (int e = tid; e < n * kBackCols; e += kSolveThreads) {
-    const int i = e / kBackCols, cc = e % kBackCols;
-    yc[e] = c0 + cc < r ? s.z[static_cast<int64_t>(i) * r + c0 + cc] : 0.0;
+  const int r = static_cast<int>(s.job->rank), c = blockIdx.x;
+  if (c >= r) return;
+  double y[NQ];
+#pragma unroll
+  for (int q = 0; q < NQ; ++q) {
+    const int i = lane + 64 * q;
+    y[q] = i < n ? s.z[static_cast<int64_t>(i) * r + c] : 0.0;
   }
-  // Reflector jr - 1 (its tau and this thread's entries of its row) is loaded into registers while
-  // reflector jr is applied, so the chain of n - 2 reflectors does not wait on a global load at
-  // each link; the barriers inside the chain only order LDS accesses (lds_barrier), so the loads
-  // stay in flight across them.
-  constexpr int kPer = kMaxN / kSolveThreads;
-  double nxt[kPer];
-  double tnext = 0.0;
-  auto fetch = [&](int jr) {
-    if (jr < 0) return;
-    tnext = s.tau[jr];
-    const double* vrow = reflector_rows(s, jr) + static_cast<int64_t>(jr) * n;
-#pragma unroll
-    for (int q = 0; q < kPer; ++q) {
-      const int i = jr + 1 + tid + q * kSolveThreads;
-      nxt[q] = i < n ? vrow[i] : 0.0;
-    }
-  };
-  __syncthreads();  // Y is in LDS
-  fetch(n - 3);
-  for (int jr = n - 3; jr >= 0; --jr) {
-    const double t = tnext;
-    double cur[kPer];
-#pragma unroll
-    for (int q = 0; q < kPer; ++q) cur[q] = nxt[q];
-    fetch(jr - 1);
-    if (t == 0.0) continue;
-    lds_barrier();  // the previous reflector's vb and red reads are done
-#pragma unroll
-    for (int q = 0; q < kPer; ++q) {
-      const int i = jr + 1 + tid + q * kSolveThreads;
-      if (i < n) vb[i] = cur[q];
-    }
-    lds_barrier();
-    double part = 0.0;
-    for (int i = jr + 1 + g; i < n; i += kGroups) part += vb[i] * yc[i * kBackCols + c];
-    // the row groups of a wave that share column c sit kBackCols lanes apart
-    for (int o = kBackCols; o < 64; o <<= 1) part += __shfl_xor(part, o, 64);
-    if (lane < kBackCols) red[wave][lane] = part;
-    lds_barrier();
-    double dot = 0.0;
-    for (int q = 0; q < kSolveThreads / 64; ++q) dot += red[q][c];
-    const double f = t * dot;
-    for (int i = jr + 1 + g; i < n; i += kGroups) yc[i * kBackCols + c] -= f * vb[i];
-  }
-  // sign: the first entry of largest magnitude of each column made positive
-  __syncthreads();  // the last reflector's red reads and Y updates are done
-  double best = -1.0;
+  back_group<NQ, MASK, NQ - (NQ >= 16 ? 4 : 1)>(s, n, n - 3, y);
+  double best = -1.0, val = 0.0;
   int bi = 0;
-  for (int i = g; i < n; i += kGroups) {
-    const double v = fabs(yc[i * kBackCols + c]);
-    if (v > best) {
-      best = v;
+#pragma unroll
+  for (int q = 0; q < NQ; ++q) {
+    const int i = lane + 64 * q;
+    if (i < n && fabs(y[q]) > best) {
+      best = fabs(y[q]);
+      val = y[q];
       bi = i;
     }
   }
-  for (int o = kBackCols; o < 64; o <<= 1) {
-    const double ob = __shfl_xor(best, o, 64);
+  for (int o = 32; o > 0; o >>= 1) {
+    const double ob = __shfl_xor(best, o, 64), ov = __shfl_xor(val, o, 64);
     const int oi = __shfl_xor(bi, o, 64);
     if (ob > best || (ob == best && oi < bi)) {
       best = ob;
+      val = ov;
       bi = oi;
     }
   }
-  if (lane < kBackCols) {
-    red[wave][lane] = best;
-    redi[wave][lane] = bi;
+  const double sg = val < 0.0 ? -1.0 : 1.0;
+#pragma unroll
+  for (int q = 0; q < NQ; ++q) {
+    const int i = lane + 64 * q;
+    if (i < n) s.z[static_cast<int64_t>(i) * r + c] = sg * y[q];
   }
-  __syncthreads();
-  best = red[0][c];
-  bi = redi[0][c];
-  for (int q = 1; q < kSolveThreads / 64; ++q) {
-    if (red[q][c] > best || (red[q][c] == best && redi[q][c] < bi)) {
-      best = red[q][c];
-      bi = redi[q][c];
-    }
-  }
-  const double sg = yc[bi * kBackCols + c] < 0.0 ? -1.0 : 1.0;
-  if (live)
-    for (int i = g; i < n; i += kGroups)
-      s.z[static_cast<int64_t>(i) * r + c0 + c] = sg * yc[i * kBackCols + c];
 }
 
 // ---- fp64 tiled products ------------------------------------------------------------------------
@@ -1345,11 +1463,11 @@ __global__ __launch_bounds__(kSolveThreads) void fit_project_kernel(const SolveA
   const int r = static_cast<int>(jb.rank);
   const int i0 = blockIdx.x * 64, m0 = blockIdx.y * 64;
   if (m0 >= r) return;
-  const bool center = a.center != 0;
+  const double inv = a.center ? 1.0 / a.rows : 0.0;
   tile_product(
       n,
       // G_c is symmetric: its column i0 + x read as a row, so the loads run along rows
-      [&](int kk, int x) { return centred(jb.gram, jb.colsum, n, kk, i0 + x, a.rows, center); },
+      [&](int kk, int x) { return centred(jb.gram, jb.colsum, n, kk, i0 + x, inv); },
       [&](int kk, int x) {
         return m0 + x < r ? s.z[static_cast<int64_t>(kk) * r + m0 + x] : 0.0;
       },
@@ -1381,150 +1499,190 @@ __global__ __launch_bounds__(kSolveThreads) void fit_normal_kernel(const SolveAr
     const int nt = w / 64;
     if (static_cast<int>(blockIdx.x) >= nt * nt) return;
     const int i0 = (blockIdx.x / nt) * 64, j0 = (blockIdx.x % nt) * 64;
-    const bool center = a.center != 0;
+    const double inv = a.center ? 1.0 / a.rows : 0.0;
     for (int e = threadIdx.x; e < 64 * 64; e += kSolveThreads) {
       const int i = i0 + e / 64, j = j0 + e % 64;
       s.x[static_cast<int64_t>(i) * w + j] =
-          centred(jb.gram, jb.colsum, n, i, j, a.rows, center) + (i == j ? a.lambda : 0.0);
+          centred(jb.gram, jb.colsum, n, i, j, inv) + (i == j ? a.lambda : 0.0);
     }
   }
 }
 
-// ---- Cholesky, one column per launch --------------------------------------------------------------
-// grid.y = 0: A^T A + lam I (X, size w), 1: Z^T Z + lam I (Y, size r).  Step k reads column k on and
-// below the diagonal, updates rows (k, s) of the lower triangle (a workgroup's kSolveRowsWide rows),
-// and stores L[i][k] twice, in places nothing reads before the solves: at [k][i] in the upper
-// triangle (column k of L as a row) and at [i][k] of a row-major copy of L just past the matrix.
-// L[k][k] goes to ldiag.  A non-positive pivot leaves NaN, which reaches every output of the layer.
-__global__ __launch_bounds__(kSolveThreads) void fit_chol_kernel(const SolveArgs a) {
-  __shared__ double lc[kFitMaxSolveWidth];
-  const int layer = blockIdx.z, w = a.w, k = a.step, tid = threadIdx.x;
+// ---- Cholesky, 64 columns per pair of launches ------------------------------------------------------
+// grid.y = 0: A^T A + lam I (X, size w), 1: Z^T Z + lam I (Y, size r).  Panel p holds columns
+// [64 p, 64 p + 64).  The panel launch factors the panel's diagonal block (every workgroup for itself)
+// and solves one 64-row block below it per workgroup in the same steps; the update launch takes
+// the panel's part off the trailing lower triangle, a 64 x 64 tile per workgroup.  L[i][k] (i > k) is
+// stored twice, in places nothing reads before the solves: at [k][i] in the upper triangle (column k of
+// L as a row) and at [i][k] of a row-major copy of L just past the matrix; 1 / L[k][k] goes to ldiag.  A
+// non-positive pivot leaves NaN, which reaches every output of the layer.  (One column per launch took
+// 7.6 ms at w = 1024; one workgroup per matrix in LDS took 140 us at w = 128.)
+constexpr int kPanel = 64;
+
+__global__ __launch_bounds__(kSolveThreads) void fit_chol_panel_kernel(const SolveArgs a) {
+  constexpr int LD = kPanel + 1;
+  __shared__ double dg[kPanel][LD], xb[kPanel][LD];  // the diagonal block; this workgroup's rows below
+  __shared__ double lt[kPanel][LD];                  // lt[k][j] = L[j][k], [k][k]: its inverse
+  const int layer = blockIdx.z, w = a.w, tid = threadIdx.x;
   const Slots s = slots(a.work, a.w, layer);
   const int r = static_cast<int>(s.job->rank);
   const bool zz = blockIdx.y == 1;
-  const int sz = zz ? r : w;
-  if (k >= sz) return;
+  const int sz = zz ? r : w, k0 = a.step * kPanel;
+  const int row0 = k0 + kPanel * static_cast<int>(blockIdx.x);  // first row of the block it stores
+  if (row0 >= sz) return;
+  const bool below = blockIdx.x > 0;
+  const int kn = sz - k0 < kPanel ? sz - k0 : kPanel;  // columns of the panel
   double* mat = zz ? s.y : s.x;
+  double* copy = mat + static_cast<int64_t>(sz) * sz;
   double* ldiag = s.ldiag + (zz ? w : 0);
-  const double piv = mat[static_cast<int64_t>(k) * sz + k];
-  const double lkk = piv > 0.0 ? sqrt(piv) : kNaN;
-  for (int i = k + 1 + tid; i < sz; i += kSolveThreads) lc[i] = mat[static_cast<int64_t>(i) * sz + k] / lkk;
-  __syncthreads();
-  const int lane = tid & 63, wave = tid >> 6;
-  const int r0 = k + 1 + blockIdx.x * kSolveRowsWide;
-  for (int i = r0 + wave; i < r0 + kSolveRowsWide && i < sz; i += kSolveThreads / 64) {
-    const double li = lc[i];
-    double* row = mat + static_cast<int64_t>(i) * sz;
-    for (int j = k + 1 + lane; j <= i; j += 64) row[j] -= li * lc[j];
-    if (lane == 0) {
-      mat[static_cast<int64_t>(k) * sz + i] = li;
-      mat[static_cast<int64_t>(sz) * sz + static_cast<int64_t>(i) * sz + k] = li;
-    }
+  const int i = tid & 63, g = tid >> 6;  // row of both blocks; columns k + 1 + g, step 4
+  // past the matrix's end: the identity, and rows of zeros
+  for (int q = g; q < kPanel; q += 4) {
+    dg[q][i] = q < kn && i < kn ? mat[static_cast<int64_t>(k0 + q) * sz + k0 + i] : (q == i ? 1.0 : 0.0);
+    xb[q][i] = below && row0 + q < sz ? mat[static_cast<int64_t>(row0 + q) * sz + k0 + i] : 0.0;
   }
-  if (blockIdx.x == 0 && tid == 0) ldiag[k] = lkk;
+  __syncthreads();
+  // column k of both blocks stays unscaled (every thread of a row reads it during step k)
+  for (int k = 0; k < kPanel; ++k) {
+    const double piv = dg[k][k];
+    const double inv = piv > 0.0 ? 1.0 / sqrt(piv) : kNaN;
+    const double l = dg[i][k] * inv, x = xb[i][k] * inv;
+    if (g == 0) lt[k][i] = i == k ? inv : l;
+    for (int j = k + 1 + g; j < kPanel; j += 4) {
+      const double lj = dg[j][k] * inv;
+      dg[i][j] -= l * lj;  // entries above the diagonal hold values nothing uses
+      xb[i][j] -= x * lj;
+    }
+    __syncthreads();
+  }
+  if (!below) {
+    for (int q = g; q < kn; q += 4) {
+      if (i > q && i < kn) mat[static_cast<int64_t>(k0 + q) * sz + k0 + i] = lt[q][i];
+      if (i < q) copy[static_cast<int64_t>(k0 + q) * sz + k0 + i] = lt[i][q];
+    }
+    if (tid < kn) ldiag[k0 + tid] = lt[tid][tid];
+    return;
+  }
+  for (int q = g; q < kPanel; q += 4) {  // a panel with rows below is whole
+    if (row0 + i < sz) mat[static_cast<int64_t>(k0 + q) * sz + row0 + i] = xb[i][q] * lt[q][q];
+    if (row0 + q < sz) copy[static_cast<int64_t>(row0 + q) * sz + k0 + i] = xb[q][i] * lt[i][i];
+  }
 }
 
-// The same factorisation for sizes up to kCholLdsN, one workgroup per matrix with the matrix in
-// LDS: one launch instead of one per column, and bit-identical to it (the same operations on every
-// entry in the same order).  grid.x = 0: A^T A + lam I, 1: Z^T Z + lam I.
-constexpr int kCholLdsN = 128, kCholThreads = 1024;
-__global__ __launch_bounds__(kCholThreads) void fit_chol_lds_kernel(const SolveArgs a) {
-  constexpr int LD = kCholLdsN + 1;
-  __shared__ double m[kCholLdsN * LD];
-  __shared__ double lc[kCholLdsN];
-  const int layer = blockIdx.y, w = a.w, tid = threadIdx.x;
+// Trailing update of panel a.step: tile (ti, tj), ti >= tj, of the rows and columns past the panel.
+__global__ __launch_bounds__(kSolveThreads) void fit_chol_update_kernel(const SolveArgs a) {
+  const int layer = blockIdx.z, w = a.w;
   const Slots s = slots(a.work, a.w, layer);
   const int r = static_cast<int>(s.job->rank);
-  const bool zz = blockIdx.x == 1;
-  const int sz = zz ? r : w;
+  const bool zz = blockIdx.y == 1;
+  const int sz = zz ? r : w, k0 = a.step * kPanel, first = k0 + kPanel;
+  if (first >= sz) return;
+  int ti = 0, rem = blockIdx.x;
+  while (rem > ti) rem -= ++ti;  // tile ti (ti + 1) / 2 + tj
+  const int i0 = first + ti * 64, j0 = first + rem * 64;
+  if (i0 >= sz) return;
   double* mat = zz ? s.y : s.x;
-  double* ldiag = s.ldiag + (zz ? w : 0);
-  for (int e = tid; e < sz * sz; e += kCholThreads) {
-    const int i = e / sz, j = e % sz;
-    if (j <= i) m[i * LD + j] = mat[static_cast<int64_t>(i) * sz + j];
-  }
-  __syncthreads();
-  for (int k = 0; k < sz; ++k) {
-    const double piv = m[k * LD + k];
-    const double lkk = piv > 0.0 ? sqrt(piv) : kNaN;
-    for (int i = k + 1 + tid; i < sz; i += kCholThreads) lc[i] = m[i * LD + k] / lkk;
-    if (tid == 0) ldiag[k] = lkk;
-    __syncthreads();
-    // rows by wave, the row's columns by lane
-    for (int i = k + 1 + (tid >> 6); i < sz; i += kCholThreads / 64) {
-      const double li = lc[i];
-      for (int j = k + 1 + (tid & 63); j <= i; j += 64) m[i * LD + j] -= li * lc[j];
-    }
-    // column k of L, as the per-column launches store it: the upper triangle and the row-major copy
-    for (int i = k + 1 + tid; i < sz; i += kCholThreads) {
-      mat[static_cast<int64_t>(k) * sz + i] = lc[i];
-      mat[static_cast<int64_t>(sz) * sz + static_cast<int64_t>(i) * sz + k] = lc[i];
-    }
-    __syncthreads();
-  }
+  // L[i][k] is read from the upper triangle, where a panel column is a row
+  tile_product(
+      kPanel,
+      [&](int kk, int x) {
+        return i0 + x < sz ? mat[static_cast<int64_t>(k0 + kk) * sz + i0 + x] : 0.0;
+      },
+      [&](int kk, int x) {
+        return j0 + x < sz ? mat[static_cast<int64_t>(k0 + kk) * sz + j0 + x] : 0.0;
+      },
+      [&](int x, int y, double v) {
+        const int i = i0 + x, j = j0 + y;
+        if (i < sz && j <= i) mat[static_cast<int64_t>(i) * sz + j] -= v;
+      });
 }
 
 // ---- triangular solves and outputs --------------------------------------------------------------
-__device__ inline double readlane_f64(double v, int lane) {
-  const int64_t b = __double_as_longlong(v);
-  const int lo = __builtin_amdgcn_readlane(static_cast<int>(b), lane);
-  const int hi = __builtin_amdgcn_readlane(static_cast<int>(b >> 32), lane);
-  return __longlong_as_double((static_cast<int64_t>(hi) << 32) | static_cast<uint32_t>(lo));
-}
-
-// One wave solves (L L^T) x = b for one right-hand side held in LDS (xs[i], lane i % 64 owns
-// entry i, so every LDS access is the lane's own).  Forward L y = b column by column: y_i =
-// b_i / L_ii, then b_j -= L[j][i] y_i for j > i with column i of L read as row i of the upper
-// triangle (`lu`, contiguous).  Backward L^T x = y the same way from the bottom: x_i = y_i / L_ii,
-// then y_j -= L[i][j] x_i for j < i with row i of L read from the row-major copy (`lr`).  The
-// entry of step i is broadcast from its owner lane.
-__device__ inline void wave_chol_solve(const double* lu, const double* lr, const double* diag,
-                                       int sz, double* xs) {
+// One wave solves (L L^T) x = b for one right-hand side in registers (entry lane + 64 q).  Forward
+// L y = b column by column: y_i = b_i / L_ii, then b_j -= L[j][i] y_i for j > i with column i of L read
+// as row i of the upper triangle (`lu`, contiguous).  Backward L^T x = y the same way from the bottom:
+// x_i = y_i / L_ii, then y_j -= L[i][j] x_i for j < i with row i of L read from the row-major copy
+// (`lr`).  The rows are loaded kAhead steps before use, so the chain of steps does not wait on a load
+// at each link (28 layers, w = 128: 65 us, 2 layers, w = 1024: 0.59 ms; with the vector in LDS and each row
+// loaded when its step came up, 204 us and 4.6 ms).
+template <int NQ>
+__device__ inline void wave_chol_solve(const double* lu, const double* lr, const double* inv, int sz,
+                                       double (&x)[NQ]) {
+  constexpr int kAhead = NQ <= 4 ? 4 : 2;
   const int lane = threadIdx.x & 63;
-  for (int i = 0; i < sz; ++i) {
-    double own = 0.0;
-    if ((i & 63) == lane) {
-      own = xs[i] / diag[i];
-      xs[i] = own;
+  // Steps run 64 at a time, so the registers a step touches are constants: q >= B going forward, q <= B
+  // going back.  Entries past the size read the row's last one; their x is never used.
+  auto block = [&](auto b_c, auto fwd_c) {
+    constexpr int B = decltype(b_c)::value;
+    constexpr bool FWD = decltype(fwd_c)::value != 0;
+    constexpr int QA = FWD ? B : 0, QZ = FWD ? NQ : B + 1;
+    const int i0 = 64 * B, i1 = sz < i0 + 64 ? sz : i0 + 64;  // steps [i0, i1), a multiple of 16 many
+    if (i0 >= sz) return;
+    const int first = FWD ? i0 : i1 - 1, dir = FWD ? 1 : -1, steps = i1 - i0;
+    const double* m = FWD ? lu : lr;
+    double row[kAhead][NQ], dg[kAhead];
+    auto load = [&](int t, int u) {
+      const int i = first + dir * (t < steps ? t : steps - 1);
+      dg[u] = inv[i];
+      const double* p = m + static_cast<int64_t>(i) * sz;
+#pragma unroll
+      for (int q = QA; q < QZ; ++q) {
+        const int j = lane + 64 * q;
+        row[u][q] = p[j < sz ? j : sz - 1];
+      }
+    };
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u) load(u, u);
+    for (int t = 0; t < steps; t += kAhead) {
+#pragma unroll
+      for (int u = 0; u < kAhead; ++u) {
+        const int i = first + dir * (t + u);
+        const double yi = readlane_f64(x[B], i & 63) * dg[u];
+        const double own = lane + i0 == i ? yi : x[B];
+        x[B] = (FWD ? lane + i0 > i : lane + i0 < i) ? x[B] - row[u][B] * yi : own;
+#pragma unroll
+        for (int q = QA; q < QZ; ++q)
+          if (q != B) x[q] -= row[u][q] * yi;
+        load(t + u + kAhead, u);
+      }
     }
-    const double yi = readlane_f64(own, i & 63);
-    const double* col = lu + static_cast<int64_t>(i) * sz;
-    for (int j = i + 1 + ((lane - i - 1) & 63); j < sz; j += 64) xs[j] -= col[j] * yi;
-  }
-  for (int i = sz - 1; i >= 0; --i) {
-    double own = 0.0;
-    if ((i & 63) == lane) {
-      own = xs[i] / diag[i];
-      xs[i] = own;
+  };
+  auto all = [&](auto self, auto b_c) {
+    constexpr int B = decltype(b_c)::value;
+    if constexpr (B < NQ) {
+      block(b_c, IntC<1>{});
+      self(self, IntC<B + 1>{});
+      block(b_c, IntC<0>{});
     }
-    const double xi = readlane_f64(own, i & 63);
-    const double* row = lr + static_cast<int64_t>(i) * sz;
-    for (int j = lane; j < i; j += 64) xs[j] -= row[j] * xi;
-  }
+  };
+  all(all, IntC<0>{});
 }
 
-// One wave per right-hand side, four per workgroup.  Waves [0, r): encoder column m,
-// E[:, m] = (A^T A + lam I)^-1 P[0:w, m] -> w_enc[m, :]; waves [r, r + w): decoder row j,
+// One wave per right-hand side, four per workgroup.  ENC: encoder column m,
+// E[:, m] = (A^T A + lam I)^-1 P[0:w, m] -> w_enc[m, :]; else decoder row j,
 // F[:, j] = (Z^T Z + lam I)^-1 P[w + j, :]^T -> w_dec[j, :].
+template <int NQ, bool ENC>
 __global__ __launch_bounds__(kSolveThreads) void fit_out_kernel(const SolveArgs a) {
-  __shared__ double xs_all[kSolveThreads / 64][kFitMaxSolveWidth];
-  const int layer = blockIdx.y, w = a.w, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int layer = blockIdx.y, w = a.w, lane = threadIdx.x & 63;
   const Slots s = slots(a.work, a.w, layer);
   const SolveJob jb = *s.job;
   const int r = static_cast<int>(jb.rank);
-  const bool bf16 = a.bf16 != 0;
-  const int t = blockIdx.x * (kSolveThreads / 64) + wave;
-  double* xs = xs_all[wave];
-  if (t < r) {
-    for (int i = lane; i < w; i += 64) xs[i] = s.m[static_cast<int64_t>(i) * r + t];
-    wave_chol_solve(s.x, s.x + static_cast<int64_t>(w) * w, s.ldiag, w, xs);
-    for (int i = lane; i < w; i += 64) store_out(jb.w_enc, static_cast<int64_t>(t) * w + i, xs[i], bf16);
-  } else if (t < r + w) {
-    const int j = t - r;
-    const double* b = s.m + static_cast<int64_t>(w + j) * r;
-    for (int l = lane; l < r; l += 64) xs[l] = b[l];
-    wave_chol_solve(s.y, s.y + static_cast<int64_t>(r) * r, s.ldiag + w, r, xs);
-    for (int l = lane; l < r; l += 64) store_out(jb.w_dec, static_cast<int64_t>(j) * r + l, xs[l], bf16);
+  const int t = blockIdx.x * (kSolveThreads / 64) + (threadIdx.x >> 6);
+  if (t >= (ENC ? r : w)) return;
+  const int sz = ENC ? w : r;
+  double x[NQ];
+#pragma unroll
+  for (int q = 0; q < NQ; ++q) {
+    const int i = lane + 64 * q;
+    x[q] = i < sz ? (ENC ? s.m[static_cast<int64_t>(i) * r + t] : s.m[static_cast<int64_t>(w + t) * r + i])
+                  : 0.0;
+  }
+  const double* l = ENC ? s.x : s.y;
+  wave_chol_solve<NQ>(l, l + static_cast<int64_t>(sz) * sz, s.ldiag + (ENC ? 0 : w), sz, x);
+#pragma unroll
+  for (int q = 0; q < NQ; ++q) {
+    const int i = lane + 64 * q;
+    if (i < sz) store_out(ENC ? jb.w_enc : jb.w_dec, static_cast<int64_t>(t) * sz + i, x[q], a.bf16 != 0);
   }
 }
 
@@ -1620,39 +1778,49 @@ hipError_t launch_fit_solve(const FitSolveParams& p, hipStream_t stream) {
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   const unsigned rt = static_cast<unsigned>((rmax + 63) / 64);
-  hipLaunchKernelGGL(fit_bisect_kernel, dim3((rmax + 3) / 4, layers), wave, 0, stream, a);
+  if (n <= 256) hipLaunchKernelGGL(fit_bisect_kernel<256>, dim3(rmax, layers), wave, 0, stream, a);
+  else hipLaunchKernelGGL(fit_bisect_kernel<kMaxN>, dim3(rmax, layers), wave, 0, stream, a);
   if (n <= kInverseLdsN)
     hipLaunchKernelGGL((fit_inverse_lds_kernel<kInverseLdsN, kInverseLdsThreads>),
                        dim3((rmax + kInverseLdsThreads - 1) / kInverseLdsThreads, layers), wave, 0,
                        stream, a);
   else
     hipLaunchKernelGGL((fit_inverse_lds_kernel<kMaxN, 1>), dim3(rmax, layers), wave, 0, stream, a);
-  if (n <= 512)
-    hipLaunchKernelGGL(fit_back_kernel<kBackColsNarrow>,
-                       dim3((rmax + kBackColsNarrow - 1) / kBackColsNarrow, layers), block, 0,
-                       stream, a);
-  else
-    hipLaunchKernelGGL(fit_back_kernel<kBackColsWide>,
-                       dim3((rmax + kBackColsWide - 1) / kBackColsWide, layers), block, 0, stream,
-                       a);
+  const dim3 back(rmax, layers);
+#define SCD_FIT_BACK(NQ)                                                                         \
+  do {                                                                                           \
+    if (n == 64 * NQ)                                                                            \
+      hipLaunchKernelGGL((fit_back_kernel<NQ, false>), back, wave, 0, stream, a);                \
+    else                                                                                         \
+      hipLaunchKernelGGL((fit_back_kernel<NQ, true>), back, wave, 0, stream, a);                 \
+  } while (0)
+  if (n <= 256) SCD_FIT_BACK(4);
+  else if (n <= 512) SCD_FIT_BACK(8);
+  else if (n <= 1024) SCD_FIT_BACK(16);
+  else SCD_FIT_BACK(32);
+#undef SCD_FIT_BACK
   hipLaunchKernelGGL(fit_project_kernel, dim3(n / 64, rt, layers), block, 0, stream, a);
   const unsigned tw = static_cast<unsigned>(p.w / 64);
   hipLaunchKernelGGL(fit_normal_kernel, dim3(rt * rt > tw * tw ? rt * rt : tw * tw, 2, layers),
                      block, 0, stream, a);
-  const int sz = p.w > rmax ? p.w : rmax;
-  if (sz <= kCholLdsN) {
-    hipLaunchKernelGGL(fit_chol_lds_kernel, dim3(2, layers), dim3(kCholThreads), 0, stream, a);
-  } else {
-    for (int k = 0; k < sz; ++k) {
-      a.step = k;
-      const int rows = sz - k - 1;
-      const int gx = rows > 0 ? (rows + kSolveRowsWide - 1) / kSolveRowsWide : 1;
-      hipLaunchKernelGGL(fit_chol_kernel, dim3(gx, 2, layers), block, 0, stream, a);
-    }
+  for (int k = 0; k * kPanel < p.w; ++k) {  // every rank is at most w
+    a.step = k;
+    const unsigned blocks = static_cast<unsigned>((p.w - k * kPanel + kPanel - 1) / kPanel);
+    hipLaunchKernelGGL(fit_chol_panel_kernel, dim3(blocks, 2, layers), block, 0, stream, a);
+    if (blocks > 1)
+      hipLaunchKernelGGL(fit_chol_update_kernel, dim3((blocks - 1) * blocks / 2, 2, layers), block, 0,
+                         stream, a);
   }
   constexpr int kWaves = kSolveThreads / 64;
-  hipLaunchKernelGGL(fit_out_kernel, dim3((rmax + p.w + kWaves - 1) / kWaves, layers), block, 0,
-                     stream, a);
+  const dim3 enc((rmax + kWaves - 1) / kWaves, layers), dec((p.w + kWaves - 1) / kWaves, layers);
+#define SCD_FIT_OUT(SZ, GRID, ENC)                                                             \
+  if (SZ <= 128) hipLaunchKernelGGL((fit_out_kernel<2, ENC>), GRID, block, 0, stream, a);      \
+  else if (SZ <= 256) hipLaunchKernelGGL((fit_out_kernel<4, ENC>), GRID, block, 0, stream, a); \
+  else if (SZ <= 512) hipLaunchKernelGGL((fit_out_kernel<8, ENC>), GRID, block, 0, stream, a); \
+  else hipLaunchKernelGGL((fit_out_kernel<16, ENC>), GRID, block, 0, stream, a)
+  SCD_FIT_OUT(p.w, enc, true);
+  SCD_FIT_OUT(rmax, dec, false);
+#undef SCD_FIT_OUT
   return hipGetLastError();
 }
 
