@@ -629,9 +629,9 @@ __global__ __launch_bounds__(256) void fit_gram_reduce_kernel(const FitGramParam
 // ---------------------------------------------------------------------------------------------
 constexpr int kSolveThreads = 256;
 constexpr int kSolveRows = 16;  // rows per workgroup of the prep and of a tridiagonal step, n <= 512
-// Rows per workgroup of a tridiagonal step for n > 512 and of a per-column Cholesky step: the
-// trailing block is then large and one layer's 16-row workgroups would leave most CUs idle, each
-// workgroup bound by its CU's share of the memory bandwidth.
+// Rows per workgroup of a tridiagonal step for n > 512: the trailing block is then large and one
+// layer's 16-row workgroups would leave most CUs idle, each workgroup bound by its CU's share of the
+// memory bandwidth.
 constexpr int kSolveRowsWide = 4;
 constexpr int kMaxN = 2 * kFitMaxSolveWidth;
 constexpr int kInverseSolves = 3;
@@ -1000,12 +1000,19 @@ __global__ __launch_bounds__(kTailThreads, 2) void fit_tridiag_tail_kernel(const
       double beta = alpha, scale = 0.0;
       tau = 0.0;
       if (!(sigma == 0.0)) {
-        // tau = (beta - alpha) / beta and scale = 1 / (alpha - beta) from one division
+        // tau = (beta - alpha) / beta and scale = 1 / (alpha - beta), from one division unless their
+        // common denominator comes near the smallest normal number (a column of about 1e-145)
         const double norm = sqrt(alpha * alpha + sigma);
         beta = alpha >= 0.0 ? -norm : norm;
-        const double diff = alpha - beta, inv = 1.0 / (beta * diff);
-        tau = -diff * diff * inv;
-        scale = beta * inv;
+        const double diff = alpha - beta, den = beta * diff;
+        if (fabs(den) < 1e-290) {
+          tau = -diff / beta;
+          scale = 1.0 / diff;
+        } else {
+          const double inv = 1.0 / den;
+          tau = -diff * diff * inv;
+          scale = beta * inv;
+        }
       }
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
