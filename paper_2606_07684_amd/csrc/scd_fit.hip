@@ -628,11 +628,12 @@ __global__ __launch_bounds__(256) void fit_gram_reduce_kernel(const FitGramParam
 //             outputs, rounded once.
 // ---------------------------------------------------------------------------------------------
 constexpr int kSolveThreads = 256;
-constexpr int kSolveRows = 16;  // rows per workgroup of the prep and of a tridiagonal step, n <= 512
-// Rows per workgroup of a tridiagonal step for n > 512: the trailing block is then large and one
-// layer's 16-row workgroups would leave most CUs idle, each workgroup bound by its CU's share of the
-// memory bandwidth.
-constexpr int kSolveRowsWide = 4;
+constexpr int kSolveRows = 16;  // rows per workgroup of the prep
+// Rows per workgroup of a tridiagonal step: 4 while the launch has at most this many rows over its
+// layers (three workgroups per CU), so that they spread over the chip; 8 above, where the vector part
+// that every workgroup repeats costs more.  Fit, ms, 4 / 8 rows: 1 layer at w = 1024 21.8 / 22.6, 2
+// layers at w = 1024 29.7 / 28.3, 4 layers at w = 512 11.2 / 10.9, 16 layers at w = 256 6.1 / 5.9.
+constexpr int64_t kTridiagNarrow = 3072;
 constexpr int kMaxN = 2 * kFitMaxSolveWidth;
 constexpr int kInverseSolves = 3;
 constexpr double kEps = 2.220446049250313e-16;  // 2^-52
@@ -698,10 +699,39 @@ __device__ inline double centred(const float* gram, const float* cs, int n, int 
   return g - static_cast<double>(cs[i]) * static_cast<double>(cs[j]) * inv;
 }
 
-__device__ inline double wave_sum(double v) {
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+// Wave-wide fp64 sum without LDS: four DPP steps inside rows of 16 lanes, then the rows (halves)
+// swapped against themselves.
+template <int CTRL>
+__device__ inline double dpp_f64(double v) {
+  const int64_t b = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_update_dpp(0, static_cast<int>(b), CTRL, 0xF, 0xF, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, static_cast<int>(b >> 32), CTRL, 0xF, 0xF, true);
+  return __longlong_as_double((static_cast<int64_t>(hi) << 32) | static_cast<uint32_t>(lo));
+}
+__device__ inline double row16_sum(double v) {
+  v += dpp_f64<0xB1>(v);   // quad_perm [1,0,3,2]
+  v += dpp_f64<0x4E>(v);   // quad_perm [2,3,0,1]
+  v += dpp_f64<0x141>(v);  // row_half_mirror
+  v += dpp_f64<0x140>(v);  // row_mirror
   return v;
 }
+// Sum over the four rows of 16 lanes (every lane keeps its column of the row).
+__device__ inline double rows4_sum(double v) {
+  const int64_t b = __double_as_longlong(v);
+  const uint32_t lo = static_cast<uint32_t>(b), hi = static_cast<uint32_t>(b >> 32);
+  auto join = [](uint32_t l, uint32_t h) {
+    return __longlong_as_double((static_cast<int64_t>(h) << 32) | l);
+  };
+  const auto l16 = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+  const auto h16 = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+  v = join(l16[0], h16[0]) + join(l16[1], h16[1]);
+  const int64_t c = __double_as_longlong(v);
+  const uint32_t lo2 = static_cast<uint32_t>(c), hi2 = static_cast<uint32_t>(c >> 32);
+  const auto l32 = __builtin_amdgcn_permlane32_swap(lo2, lo2, false, false);
+  const auto h32 = __builtin_amdgcn_permlane32_swap(hi2, hi2, false, false);
+  return join(l32[0], h32[0]) + join(l32[1], h32[1]);
+}
+__device__ inline double wave_sum_dpp(double v) { return rows4_sum(row16_sum(v)); }
 
 __device__ inline void store_out(void* dst, int64_t i, double v, bool bf16) {
   if (bf16) static_cast<__bf16*>(dst)[i] = static_cast<__bf16>(static_cast<float>(v));
@@ -745,74 +775,103 @@ __global__ __launch_bounds__(kSolveThreads) void fit_prep_kernel(const FitSolveP
 // Source A^(k): G_c (Z) for k <= 0, else the previous launch's destination; destination: X for even
 // k, Y for odd k.  Reflector k+1 goes into row k+1 of the destination, a row no later launch
 // writes; p alternates between two vectors.
-// Every global load of a launch is issued at its start (the reflector and p of the previous launch,
-// row k+1 and, for n <= 64 PRE, this workgroup's rows of the source), so the launch waits on one
-// round of loads rather than three.
+// Every global load of a launch is issued at its start (the reflector, p and tau of the previous
+// launch, row k+1 and this workgroup's rows of the source, in registers), so the launch waits on one
+// round of loads and the rows arrive while the vector part's two barriers pass.  PRE: row entries per
+// lane, n - k - 2 <= 64 PRE.  Every workgroup repeats the vector part (each thread keeps its own entries
+// in registers).  Bound by launch latency and by streaming the block twice: with
+// the rows loaded after the vector part, four barriers and shuffled sums, each of the 1791 steps at
+// w = 1024 took about 10 us more (fit of two layers 46.3 ms, now 28.3).
 template <int PRE, int ROWS>
-__device__ __forceinline__ void tridiag_step(const SolveArgs& a) {
-  __shared__ double vk[kMaxN], wk[kMaxN], vn[kMaxN];
+__global__ __launch_bounds__(kSolveThreads, 2) void fit_tridiag_kernel(const SolveArgs a) {
+  constexpr int kVec = 64 * PRE + 1;  // entries k + 1 .. n - 1
+  __shared__ double vk[kVec], wk[kVec], vn[kVec];
   __shared__ double red[2][kSolveThreads / 64];
   const int layer = blockIdx.y, n = 2 * a.w, k = a.step, tid = threadIdx.x;
-  const int lane = tid & 63, wave = tid >> 6;
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   constexpr int kWaves = kSolveThreads / 64, kRowsPerWave = ROWS / kWaves;
+  constexpr int kOwn = (kVec + kSolveThreads - 1) / kSolveThreads;  // vector entries per thread
   static_assert(ROWS % kWaves == 0, "whole rows per wave");
   const Slots s = slots(a.work, a.w, layer);
   const double* src = k <= 0 ? s.z : ((k - 1) & 1 ? s.y : s.x);
   double* dst = (k & 1) ? s.y : s.x;  // k = -1 is odd: Y (only its reflector row is written)
   double* p_next = ((k + 1) & 1) ? s.p1 : s.p0;
-  const int r0 = k + 2 + blockIdx.x * ROWS;
-  // loads: reflector k and p_k into vk / wk, row k+1 of the source into vn, own rows to registers
+  // index x of the LDS vectors and of the block is row or column o + x
+  const int o = k + 1, m = n - o;
+  const int r0 = 1 + blockIdx.x * ROWS;
+  // loads: reflector k, p_k and row k+1 of the source (own entries), own rows
+  double vo[kOwn], wo[kOwn], co[kOwn], tau_k = 0.0;
+#pragma unroll
+  for (int u = 0; u < kOwn; ++u) vo[u] = wo[u] = 0.0;
   if (k >= 0) {
-    const double* vrow = reflector_rows(s, k) + static_cast<int64_t>(k) * n;
-    const double* p_cur = (k & 1) ? s.p1 : s.p0;
-    for (int i = k + 1 + tid; i < n; i += kSolveThreads) {
-      vk[i] = vrow[i];
-      wk[i] = p_cur[i];
-    }
-  } else {
-    for (int i = tid; i < n; i += kSolveThreads) vk[i] = wk[i] = 0.0;
-  }
-  const double* row1 = src + static_cast<int64_t>(k + 1) * n;
-  for (int i = k + 1 + tid; i < n; i += kSolveThreads) vn[i] = row1[i];
-  double pre[PRE > 0 ? kRowsPerWave : 1][PRE > 0 ? PRE : 1];
-  if constexpr (PRE > 0) {
-    for (int q = 0; q < kRowsPerWave; ++q) {
-      const int i = r0 + wave + kWaves * q;
-      for (int u = 0; u < PRE; ++u) {
-        const int j = k + 2 + lane + 64 * u;
-        pre[q][u] = (i < n && j < n) ? src[static_cast<int64_t>(i) * n + j] : 0.0;
+    const double* vrow = reflector_rows(s, k) + static_cast<int64_t>(k) * n + o;
+    const double* p_cur = ((k & 1) ? s.p1 : s.p0) + o;
+    tau_k = s.tau[k];
+#pragma unroll
+    for (int u = 0; u < kOwn; ++u) {
+      const int i = tid + kSolveThreads * u;
+      if (i < m) {
+        vo[u] = vrow[i];
+        wo[u] = p_cur[i];
       }
     }
   }
-  __syncthreads();
-  // w_k = p_k - (tau_k / 2)(p_k . v_k) v_k (zero for launch -1)
-  double kk = 0.0;
-  if (k >= 0) {
-    double dot = 0.0;
-    for (int i = k + 1 + tid; i < n; i += kSolveThreads) dot += wk[i] * vk[i];
-    dot = wave_sum(dot);
-    if (lane == 0) red[0][wave] = dot;
-    __syncthreads();
-    double t = 0.0;
-    for (int q = 0; q < kWaves; ++q) t += red[0][q];
-    kk = 0.5 * s.tau[k] * t;
+  const double* row1 = src + static_cast<int64_t>(o) * n + o;
+#pragma unroll
+  for (int u = 0; u < kOwn; ++u) {
+    const int i = tid + kSolveThreads * u;
+    co[u] = i < m ? row1[i] : 0.0;
   }
-  const double vk1 = vk[k + 1], wk1 = wk[k + 1] - kk * vk1;
+  double pre[kRowsPerWave][PRE];
+#pragma unroll
+  for (int q = 0; q < kRowsPerWave; ++q) {
+    const int i = r0 + wave + kWaves * q;
+    const double* arow = src + static_cast<int64_t>(o + (i < m ? i : 0)) * n + o;
+#pragma unroll
+    for (int u = 0; u < PRE; ++u) {
+      const int j = 1 + lane + 64 * u;
+      pre[q][u] = arow[j < m ? j : m - 1];
+    }
+  }
+  // w_k = p_k - (tau_k / 2)(p_k . v_k) v_k (zero for launch -1)
+  double dot = 0.0;
+#pragma unroll
+  for (int u = 0; u < kOwn; ++u) dot += wo[u] * vo[u];
+  dot = wave_sum_dpp(dot);
+  if (lane == 0) red[0][wave] = dot;
+  if (tid == 0) {
+    vk[0] = vo[0];
+    wk[0] = wo[0];
+  }
+  lds_barrier();
+  double t = 0.0;
+#pragma unroll
+  for (int q = 0; q < kWaves; ++q) t += red[0][q];
+  const double kk = 0.5 * tau_k * t;
+  const double vk1 = vk[0], wk1 = wk[0] - kk * vk1;
   // column k+1 of A^(k+1) (row k+1, the matrix being symmetric) and w_k, own entries only
   double sig = 0.0;
-  for (int i = k + 1 + tid; i < n; i += kSolveThreads) {
-    const double wi = wk[i] - kk * vk[i];
-    if (i > k + 1) wk[i] = wi;  // entry k+1 stays p_k's: every thread reads it above
-    const double c = vn[i] - vk1 * wi - wk1 * vk[i];
-    vn[i] = c;
-    if (i >= k + 3) sig += c * c;
+#pragma unroll
+  for (int u = 0; u < kOwn; ++u) {
+    const int i = tid + kSolveThreads * u;
+    const double wi = wo[u] - kk * vo[u];
+    co[u] = co[u] - vk1 * wi - wk1 * vo[u];
+    if (i < m) {
+      vn[i] = co[u];
+      if (i > 0) {  // entry 0 stays p_k's: every thread reads it above
+        vk[i] = vo[u];
+        wk[i] = wi;
+      }
+      if (i >= 2) sig += co[u] * co[u];
+    }
   }
-  sig = wave_sum(sig);
+  sig = wave_sum_dpp(sig);
   if (lane == 0) red[1][wave] = sig;
-  __syncthreads();
+  lds_barrier();
   double sigma = 0.0;
+#pragma unroll
   for (int q = 0; q < kWaves; ++q) sigma += red[1][q];
-  const double d_next = vn[k + 1], alpha = vn[k + 2];
+  const double d_next = vn[0], alpha = vn[1];
   double tau = 0.0, beta = alpha, scale = 0.0;
   if (!(sigma == 0.0)) {
     const double norm = sqrt(alpha * alpha + sigma);
@@ -820,39 +879,45 @@ __device__ __forceinline__ void tridiag_step(const SolveArgs& a) {
     tau = (beta - alpha) / beta;
     scale = 1.0 / (alpha - beta);
   }
-  // v_{k+1}: entries past its first scaled in place; its first entry (1) is never stored in vn,
-  // so alpha stays readable
-  for (int i = k + 3 + tid; i < n; i += kSolveThreads) vn[i] *= scale;
-  __syncthreads();
-  // this workgroup's rows of A^(k+1) and of p_{k+1}
+  // this workgroup's rows of A^(k+1) and of p_{k+1}; v_{k+1} is the column scaled, its first entry 1
+  // (entries past the end: zero)
+  double acc[kRowsPerWave], vi[kRowsPerWave], wi[kRowsPerWave];
+#pragma unroll
   for (int q = 0; q < kRowsPerWave; ++q) {
     const int i = r0 + wave + kWaves * q;
-    if (i >= n || i >= r0 + ROWS) break;
-    const double* arow = src + static_cast<int64_t>(i) * n;
-    double* orow = dst + static_cast<int64_t>(i) * n;
-    const double vi = vk[i], wi = wk[i];
-    double acc = 0.0;
-    auto entry = [&](int j, double x) {
-      const double v = x - vi * wk[j] - wi * vk[j];
-      if (k >= 0) orow[j] = v;
-      if (k == n - 3) s.d[n - 1] = v;  // the last launch: i = j = n - 1
-      acc += v * (j == k + 2 ? 1.0 : vn[j]);
-    };
-    if constexpr (PRE > 0) {
+    acc[q] = 0.0;
+    vi[q] = vk[i < m ? i : 0];
+    wi[q] = wk[i < m ? i : 0];
+  }
 #pragma unroll
-      for (int u = 0; u < PRE; ++u) {
-        const int j = k + 2 + lane + 64 * u;
-        if (j < n) entry(j, pre[q][u]);
+  for (int u = 0; u < PRE; ++u) {
+    const int j = 1 + lane + 64 * u;
+    if (j < m) {
+      const double wj = wk[j], vj = vk[j], nj = j == 1 ? 1.0 : vn[j] * scale;
+#pragma unroll
+      for (int q = 0; q < kRowsPerWave; ++q) {
+        const int i = r0 + wave + kWaves * q;
+        const double v = pre[q][u] - vi[q] * wj - wi[q] * vj;
+        if (i < m) {
+          if (k >= 0) dst[static_cast<int64_t>(o + i) * n + o + j] = v;
+          acc[q] += v * nj;
+        }
       }
-    } else {
-      for (int j = k + 2 + lane; j < n; j += 64) entry(j, arow[j]);
     }
-    acc = wave_sum(acc);
-    if (lane == 0) p_next[i] = tau * acc;
+  }
+#pragma unroll
+  for (int q = 0; q < kRowsPerWave; ++q) {
+    const int i = r0 + wave + kWaves * q;
+    const double y = wave_sum_dpp(acc[q]);
+    if (lane == 0 && i < m) p_next[o + i] = tau * y;
   }
   if (blockIdx.x == 0) {
-    double* vrow = dst + static_cast<int64_t>(k + 1) * n;
-    for (int i = k + 2 + tid; i < n; i += kSolveThreads) vrow[i] = i == k + 2 ? 1.0 : vn[i];
+    double* vrow = dst + static_cast<int64_t>(o) * n + o;
+#pragma unroll
+    for (int u = 0; u < kOwn; ++u) {
+      const int i = tid + kSolveThreads * u;
+      if (i >= 1 && i < m) vrow[i] = i == 1 ? 1.0 : co[u] * scale;
+    }
     if (tid == 0) {
       s.d[k + 1] = d_next;
       s.e[k + 1] = beta;
@@ -860,48 +925,6 @@ __device__ __forceinline__ void tridiag_step(const SolveArgs& a) {
     }
   }
 }
-
-constexpr int kTridiagPre = 8;  // row entries per lane held in registers: n <= 512
-__global__ __launch_bounds__(kSolveThreads) void fit_tridiag_pre_kernel(const SolveArgs a) {
-  tridiag_step<kTridiagPre, kSolveRows>(a);
-}
-__global__ __launch_bounds__(kSolveThreads) void fit_tridiag_kernel(const SolveArgs a) {
-  tridiag_step<0, kSolveRowsWide>(a);
-}
-
-// Wave-wide fp64 sum without LDS: four DPP steps inside rows of 16 lanes, then the rows (halves)
-// swapped against themselves.
-template <int CTRL>
-__device__ inline double dpp_f64(double v) {
-  const int64_t b = __double_as_longlong(v);
-  const int lo = __builtin_amdgcn_update_dpp(0, static_cast<int>(b), CTRL, 0xF, 0xF, true);
-  const int hi = __builtin_amdgcn_update_dpp(0, static_cast<int>(b >> 32), CTRL, 0xF, 0xF, true);
-  return __longlong_as_double((static_cast<int64_t>(hi) << 32) | static_cast<uint32_t>(lo));
-}
-__device__ inline double row16_sum(double v) {
-  v += dpp_f64<0xB1>(v);   // quad_perm [1,0,3,2]
-  v += dpp_f64<0x4E>(v);   // quad_perm [2,3,0,1]
-  v += dpp_f64<0x141>(v);  // row_half_mirror
-  v += dpp_f64<0x140>(v);  // row_mirror
-  return v;
-}
-// Sum over the four rows of 16 lanes (every lane keeps its column of the row).
-__device__ inline double rows4_sum(double v) {
-  const int64_t b = __double_as_longlong(v);
-  const uint32_t lo = static_cast<uint32_t>(b), hi = static_cast<uint32_t>(b >> 32);
-  auto join = [](uint32_t l, uint32_t h) {
-    return __longlong_as_double((static_cast<int64_t>(h) << 32) | l);
-  };
-  const auto l16 = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
-  const auto h16 = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
-  v = join(l16[0], h16[0]) + join(l16[1], h16[1]);
-  const int64_t c = __double_as_longlong(v);
-  const uint32_t lo2 = static_cast<uint32_t>(c), hi2 = static_cast<uint32_t>(c >> 32);
-  const auto l32 = __builtin_amdgcn_permlane32_swap(lo2, lo2, false, false);
-  const auto h32 = __builtin_amdgcn_permlane32_swap(hi2, hi2, false, false);
-  return join(l32[0], h32[0]) + join(l32[1], h32[1]);
-}
-__device__ inline double wave_sum_dpp(double v) { return rows4_sum(row16_sum(v)); }
 
 __device__ inline double readlane_f64(double v, int lane) {
   const int64_t b = __double_as_longlong(v);
@@ -1775,10 +1798,18 @@ hipError_t launch_fit_solve(const FitSolveParams& p, hipStream_t stream) {
   for (int k = -1; k < k0; ++k) {
     a.step = k;
     const int rows = n - k - 2;
-    const int rpw = n <= 64 * kTridiagPre ? kSolveRows : kSolveRowsWide;
+    const int rpw = static_cast<int64_t>(rows) * layers > kTridiagNarrow ? 8 : 4;
     const dim3 grid((rows + rpw - 1) / rpw, layers);
-    if (n <= 64 * kTridiagPre) hipLaunchKernelGGL(fit_tridiag_pre_kernel, grid, block, 0, stream, a);
-    else hipLaunchKernelGGL(fit_tridiag_kernel, grid, block, 0, stream, a);
+#define SCD_FIT_TRIDIAG(PRE)                                                                        \
+  do {                                                                                              \
+    if (rpw == 8) hipLaunchKernelGGL((fit_tridiag_kernel<PRE, 8>), grid, block, 0, stream, a);      \
+    else hipLaunchKernelGGL((fit_tridiag_kernel<PRE, 4>), grid, block, 0, stream, a);               \
+  } while (0)
+    if (rows <= 512) SCD_FIT_TRIDIAG(8);
+    else if (rows <= 1024) SCD_FIT_TRIDIAG(16);
+    else if (rows <= 1536) SCD_FIT_TRIDIAG(24);
+    else SCD_FIT_TRIDIAG(32);
+#undef SCD_FIT_TRIDIAG
   }
   a.step = k0;
   hipLaunchKernelGGL(fit_tridiag_tail_kernel, dim3(layers), dim3(kTailThreads), 0, stream, a);

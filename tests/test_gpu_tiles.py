@@ -7,6 +7,7 @@ import torch
 import paper_2606_07684_amd as scd
 from synth import workloads as W
 from tests import parity_util as U
+from tests import test_gpu_fit as F
 
 pytestmark = pytest.mark.gpu
 BF16_TOL = U.TOL["bf16"]
@@ -119,3 +120,25 @@ def test_encode_shapes(heads, head_dim, shared, tokens, layers, ranks, mu):
     rope = scd.scd_rope_table(U.model_of(wl), wl.max_position)
     out = U.run_gpu(wl, inp, rope, which=("encode",))
     U.assert_within(U.compare_all(wl, inp, out), BF16_TOL, wl.name)
+
+
+# The fit's tridiagonal steps: row registers of 8, 16, 24 and 32 per lane (trailing blocks of up to 512,
+# 1024, 1536 and 2047 rows, each entered and left inside one fit), 4 rows per workgroup and, above 3072
+# rows over the layers, 8; widths whose last workgroup and last lane registers are partly filled.
+@pytest.mark.parametrize("heads,head_dim,tokens,layers", [
+    (3, 64, (400, 61), 1), (9, 64, (1201,), 1), (13, 64, (1701,), 2), (9, 64, (1201,), 3)])
+def test_fit_tridiagonal_shapes(heads, head_dim, tokens, layers):
+    wl = W.Workload(f"fit_{heads}_{layers}", layers, 256, heads, head_dim, tokens, (32,) * layers, (),
+                    5e5, "bf16", ranks_v=(32,) * layers)
+    dev = torch.device("cuda")
+    R, a_in, b_in, rope = F._setup(wl, "v", dev)
+    lam = F._lam(wl)
+    w_enc, w_dec, mu_enc, mu_dec, _, _ = scd.fit_reuse(U.model_of(wl), U.batch_of(wl, dev), rope,
+                                                       scd.FIT_VALUES, a_in, b_in, lam, center=True)
+    errs = {}
+    for l in R:
+        want = F._oracle_fit(wl, "v", a_in, b_in, l, lam)
+        for name, got, ref in zip(("w_enc", "w_dec", "mu_enc", "mu_dec"),
+                                  (w_enc[l], w_dec[l], mu_enc[l], mu_dec[l]), want):
+            errs[(name, l)] = U.max_abs_rel(U.f64(got), ref)
+    U.assert_within(errs, BF16_TOL, wl.name)
