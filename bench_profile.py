@@ -28,7 +28,7 @@ import bench
 ROOT = os.path.dirname(os.path.abspath(__file__))
 # kernel-name fragment -> step (first match wins: the aligner's hidden layer inside the Patch step
 # before the unfolded aligner timed beside it)
-PHASES = {"encode_bf16_kernel": "encode", "reuse_decode": "reuse_decode",
+PHASES = {"encode_bf16_kernel": "encode", "encode_kv_bf16": "encode", "reuse_decode": "reuse_decode",
           "patch_kv": "patch", "patch_align_act": "patch", "patch_align": "aligner",
           "patch_fold": "fold", "EncodeKV": "encode", "EncodeH": "encode",
           "ReuseDecode": "reuse_decode", "PatchKV": "patch", "PatchAlign": "patch",
