@@ -612,7 +612,7 @@ __global__ __launch_bounds__(256) void fit_gram_reduce_kernel(const FitGramParam
 //             for column k + 1 applies reflector k to the trailing block, forms reflector k + 1
 //             from the updated column and the product p = tau A v that the next launch needs.  Two
 //             matrix copies take turns as source and destination, so no workgroup reads what
-//             another workgroup of the same launch writes.  The last steps (a trailing block of at
+//             another workgroup of the same launch writes; only every second launch writes.  The last steps (a trailing block of at
 //             most 256 rows) run in one launch with the block in registers;
 //   bisect    the r largest eigenvalues of T by multisection on Sturm counts, one wave each;
 //   inverse   their eigenvectors of T by inverse iteration (three solves with T - lambda I, factored
@@ -629,10 +629,12 @@ __global__ __launch_bounds__(256) void fit_gram_reduce_kernel(const FitGramParam
 // ---------------------------------------------------------------------------------------------
 constexpr int kSolveThreads = 256;
 constexpr int kSolveRows = 16;  // rows per workgroup of the prep
-// Rows per workgroup of a tridiagonal step: 4 while the launch has at most this many rows over its
-// layers (three workgroups per CU), so that they spread over the chip; 8 above, where the vector part
-// that every workgroup repeats costs more.  Fit, ms, 4 / 8 rows: 1 layer at w = 1024 21.8 / 22.6, 2
-// layers at w = 1024 29.7 / 28.3, 4 layers at w = 512 11.2 / 10.9, 16 layers at w = 256 6.1 / 5.9.
+// Rows per workgroup of 4 waves of a tridiagonal step: 4 while the launch has at most this many rows
+// over its layers (three workgroups per CU), so that they spread over the chip; 8 above, where the vector
+// part that every workgroup repeats costs more.  Above 1024 rows workgroups have 8 waves and twice the
+// rows: the LDS holds one with a pair's five vectors.  Fit, ms, 4 / 8 rows: 1 layer at w = 1024 21.8 / 22.6, 2
+// layers at w = 1024 29.7 / 28.3, 4 layers at w = 512 11.2 / 10.9, 16 layers at w = 256 6.1 / 5.9 (all
+// with 4 waves and a write per launch).
 constexpr int64_t kTridiagNarrow = 3072;
 constexpr int kMaxN = 2 * kFitMaxSolveWidth;
 constexpr int kInverseSolves = 3;
@@ -738,8 +740,12 @@ __device__ inline void store_out(void* dst, int64_t i, double v, bool bf16) {
   else static_cast<float*>(dst)[i] = static_cast<float>(v);
 }
 
-// Reflector j lives in row j of X (j odd) or Y (j even), entries j+1 .. n-1 (the first one 1).
-__device__ inline double* reflector_rows(const Slots& s, int j) { return (j & 1) ? s.x : s.y; }
+// Where launch k of the tridiagonal steps writes (the matrix and reflector k+1): the two launches of a
+// pair share a destination, pairs alternate between X and Y (launch -1: Y).
+__device__ inline double* step_dst(const Slots& s, int k) { return ((k >> 1) & 1) ? s.y : s.x; }
+
+// Reflector j lives in row j of the destination of launch j-1, entries j+1 .. n-1 (the first one 1).
+__device__ inline double* reflector_rows(const Slots& s, int j) { return step_dst(s, j - 1); }
 
 // ---- prep: G_c into Z, the offsets, the job table --------------------------------------------
 __global__ __launch_bounds__(kSolveThreads) void fit_prep_kernel(const FitSolveParams p) {
@@ -772,35 +778,41 @@ __global__ __launch_bounds__(kSolveThreads) void fit_prep_kernel(const FitSolveP
 //   beta = -sign(x_0) ||x||, tau = (beta - x_0) / beta, v = x / (x_0 - beta) with v_0 = 1, so that
 //   (I - tau v v^T) x = beta e_0 (e_{k+1} = beta; x with nothing below x_0 takes tau = 0);
 //   p_{k+1} = tau_{k+1} A^(k+1) v_{k+1} on rows [k+2, n), this workgroup's rows only.
-// Source A^(k): G_c (Z) for k <= 0, else the previous launch's destination; destination: X for even
-// k, Y for odd k.  Reflector k+1 goes into row k+1 of the destination, a row no later launch
-// writes; p alternates between two vectors.
+// Launches run in pairs (k even, k + 1), and only the second writes the matrix: the first (which leaves
+// its w in lam for the second) takes its updated rows no further than the registers, the second reads the
+// same source and applies both reflectors, in the same order.  Above 1024 rows a step is bound by
+// streaming the block, and a write less per pair took the fit of two layers at w = 1024 from 28.4 to 26.9
+// ms, of one from 22.0 to 20.5.  Source: G_c (Z) for k <= 1, else the previous pair's destination
+// (step_dst).  The last launch writes whatever its place, for the tail.  Reflector k+1 goes into row
+// k+1 of the destination, a row no later launch writes; p alternates between two vectors.
 // Every global load of a launch is issued at its start (the reflector, p and tau of the previous
 // launch, row k+1 and this workgroup's rows of the source, in registers), so the launch waits on one
 // round of loads and the rows arrive while the vector part's two barriers pass.  PRE: row entries per
-// lane, n - k - 2 <= 64 PRE.  Every workgroup repeats the vector part (each thread keeps its own entries
+// lane, n - k - 2 <= 64 PRE.  PAIR: the second of a pair.  write: store the matrix.  Every workgroup repeats the vector part (each thread keeps its own entries
 // in registers).  Bound by launch latency and by streaming the block twice: with
 // the rows loaded after the vector part, four barriers and shuffled sums, each of the 1791 steps at
-// w = 1024 took about 10 us more (fit of two layers 46.3 ms, now 28.3).
-template <int PRE, int ROWS>
-__global__ __launch_bounds__(kSolveThreads, 2) void fit_tridiag_kernel(const SolveArgs a) {
+// w = 1024 took about 10 us more (fit of two layers 46.3 ms, then 28.3).
+template <int PRE, int ROWS, int THREADS, bool PAIR>
+__global__ __launch_bounds__(THREADS, 2) void fit_tridiag_kernel(const SolveArgs a, int write) {
   constexpr int kVec = 64 * PRE + 1;  // entries k + 1 .. n - 1
-  __shared__ double vk[kVec], wk[kVec], vn[kVec];
-  __shared__ double red[2][kSolveThreads / 64];
+  __shared__ double vk[kVec], wk[kVec], vn[kVec], vp[PAIR ? kVec : 1], wp[PAIR ? kVec : 1];
+  __shared__ double red[2][THREADS / 64];
   const int layer = blockIdx.y, n = 2 * a.w, k = a.step, tid = threadIdx.x;
   const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  constexpr int kWaves = kSolveThreads / 64, kRowsPerWave = ROWS / kWaves;
-  constexpr int kOwn = (kVec + kSolveThreads - 1) / kSolveThreads;  // vector entries per thread
+  constexpr int kWaves = THREADS / 64, kRowsPerWave = ROWS / kWaves;
+  constexpr int kOwn = (kVec + THREADS - 1) / THREADS;  // vector entries per thread
   static_assert(ROWS % kWaves == 0, "whole rows per wave");
   const Slots s = slots(a.work, a.w, layer);
-  const double* src = k <= 0 ? s.z : ((k - 1) & 1 ? s.y : s.x);
-  double* dst = (k & 1) ? s.y : s.x;  // k = -1 is odd: Y (only its reflector row is written)
+  const double* src = k <= 1 ? s.z : step_dst(s, (k & ~1) - 1);
+  double* dst = step_dst(s, k);
   double* p_next = ((k + 1) & 1) ? s.p1 : s.p0;
   // index x of the LDS vectors and of the block is row or column o + x
   const int o = k + 1, m = n - o;
   const int r0 = 1 + blockIdx.x * ROWS;
-  // loads: reflector k, p_k and row k+1 of the source (own entries), own rows
+  // loads: reflector k, p_k and row k+1 of the source (own entries), own rows; the pair's first launch's
+  // reflector and w
   double vo[kOwn], wo[kOwn], co[kOwn], tau_k = 0.0;
+  double vpo[PAIR ? kOwn : 1], wpo[PAIR ? kOwn : 1], vp0 = 0.0, wp0 = 0.0;
 #pragma unroll
   for (int u = 0; u < kOwn; ++u) vo[u] = wo[u] = 0.0;
   if (k >= 0) {
@@ -809,17 +821,29 @@ __global__ __launch_bounds__(kSolveThreads, 2) void fit_tridiag_kernel(const Sol
     tau_k = s.tau[k];
 #pragma unroll
     for (int u = 0; u < kOwn; ++u) {
-      const int i = tid + kSolveThreads * u;
+      const int i = tid + THREADS * u;
       if (i < m) {
         vo[u] = vrow[i];
         wo[u] = p_cur[i];
       }
     }
   }
+  if constexpr (PAIR) {
+    const double* vrow = reflector_rows(s, k - 1) + static_cast<int64_t>(k - 1) * n + o;
+    const double* w_prev = s.lam + o;
+    vp0 = vrow[0];
+    wp0 = w_prev[0];
+#pragma unroll
+    for (int u = 0; u < kOwn; ++u) {
+      const int i = tid + THREADS * u;
+      vpo[u] = i < m ? vrow[i] : 0.0;
+      wpo[u] = i < m ? w_prev[i] : 0.0;
+    }
+  }
   const double* row1 = src + static_cast<int64_t>(o) * n + o;
 #pragma unroll
   for (int u = 0; u < kOwn; ++u) {
-    const int i = tid + kSolveThreads * u;
+    const int i = tid + THREADS * u;
     co[u] = i < m ? row1[i] : 0.0;
   }
   double pre[kRowsPerWave][PRE];
@@ -853,10 +877,15 @@ __global__ __launch_bounds__(kSolveThreads, 2) void fit_tridiag_kernel(const Sol
   double sig = 0.0;
 #pragma unroll
   for (int u = 0; u < kOwn; ++u) {
-    const int i = tid + kSolveThreads * u;
+    const int i = tid + THREADS * u;
     const double wi = wo[u] - kk * vo[u];
+    if constexpr (PAIR) co[u] = co[u] - vp0 * wpo[u] - wp0 * vpo[u];
     co[u] = co[u] - vk1 * wi - wk1 * vo[u];
     if (i < m) {
+      if constexpr (PAIR) {
+        vp[i] = vpo[u];
+        wp[i] = wpo[u];
+      }
       vn[i] = co[u];
       if (i > 0) {  // entry 0 stays p_k's: every thread reads it above
         vk[i] = vo[u];
@@ -881,13 +910,15 @@ __global__ __launch_bounds__(kSolveThreads, 2) void fit_tridiag_kernel(const Sol
   }
   // this workgroup's rows of A^(k+1) and of p_{k+1}; v_{k+1} is the column scaled, its first entry 1
   // (entries past the end: zero)
-  double acc[kRowsPerWave], vi[kRowsPerWave], wi[kRowsPerWave];
+  double acc[kRowsPerWave], vi[kRowsPerWave], wi[kRowsPerWave], vpi[kRowsPerWave], wpi[kRowsPerWave];
 #pragma unroll
   for (int q = 0; q < kRowsPerWave; ++q) {
     const int i = r0 + wave + kWaves * q;
     acc[q] = 0.0;
     vi[q] = vk[i < m ? i : 0];
     wi[q] = wk[i < m ? i : 0];
+    vpi[q] = PAIR ? vp[i < m ? i : 0] : 0.0;
+    wpi[q] = PAIR ? wp[i < m ? i : 0] : 0.0;
   }
 #pragma unroll
   for (int u = 0; u < PRE; ++u) {
@@ -897,9 +928,11 @@ __global__ __launch_bounds__(kSolveThreads, 2) void fit_tridiag_kernel(const Sol
 #pragma unroll
       for (int q = 0; q < kRowsPerWave; ++q) {
         const int i = r0 + wave + kWaves * q;
-        const double v = pre[q][u] - vi[q] * wj - wi[q] * vj;
+        double v = pre[q][u];
+        if constexpr (PAIR) v = v - vpi[q] * wp[j] - wpi[q] * vp[j];
+        v = v - vi[q] * wj - wi[q] * vj;
         if (i < m) {
-          if (k >= 0) dst[static_cast<int64_t>(o + i) * n + o + j] = v;
+          if (write) dst[static_cast<int64_t>(o + i) * n + o + j] = v;
           acc[q] += v * nj;
         }
       }
@@ -915,8 +948,11 @@ __global__ __launch_bounds__(kSolveThreads, 2) void fit_tridiag_kernel(const Sol
     double* vrow = dst + static_cast<int64_t>(o) * n + o;
 #pragma unroll
     for (int u = 0; u < kOwn; ++u) {
-      const int i = tid + kSolveThreads * u;
-      if (i >= 1 && i < m) vrow[i] = i == 1 ? 1.0 : co[u] * scale;
+      const int i = tid + THREADS * u;
+      if (i >= 1 && i < m) {
+        vrow[i] = i == 1 ? 1.0 : co[u] * scale;
+        if (!PAIR) s.lam[o + i] = wo[u] - kk * vo[u];
+      }
     }
     if (tid == 0) {
       s.d[k + 1] = d_next;
@@ -961,7 +997,7 @@ __global__ __launch_bounds__(kTailThreads, 2) void fit_tridiag_tail_kernel(const
   const Slots s = slots(a.work, a.w, layer);
   const int o = k0 + 1;  // global index of local row / column 0
   const int m0 = n - o;  // rows of the block (<= kTailN)
-  const double* src = k0 <= 0 ? s.z : ((k0 - 1) & 1 ? s.y : s.x);
+  const double* src = k0 <= 0 ? s.z : step_dst(s, k0 - 1);
   double am[kRB][kCB];  // blocks b <= 2 row + 1
 #pragma unroll
   for (int r = 0; r < kRB; ++r)
@@ -1055,7 +1091,7 @@ __global__ __launch_bounds__(kTailThreads, 2) void fit_tridiag_tail_kernel(const
     lds_barrier();
     // reflector k + 1 where the per-column launches keep it
     if (tid < kTailN && tid > c && tid < m0)
-      (((k + 1) & 1) ? s.x : s.y)[static_cast<int64_t>(k + 1) * n + o + tid] = ns[tid];
+      reflector_rows(s, k + 1)[static_cast<int64_t>(k + 1) * n + o + tid] = ns[tid];
     // A^(k+1) on [c + 1, m0)^2 and the sums of A^(k+1) v_{k+1}; column c + 1 for the next step
     double vi[kRB], wi[kRB], ni[kRB], rs[kRB];
 #pragma unroll
@@ -1798,18 +1834,31 @@ hipError_t launch_fit_solve(const FitSolveParams& p, hipStream_t stream) {
   for (int k = -1; k < k0; ++k) {
     a.step = k;
     const int rows = n - k - 2;
-    const int rpw = static_cast<int64_t>(rows) * layers > kTridiagNarrow ? 8 : 4;
-    const dim3 grid((rows + rpw - 1) / rpw, layers);
-#define SCD_FIT_TRIDIAG(PRE)                                                                        \
-  do {                                                                                              \
-    if (rpw == 8) hipLaunchKernelGGL((fit_tridiag_kernel<PRE, 8>), grid, block, 0, stream, a);      \
-    else hipLaunchKernelGGL((fit_tridiag_kernel<PRE, 4>), grid, block, 0, stream, a);               \
+    const bool pair = k >= 0 && (k & 1) != 0;  // k0 is odd: the last launch is a pair's first
+    const int write = pair || k == k0 - 1 ? 1 : 0;
+    const int scale = rows > 1024 ? 2 : 1;
+    const int rpw = (static_cast<int64_t>(rows) * layers > kTridiagNarrow ? 8 : 4) * scale;
+    const dim3 grid((rows + rpw - 1) / rpw, layers), threads(kSolveThreads * scale);
+#define SCD_FIT_TRIDIAG_ROWS(PRE, ROWS, THREADS)                                                  \
+  do {                                                                                           \
+    if (pair)                                                                                    \
+      hipLaunchKernelGGL((fit_tridiag_kernel<PRE, ROWS, THREADS, true>), grid, threads, 0,       \
+                         stream, a, write);                                                      \
+    else                                                                                         \
+      hipLaunchKernelGGL((fit_tridiag_kernel<PRE, ROWS, THREADS, false>), grid, threads, 0,      \
+                         stream, a, write);                                                      \
   } while (0)
-    if (rows <= 512) SCD_FIT_TRIDIAG(8);
-    else if (rows <= 1024) SCD_FIT_TRIDIAG(16);
-    else if (rows <= 1536) SCD_FIT_TRIDIAG(24);
-    else SCD_FIT_TRIDIAG(32);
+#define SCD_FIT_TRIDIAG(PRE, S)                                                                  \
+  do {                                                                                           \
+    if (rpw == 8 * S) SCD_FIT_TRIDIAG_ROWS(PRE, 8 * S, kSolveThreads * S);                       \
+    else SCD_FIT_TRIDIAG_ROWS(PRE, 4 * S, kSolveThreads * S);                                    \
+  } while (0)
+    if (rows <= 512) SCD_FIT_TRIDIAG(8, 1);
+    else if (rows <= 1024) SCD_FIT_TRIDIAG(16, 1);
+    else if (rows <= 1536) SCD_FIT_TRIDIAG(24, 2);
+    else SCD_FIT_TRIDIAG(32, 2);
 #undef SCD_FIT_TRIDIAG
+#undef SCD_FIT_TRIDIAG_ROWS
   }
   a.step = k0;
   hipLaunchKernelGGL(fit_tridiag_tail_kernel, dim3(layers), dim3(kTailThreads), 0, stream, a);
