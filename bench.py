@@ -312,9 +312,10 @@ def time_fit(dev, steps, warmup, stream, fit_workload="fit_llama3_8b_head_shared
             "solve": {"kernels": "fit_prep/tridiag/bisect/inverse/back/project/normal/chol/out",
                       "ms_per_call": round(solve_ms / 2, 3), "calls": 2,
                       "layers_per_call": len(R),
-                      # prep, the per-column Householder steps until 128 rows remain, their
-                      # one-launch tail, five stages, the Cholesky (one launch up to 128), the solves
-                      "launches_per_call": 1 + max(n2 - 128, 0) + 1 + 5 + (1 if w <= 128 else w) + 1}}
+                      # prep, the per-column Householder steps until 256 rows remain, their
+                      # one-launch tail, five stages, the Cholesky (panels of 64 columns, an update
+                      # after all but the last), the two solves
+                      "launches_per_call": 1 + max(n2 - 256, 0) + 1 + 5 + 2 * (w // 64) - 1 + 2}}
 
 
 def time_receive(wl, dev, steps, warmup, stream, model, batch, rope, inp, z_k, z_v, z_h,
