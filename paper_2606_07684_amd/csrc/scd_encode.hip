@@ -46,7 +46,8 @@ __device__ constexpr int chunk_col(int s, int h, bool derope) {
 // DEROPE = key jobs; MU = every job of the launch has an offset.
 template <int RB, int DH, bool DEROPE, bool MU, int DEPTH>
 __global__ __launch_bounds__(kThreads) void encode_bf16_kernel(GemmParams p) {
-  // With an offset a workgroup takes 127 rows and mu itself as its last one (not rotated)
+  // With an offset a workgroup takes 127 rows and mu itself as its last one, which is not rotated: a
+  // rotation by zero would turn an infinite entry's partner into NaN
   constexpr int kRows = MU ? kEncodeRowsMu : kEncodeRows;
   extern __shared__ __attribute__((aligned(16))) uint16_t lds[];
   // Weight chunk rows: padded (DEPTH 1) or swizzled without padding (DEPTH 2, where every wave must
@@ -121,8 +122,8 @@ __global__ __launch_bounds__(kThreads) void encode_bf16_kernel(GemmParams p) {
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
         const float2 v = cs_row[16 * o + 8 * h + e];
-        cs_c[o][e] = mu_row ? 1.f : v.x;
-        cs_s[o][e] = mu_row ? 0.f : v.y;
+        cs_c[o][e] = v.x;
+        cs_s[o][e] = v.y;
       }
   }
 
@@ -171,8 +172,8 @@ __global__ __launch_bounds__(kThreads) void encode_bf16_kernel(GemmParams p) {
             u[e] = a * cc + b * sn;
             v[e] = b * cc - a * sn;
           }
-          bu = __builtin_bit_cast(bf16x8, pack8(u));
-          bv = __builtin_bit_cast(bf16x8, pack8(v));
+          bu = __builtin_bit_cast(bf16x8, mu_row ? x[s] : pack8(u));
+          bv = __builtin_bit_cast(bf16x8, mu_row ? x[s + 1] : pack8(v));
         } else {
           bu = __builtin_bit_cast(bf16x8, x[s]);
           bv = __builtin_bit_cast(bf16x8, x[s + 1]);

@@ -122,6 +122,24 @@ def test_encode_shapes(heads, head_dim, shared, tokens, layers, ranks, mu):
     U.assert_within(U.compare_all(wl, inp, out), BF16_TOL, wl.name)
 
 
+# An infinite offset entry reaches every code as minus infinity times its encoder weight's sign, and
+# nothing becomes NaN: on the streamed kernel (w = 1024, rank 256), the resident one (w = 256) and the
+# generic one (heads of 32; fp32), keys and values.
+@pytest.mark.parametrize("dtype,heads,head_dim,rank,tokens", [
+    ("bf16", 8, 128, 256, 17000), ("bf16", 2, 128, 64, 300), ("bf16", 4, 32, 32, 300), ("f32", 4, 64, 32, 300)])
+def test_encode_infinite_offset(dtype, heads, head_dim, rank, tokens):
+    wl = W.Workload(f"inf_{dtype}_{rank}", 1, 256, heads, head_dim, (tokens,), (rank,), (), 5e5, dtype,
+                    with_mu=True)
+    inp = W.Inputs(wl, torch.device("cuda"), decode=False, patch=False)
+    col = head_dim // 2 + 5
+    for mu in (inp.mu_k[0], inp.mu_v[0]):
+        mu[col] = float("inf")
+    out = U.run_gpu(wl, inp, scd.scd_rope_table(U.model_of(wl), wl.max_position), which=("encode",))
+    for z, w in ((out["z_k"][0], inp.w_enc_k[0]), (out["z_v"][0], inp.w_enc_v[0])):
+        assert bool((w[:, col] != 0).all())
+        assert torch.equal(z.float(), (-torch.inf * w[:, col].float().sign()).expand(z.shape))
+
+
 # The fit's tridiagonal steps: row registers of 8, 16, 24 and 32 per lane (trailing blocks of up to 512,
 # 1024, 1536 and 2047 rows, each entered and left inside one fit), 4 rows per workgroup and, above 3072
 # rows over the layers, 8; widths whose last workgroup and last lane registers are partly filled.
