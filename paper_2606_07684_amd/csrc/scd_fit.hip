@@ -692,13 +692,18 @@ __device__ inline Slots slots(double* work, int w, int layer) {
   return s;
 }
 
-// Centred Gram entry G[i][j] - s_i s_j / N in fp64 (inv = 1 / N, or 0 without centring); every stage
-// that needs G_c evaluates it with this one expression, so all see the same values.  (A division per
-// entry cost more than the products it fed.)
-__device__ inline double centred(const float* gram, const float* cs, int n, int i, int j, double inv) {
+// Centred Gram entry G[i][j] - s_i s_j / N in fp64 (inv = 1 / N rounded, or 0 without centring); every
+// stage that needs G_c evaluates it with this one expression, so all see the same values.  The product
+// of two fp32 sums is exact, and the quotient is its product with inv corrected by the exact remainder,
+// which rounds as a division does (Markstein's theorem) at a quarter of its instructions.  A channel that is
+// constant over the rows thus centres to exact zeros, as with a division; s_i s_j inv alone leaves
+// rounding noise that the solve takes for a direction.
+__device__ inline double centred(const float* gram, const float* cs, int n, int i, int j, double rows,
+                                 double inv) {
   const double g = static_cast<double>(gram[static_cast<int64_t>(i) * n + j]);
   if (inv == 0.0) return g;
-  return g - static_cast<double>(cs[i]) * static_cast<double>(cs[j]) * inv;
+  const double s = static_cast<double>(cs[i]) * static_cast<double>(cs[j]), q = s * inv;
+  return g - fma(fma(-q, rows, s), inv, q);
 }
 
 // Wave-wide fp64 sum without LDS: four DPP steps inside rows of 16 lanes, then the rows (halves)
@@ -757,7 +762,7 @@ __global__ __launch_bounds__(kSolveThreads) void fit_prep_kernel(const FitSolveP
   const int i0 = blockIdx.x * kSolveRows;
   for (int e = threadIdx.x; e < kSolveRows * n; e += kSolveThreads) {
     const int i = i0 + e / n, j = e % n;
-    if (i < n) s.z[static_cast<int64_t>(i) * n + j] = centred(jb.gram, jb.colsum, n, i, j, center ? 1.0 / rows : 0.0);
+    if (i < n) s.z[static_cast<int64_t>(i) * n + j] = centred(jb.gram, jb.colsum, n, i, j, rows, center ? 1.0 / rows : 0.0);
   }
   if (blockIdx.x != 0) return;
   if (threadIdx.x == 0)
@@ -1533,7 +1538,7 @@ __global__ __launch_bounds__(kSolveThreads) void fit_project_kernel(const SolveA
   tile_product(
       n,
       // G_c is symmetric: its column i0 + x read as a row, so the loads run along rows
-      [&](int kk, int x) { return centred(jb.gram, jb.colsum, n, kk, i0 + x, inv); },
+      [&](int kk, int x) { return centred(jb.gram, jb.colsum, n, kk, i0 + x, a.rows, inv); },
       [&](int kk, int x) {
         return m0 + x < r ? s.z[static_cast<int64_t>(kk) * r + m0 + x] : 0.0;
       },
@@ -1569,7 +1574,7 @@ __global__ __launch_bounds__(kSolveThreads) void fit_normal_kernel(const SolveAr
     for (int e = threadIdx.x; e < 64 * 64; e += kSolveThreads) {
       const int i = i0 + e / 64, j = j0 + e % 64;
       s.x[static_cast<int64_t>(i) * w + j] =
-          centred(jb.gram, jb.colsum, n, i, j, inv) + (i == j ? a.lambda : 0.0);
+          centred(jb.gram, jb.colsum, n, i, j, a.rows, inv) + (i == j ? a.lambda : 0.0);
     }
   }
 }

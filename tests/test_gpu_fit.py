@@ -427,3 +427,23 @@ def test_fitted_bases_at_the_config1_shape_through_the_codec():
         assert U.max_abs_rel(want_k, U.f64(held["k"][1][l])) < 0.2
         assert not torch.allclose(fits["v"][1][l].float(), fits["v"][0][l].float().T)
     U.assert_within(errs, U.TOL[wl.dtype], "fitted bases at the config-1 shape")
+
+
+def test_constant_channel_centres_to_exact_zeros():
+    # A producer channel that is constant over the rows: with integer rows the fp32 sums are exact, so its
+    # centred row of the Gram is exactly zero (98 * 98 * (1 / 98) is not 98 in fp64, 98 * 98 / 98 is).  Its
+    # encoder weights are then exactly zero with lambda > 0, and A^T A is singular with lambda = 0, which
+    # leaves NaN in the layer's outputs.
+    dev, w, r, n = torch.device("cuda"), 64, 16, 98
+    X = torch.randint(-3, 4, (n, 2 * w), generator=torch.Generator().manual_seed(5)).double()
+    X[:, 7] = 1.0
+    model = scd.Model(n_layers=1, d_model=64, n_kv_heads=1, head_dim=64, rope_theta=1e4, dtype="f32",
+                      is_patch=[0], rank_k=[r], rank_v=[r], rank_h=[r])
+    gram, colsum = [(X.T @ X).float().to(dev)], [X.sum(0).float().to(dev)]
+    out = [[torch.empty(*s, device=dev)] for s in ((r, w), (w, r), (w,), (w,))]
+    ws = torch.empty(scd.scd_fit_workspace_bytes(model, n), dtype=torch.uint8, device=dev)
+    scd.scd_fit_solve(model, scd.FIT_VALUES, n, 1.0, True, gram, colsum, *out, ws)
+    assert all(bool(torch.isfinite(t[0]).all()) for t in out)
+    assert bool((out[0][0][:, 7] == 0).all()) and bool((out[0][0][:, 6] != 0).all())
+    scd.scd_fit_solve(model, scd.FIT_VALUES, n, 0.0, True, gram, colsum, *out, ws)
+    assert bool(torch.isnan(out[0][0]).all())
