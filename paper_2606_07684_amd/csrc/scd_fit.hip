@@ -1360,8 +1360,10 @@ __device__ inline void inverse_cluster(const double* d, const double* e, int n, 
       }
       sc = mx > 0.0 ? 1.0 / mx : 1.0;
     }
+    // a norm past fp64's range (only a zero matrix gets there, whose pivots are all the guard) leaves NaN:
+    // dividing by it would pass a zero vector off as a direction
     const Strided o = out(m);
-    const double inv = 1.0 / sqrt(ss);
+    const double inv = ss < INFINITY ? 1.0 / sqrt(ss) : kNaN;
     for (int i = 0; i < n; ++i) o[i] = y[i] * inv;
   }
 }

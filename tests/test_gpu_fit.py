@@ -447,3 +447,17 @@ def test_constant_channel_centres_to_exact_zeros():
     assert bool((out[0][0][:, 7] == 0).all()) and bool((out[0][0][:, 6] != 0).all())
     scd.scd_fit_solve(model, scd.FIT_VALUES, n, 0.0, True, gram, colsum, *out, ws)
     assert bool(torch.isnan(out[0][0]).all())
+
+
+@pytest.mark.parametrize("w", [64, 256])
+def test_zero_gram_leaves_nan(w):
+    # A zero Gram has no directions: every entry of the layer's encoder and decoder is NaN, none a plain
+    # number, on both instances of the inverse iteration.
+    dev, r = torch.device("cuda"), 16
+    model = scd.Model(n_layers=1, d_model=64, n_kv_heads=w // 64, head_dim=64, rope_theta=1e4, dtype="f32",
+                      is_patch=[0], rank_k=[r], rank_v=[r], rank_h=[r])
+    gram, colsum = [torch.zeros(2 * w, 2 * w, device=dev)], [torch.zeros(2 * w, device=dev)]
+    out = [[torch.empty(*s, device=dev)] for s in ((r, w), (w, r), (w,), (w,))]
+    ws = torch.empty(scd.scd_fit_workspace_bytes(model, 100), dtype=torch.uint8, device=dev)
+    scd.scd_fit_solve(model, scd.FIT_VALUES, 100, 1.0, True, gram, colsum, *out, ws)
+    assert bool(torch.isnan(out[0][0]).all()) and bool(torch.isnan(out[1][0]).all())
