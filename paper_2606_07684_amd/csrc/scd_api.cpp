@@ -161,7 +161,7 @@ scd::GemmParams base_params(const scd_model_t* m, const scd_batch_t* b, int64_t 
 // Jobs on the generic kernel.
 scd_status_t run_generic(scd::Op op, const scd::GemmParams& base,
                          const std::vector<scd::GemmJob>& jobs, int dtype, hipStream_t stream) {
-  const scd::GenericShape shape = scd::generic_shape(jobs.data(), jobs.size(), base.m);
+  const scd::GenericShape shape = scd::generic_shape(op, dtype == SCD_BF16, jobs.data(), jobs.size(), base.m);
   JobPacker jp(base, scd::generic_rows(shape), scd::generic_cols(shape));
   for (const auto& j : jobs) jp.add(j);
   for (const auto& p : jp.build()) {

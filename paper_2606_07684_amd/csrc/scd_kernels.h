@@ -49,15 +49,18 @@ struct GemmParams {
 static_assert(sizeof(GemmParams) <= 4096, "kernel argument block");
 
 // Workgroup shape of a generic launch, by the rows x columns of C it computes: 4 waves of 32 x 64 or
-// 32 x 32 along the rows, or one tile whose 4 or 8 waves split the contraction.
-enum class GenericShape : int { k128x64 = 0, k128x32 = 1, k32x64 = 2, k32x32 = 3 };
-GenericShape generic_shape(const GemmJob* jobs, size_t n_jobs, int64_t m);
-int generic_rows(GenericShape s);
-int generic_cols(GenericShape s);
+// 32 x 32 along the rows, one tile whose 4 or 8 waves split the contraction, or a 128 x 128 tile staged
+// through LDS (the bf16 decode and Patch only).
+enum class GenericShape : int { k128x64 = 0, k128x32 = 1, k32x64 = 2, k32x32 = 3, kStaged = 4 };
 
 // The codec step a launch performs; each step is its own kernel symbol so profiles attribute time
 // per step.
 enum class Op : int { kReuseDecode = 0, kPatchKV = 1, kEncodeKV = 2, kEncodeH = 3, kPatchAlign = 4 };
+
+// Shape of a launch of n_jobs products of m rows.
+GenericShape generic_shape(Op op, bool bf16, const GemmJob* jobs, size_t n_jobs, int64_t m);
+int generic_rows(GenericShape s);
+int generic_cols(GenericShape s);
 
 // Launchers (return the hipError_t of the launch).
 hipError_t launch_gemm(Op op, bool bf16, GenericShape shape, const GemmParams& p,

@@ -88,6 +88,23 @@ def test_generic_shapes(dtype, heads, head_dim, tokens):
     U.assert_within(U.compare_all(wl, inp, out), U.TOL[dtype], wl.name)
 
 
+# The staged tiles of the bf16 decode and Patch off the specialised kernels' shapes: rows that end inside a
+# tile (192 and 160 columns), heads of 32, 64 and 128, more than 256 requests (some empty) with start
+# positions, ranks that end inside a contraction step, with and without offsets and biases.
+@pytest.mark.parametrize("heads,head_dim,d_model,tokens,layers,ranks,mu", [
+    (3, 64, 96, (1500, 559), 6, (16, 48, 96, 128, 176, 192), True),
+    (5, 32, 160, (1999,), 6, (32, 80, 160, 16, 128, 64), False),
+    (8, 128, 64, tuple(i % 13 for i in range(300)), 3, (112, 256, 64), True)])
+def test_staged_tiles(heads, head_dim, d_model, tokens, layers, ranks, mu):
+    wl = W.Workload(f"staged_{heads}_{head_dim}", layers, d_model, heads, head_dim, tokens, ranks, (0,) if d_model > 64
+                    else (), 1e4, "bf16", with_bias=mu, with_mu=mu, pos0=tuple(5 * i for i in range(len(tokens))))
+    dev = torch.device("cuda")
+    inp = W.Inputs(wl, dev, encode=False)
+    rope = scd.scd_rope_table(U.model_of(wl), wl.max_position)
+    out = U.run_gpu(wl, inp, rope, which=("decode", "patch"), fill=float("nan"))
+    U.assert_within(U.compare_all(wl, inp, out), BF16_TOL, wl.name)
+
+
 # Ranks that are odd multiples of 16 on the bf16 decode (the contraction's last step zeroed).
 @pytest.mark.parametrize("ranks,ranks_v", [((16, 48, 80), (112, 16, 48)), ((144, 176, 208), (240, 16, 144))])
 def test_decode_odd_ranks(ranks, ranks_v):

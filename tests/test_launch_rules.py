@@ -1,0 +1,43 @@
+"""The launch rules (which kernel shape a call takes), evaluated on the host: each case names the side of
+a rule that a GPU test or a measurement stands on, so that a changed rule cannot move it silently."""
+import ctypes
+
+import pytest
+
+import paper_2606_07684_amd as scd
+
+DECODE, PATCH, ENCODE_KV = 0, 1, 2
+K128X64, K128X32, K32X64, K32X32, STAGED = range(5)
+
+
+class _Job(ctypes.Structure):
+    _fields_ = [(n, ctypes.c_void_p) for n in ("a", "b", "c", "vec")] + [
+        (n, ctypes.c_int32) for n in ("n", "k", "flags", "tile_begin")]
+
+
+def _rule(symbol, res, *args):
+    fn = getattr(scd.load_library(), symbol)
+    fn.restype, fn.argtypes = res, list(args)
+    return fn
+
+
+def generic_shape(op, bf16, m, jobs):
+    arr = (_Job * len(jobs))(*[_Job(None, None, None, None, n, k, 0, 0) for n, k in jobs])
+    fn = _rule("_ZN3scd13generic_shapeENS_2OpEbPKNS_7GemmJobEml", ctypes.c_int, ctypes.c_int,
+               ctypes.c_bool, ctypes.c_void_p, ctypes.c_size_t, ctypes.c_int64)
+    return fn(op, bf16, arr, len(jobs), m)
+
+
+@pytest.mark.parametrize("op,bf16,tokens,jobs,want", [
+    # bf16 decode: more than 256 requests of an 8-head model, heads of 32, a short prefix, heads' shared rows
+    (DECODE, True, 32768, [(1024, 128)] * 56, STAGED), (DECODE, True, 8192, [(512, 64)] * 16, STAGED),
+    (DECODE, True, 64, [(512, 64)] * 16, K128X32), (DECODE, True, 131072, [(64, 64)] * 8, K128X64),
+    (DECODE, True, 262144, [(32, 32)] * 12, K128X32),
+    # bf16 Patch: heads of 32, and a prefix whose contraction is better split
+    (PATCH, True, 8192, [(512, 2048)] * 8, STAGED), (PATCH, True, 200, [(1024, 4128)] * 8, K32X64),
+    # fp32 decode takes 16-byte stores of 32 x 64 waves; the key and value encode, by the last round
+    (DECODE, False, 8192, [(1024, 128)] * 32, K128X64), (DECODE, False, 100, [(256, 32)] * 6, K128X32),
+    (ENCODE_KV, False, 4099, [(64, 512)] * 16, K32X64), (ENCODE_KV, False, 8192, [(64, 512)] * 16, K128X64),
+    (ENCODE_KV, False, 64, [(64, 512)] * 16, K32X32), (ENCODE_KV, True, 4099, [(128, 1024)] * 16, K128X64)])
+def test_generic_shape(op, bf16, tokens, jobs, want):
+    assert generic_shape(op, bf16, tokens, jobs) == want
