@@ -27,9 +27,10 @@
 // entries; the product in fp32 is within a few ulp of cos/sin(p w).  Codes and factors are reused
 // for every channel group.
 //
-// Ranks are multiples of 16, one MFMA step; a rank of 32 KCH - 16 runs its instance's last step on zeros
-// (zeroed code registers, zeroed LDS columns).  Rank 48 at 8192 tokens x 28 layers: 230 us, 712 us on
-// the generic kernel that took such ranks before.
+// Ranks are multiples of 16, one MFMA step; odd multiples are instances of their own (ODD).  With the
+// rank a run-time value, eleven instances needed more than the 256 registers of two waves per SIMD (keys of
+// rank 256 spilled 16, values of rank 128 4); four spill 2 this way.  Rank 48 at 8192 tokens x 28 layers:
+// 230 us with a zeroed last step, 712 us on the generic kernel.
 #include "scd_device.h"
 
 namespace scd {
@@ -59,19 +60,20 @@ struct DecodeCtx {
   uint16_t* C;           // output rows [M, N]
   int64_t M;
   int N, n0;             // row width, first channel of the chunk
-  int K;                 // rank: 32 KCH, or 32 KCH - 16
   bool silu;             // SiLU after the offset (the aligner's first product; never with RoPE)
 };
 
 // One tile: the TT rows from row t0 of the current layer-branch, channels [n0, n0 + 128 NHG).
-// KCH = rank / 32 rounded up, NHG = channel groups of 128, DH = head_dim, ROPE = key jobs, FULL = all TT
-// rows exist (only the last tile of a layer-branch can be partial).
-template <int KCH, int NHG, int DH, bool ROPE, bool FULL, int TT = 32 * waves_for(NHG, KCH)>
+// KCH = rank / 32 rounded up, ODD = the rank is 32 KCH - 16, NHG = channel groups of 128, DH = head_dim,
+// ROPE = key jobs, FULL = all TT rows exist (only the last tile of a layer-branch can be partial).
+template <int KCH, bool ODD, int NHG, int DH, bool ROPE, bool FULL, int TT = 32 * waves_for(NHG, KCH)>
 __device__ __forceinline__ void decode_tile(const GemmParams& p, const LdsBatch& lb,
                                             const DecodeCtx& c, int64_t t0, const uint16_t* Fs,
                                             const uint16_t* mus, const float2* dtab, int lane,
                                             int wave) {
-  constexpr int LDK = 32 * KCH + 8;
+  constexpr int kSteps = 2 * KCH - (ODD ? 1 : 0);  // MFMA steps of 16
+  constexpr int K = 16 * kSteps;
+  constexpr int LDK = K + 8;  // an odd number of 16-byte pieces
   constexpr int HALF = DH / 2;
   constexpr int PS = HALF / 32;  // blocks between RoPE partners: 2 (d_h 128) or 1 (d_h 64)
   constexpr int DSTRIDE = HALF + 2;  // padded LDS row of the in-half factor table (float2)
@@ -84,15 +86,11 @@ __device__ __forceinline__ void decode_tile(const GemmParams& p, const LdsBatch&
 
     // codes: lane half h holds k = 16i + 8h + (0..7); rows past the end read row 0 (in bounds,
     // never stored)
-    uint4 z[2 * KCH];
+    uint4 z[kSteps];
     {
-      const uint16_t* zr = c.Z + (row < c.M ? row : 0) * c.K + 8 * h;
+      const uint16_t* zr = c.Z + (row < c.M ? row : 0) * K + 8 * h;
 #pragma unroll
-      for (int i = 0; i < 2 * KCH - 1; ++i) z[i] = *reinterpret_cast<const uint4*>(zr + 16 * i);
-      // a rank of 32 KCH - 16 ends one step early: zero codes (against a zeroed basis)
-      constexpr int kLast = 2 * KCH - 1;
-      z[kLast] = make_uint4(0, 0, 0, 0);
-      if (c.K == 32 * KCH) z[kLast] = *reinterpret_cast<const uint4*>(zr + 16 * kLast);
+      for (int i = 0; i < kSteps; ++i) z[i] = *reinterpret_cast<const uint4*>(zr + 16 * i);
     }
 
     // RoPE factors of this row for its pair indices i0(q) + r, q = 0, 1
@@ -126,7 +124,7 @@ __device__ __forceinline__ void decode_tile(const GemmParams& p, const LdsBatch&
 #pragma unroll
         for (int e = 0; e < 16; ++e) acc[s][e] = 0.f;
 #pragma unroll
-      for (int i = 0; i < 2 * KCH; ++i) {
+      for (int i = 0; i < kSteps; ++i) {
         const bf16x8 bz = __builtin_bit_cast(bf16x8, z[i]);
 #pragma unroll
         for (int s = 0; s < 4; ++s) {
@@ -207,17 +205,17 @@ __device__ __forceinline__ void decode_tile(const GemmParams& p, const LdsBatch&
 // take the same share, on the same XCD), so a launch sized to the machine runs as one round
 // with every workgroup busy to the end.  A workgroup stages a layer-branch's basis chunk once,
 // when its share enters that layer-branch.
-template <int KCH, int NHG, int DH, bool ROPE>
+template <int KCH, bool ODD, int NHG, int DH, bool ROPE>
 __device__ __forceinline__ void decode_body(const GemmParams& p, uint16_t* lds,
                                             LdsBatch& lbatch) {
   constexpr int kWaves = waves_for(NHG, KCH);
   constexpr int kThreads = 64 * kWaves;
   constexpr int kTT = 32 * kWaves;
   constexpr int CN = 128 * NHG;
-  constexpr int LDK = 32 * KCH + 8;
+  constexpr int K = 32 * KCH - (ODD ? 16 : 0);
+  constexpr int LDK = K + 8;
   constexpr int HALF = DH / 2;
   constexpr int DSTRIDE = HALF + 2;
-  const int K = p.jobs[0].k;  // every job of a launch has the same rank
   uint16_t* Fs = lds;                                                   // [CN][LDK]
   uint16_t* mus = Fs + CN * LDK;                                        // [CN]
   float2* dtab = reinterpret_cast<float2*>(mus + CN);                   // [kDRows][DSTRIDE]
@@ -250,7 +248,6 @@ __device__ __forceinline__ void decode_body(const GemmParams& p, uint16_t* lds,
   c.M = M;
   c.N = N;
   c.n0 = nc * CN;
-  c.K = K;
   int cur = -1;
 #pragma unroll 1
   for (int64_t gt = first; gt < last; ++gt) {
@@ -271,10 +268,6 @@ __device__ __forceinline__ void decode_body(const GemmParams& p, uint16_t* lds,
       c.silu = (job.flags & kSiluOut) != 0;
       dma_rows(Fs, CN, K / 8, LDK / 8, wave, kWaves, lane,
                [&](int rho) { return F + static_cast<int64_t>(c.n0 + row_of_lds(rho)) * K; });
-      if (K != 32 * KCH) {  // columns K .. K + 15 of every LDS row: the step past an odd multiple of 16
-        for (int i = tid; i < 2 * CN; i += kThreads)
-          *reinterpret_cast<uint4*>(Fs + (i >> 1) * LDK + K + 8 * (i & 1)) = make_uint4(0, 0, 0, 0);
-      }
       if (tid < CN / 8) {
         const uint4 v = add_mu ? *reinterpret_cast<const uint4*>(mu + c.n0 + 8 * tid)
                                : make_uint4(0, 0, 0, 0);
@@ -290,83 +283,70 @@ __device__ __forceinline__ void decode_body(const GemmParams& p, uint16_t* lds,
     }
     // one bounds-checked body for full and partial tiles (a second copy of the loop body costs
     // registers)
-    decode_tile<KCH, NHG, DH, ROPE, false>(p, lbatch, c, t0, Fs, mus, dtab, lane, wave);
+    decode_tile<KCH, ODD, NHG, DH, ROPE, false>(p, lbatch, c, t0, Fs, mus, dtab, lane, wave);
   }
 }
 
-template <int KCH, int NHG, int DH, bool ROPE>
+template <int KCH, bool ODD, int NHG, int DH, bool ROPE>
 __global__ __launch_bounds__(64 * waves_for(NHG, KCH), 2) void reuse_decode_bf16_kernel(
     GemmParams p) {
   extern __shared__ __attribute__((aligned(16))) uint16_t lds[];
   __shared__ LdsBatch lbatch;
-  decode_body<KCH, NHG, DH, ROPE>(p, lds, lbatch);
+  decode_body<KCH, ODD, NHG, DH, ROPE>(p, lds, lbatch);
 }
 
 // The aligner's first product (act = SiLU(z_h w1^T + b1)) on the same body: a short contraction
 // whose time is writing its output, like the Reuse decode; its own symbol so that profiles keep
 // the two steps apart.
-template <int KCH, int NHG, int DH>
+template <int KCH, bool ODD, int NHG, int DH>
 __global__ __launch_bounds__(64 * waves_for(NHG, KCH), 2) void patch_align_act_bf16_kernel(
     GemmParams p) {
   extern __shared__ __attribute__((aligned(16))) uint16_t lds[];
   __shared__ LdsBatch lbatch;
-  decode_body<KCH, NHG, DH, false>(p, lds, lbatch);
+  decode_body<KCH, ODD, NHG, DH, false>(p, lds, lbatch);
+}
+
+// Instances by rank; ranks above 128 use at most two channel groups per workgroup
+// (decode_channel_groups).
+template <int NHG, int DH, typename LaunchFn>
+hipError_t for_rank(int rank, LaunchFn launch) {
+  switch (rank) {
+#define SCD_DECODE_CASE(KC)                                   \
+  case 32 * KC - 16: return launch(IntC<KC>{}, IntC<1>{});    \
+  case 32 * KC: return launch(IntC<KC>{}, IntC<0>{});
+    SCD_DECODE_CASE(1) SCD_DECODE_CASE(2) SCD_DECODE_CASE(3) SCD_DECODE_CASE(4)
+    default:
+      break;
+  }
+  if constexpr (NHG <= 2) {
+    switch (rank) {
+      SCD_DECODE_CASE(5) SCD_DECODE_CASE(6) SCD_DECODE_CASE(7) SCD_DECODE_CASE(8)
+      default:
+        break;
+    }
+  }
+#undef SCD_DECODE_CASE
+  return hipErrorInvalidValue;
 }
 
 template <int NHG, int DH>
-hipError_t launch_align_kch(int kch, const GemmParams& p, int grid_size, size_t lds,
-                            hipStream_t stream) {
-  switch (kch) {
-#define SCD_ALIGN_CASE(KC)                                                                     \
-  case KC:                                                                                     \
-    hipLaunchKernelGGL((patch_align_act_bf16_kernel<KC, NHG, DH>), dim3(grid_size),           \
-                       dim3(64 * waves_for(NHG, KC)), lds, stream, p);                        \
+hipError_t launch_align(int rank, const GemmParams& p, int grid_size, size_t lds, hipStream_t stream) {
+  return for_rank<NHG, DH>(rank, [&](auto kch, auto odd) {
+    constexpr int KCH = decltype(kch)::value;
+    hipLaunchKernelGGL((patch_align_act_bf16_kernel<KCH, decltype(odd)::value != 0, NHG, DH>),
+                       dim3(grid_size), dim3(64 * waves_for(NHG, KCH)), lds, stream, p);
     return hipGetLastError();
-    SCD_ALIGN_CASE(1) SCD_ALIGN_CASE(2) SCD_ALIGN_CASE(3) SCD_ALIGN_CASE(4)
-    default:
-      break;
-  }
-  // ranks above 128 use at most two channel groups per workgroup (decode_channel_groups)
-  if constexpr (NHG <= 2) {
-    switch (kch) {
-      SCD_ALIGN_CASE(5) SCD_ALIGN_CASE(6) SCD_ALIGN_CASE(7) SCD_ALIGN_CASE(8)
-      default:
-        break;
-    }
-  }
-#undef SCD_ALIGN_CASE
-  return hipErrorInvalidValue;
+  });
 }
 
 template <int NHG, int DH, bool ROPE>
-hipError_t launch_kch(int kch, const GemmParams& p, int grid_size, size_t lds,
-                      hipStream_t stream) {
-  switch (kch) {
-#define SCD_DECODE_CASE(KC)                                                                   \
-  case KC:                                                                                    \
-    hipLaunchKernelGGL((reuse_decode_bf16_kernel<KC, NHG, DH, ROPE>), dim3(grid_size),       \
-                       dim3(64 * waves_for(NHG, KC)), lds, stream, p);                        \
+hipError_t launch_decode(int rank, const GemmParams& p, int grid_size, size_t lds, hipStream_t stream) {
+  return for_rank<NHG, DH>(rank, [&](auto kch, auto odd) {
+    constexpr int KCH = decltype(kch)::value;
+    hipLaunchKernelGGL((reuse_decode_bf16_kernel<KCH, decltype(odd)::value != 0, NHG, DH, ROPE>),
+                       dim3(grid_size), dim3(64 * waves_for(NHG, KCH)), lds, stream, p);
     return hipGetLastError();
-    SCD_DECODE_CASE(1) SCD_DECODE_CASE(2) SCD_DECODE_CASE(3) SCD_DECODE_CASE(4)
-#undef SCD_DECODE_CASE
-    default:
-      break;
-  }
-  // ranks above 128 use at most two channel groups per workgroup (decode_channel_groups)
-  if constexpr (NHG <= 2) {
-    switch (kch) {
-#define SCD_DECODE_CASE(KC)                                                                   \
-  case KC:                                                                                    \
-    hipLaunchKernelGGL((reuse_decode_bf16_kernel<KC, NHG, DH, ROPE>), dim3(grid_size),       \
-                       dim3(64 * waves_for(NHG, KC)), lds, stream, p);                        \
-    return hipGetLastError();
-      SCD_DECODE_CASE(5) SCD_DECODE_CASE(6) SCD_DECODE_CASE(7) SCD_DECODE_CASE(8)
-#undef SCD_DECODE_CASE
-      default:
-        break;
-    }
-  }
-  return hipErrorInvalidValue;
+  });
 }
 
 }  // namespace
@@ -442,7 +422,7 @@ hipError_t launch_decode_bf16(int nhg, const GemmParams& p, hipStream_t stream, 
   for (int i = 1; i < p.n_jobs; ++i)
     if (p.jobs[i].n != p.jobs[0].n) return hipErrorInvalidValue;
   const int kch = (rank + 31) / 32;
-  const size_t lds = decode_bf16_lds_bytes(nhg, 32 * kch, p.head_dim);
+  const size_t lds = decode_bf16_lds_bytes(nhg, rank, p.head_dim);
   // one round of workgroups: as many as the compute units hold at once (LDS and the two waves per
   // SIMD the kernel is built for), in whole sets of channel-chunk siblings, at most one set per
   // row tile
@@ -460,9 +440,9 @@ hipError_t launch_decode_bf16(int nhg, const GemmParams& p, hipStream_t stream, 
   if (align && rope) return hipErrorInvalidValue;
 #define SCD_DECODE_DISPATCH(NHG, DH)                                                    \
   if (nhg == NHG && p.head_dim == DH)                                                   \
-    return align  ? launch_align_kch<NHG, DH>(kch, p, grid_size, lds, stream)           \
-           : rope ? launch_kch<NHG, DH, true>(kch, p, grid_size, lds, stream)           \
-                  : launch_kch<NHG, DH, false>(kch, p, grid_size, lds, stream);
+    return align  ? launch_align<NHG, DH>(rank, p, grid_size, lds, stream)              \
+           : rope ? launch_decode<NHG, DH, true>(rank, p, grid_size, lds, stream)       \
+                  : launch_decode<NHG, DH, false>(rank, p, grid_size, lds, stream);
   SCD_DECODE_DISPATCH(4, 128)
   SCD_DECODE_DISPATCH(2, 128)
   SCD_DECODE_DISPATCH(1, 128)
