@@ -48,9 +48,18 @@ constexpr int waves_for(int nhg, int kch) {
 // stores in flight closer together: rank 32 at 16,384 tokens x 28 layers (keys and values, 1.88 GB
 // written) takes 420 us with one such workgroup per CU and 545 us with two; rank 64, 442 us with 4
 // waves and 530 us with 8.  Longer contractions need the second wave of each SIMD (rank 128 at 8192
-// tokens: 289 us with 8 waves, 315 us with 4).
-constexpr int wgs_per_cu(int nhg, int kch) {
-  return waves_for(nhg, kch) == 8 || (nhg == 4 && kch <= 2) ? 1 : 2;
+// tokens: 289 us with 8 waves, 315 us with 4).  While the output stays in the memory-side cache (`cached`)
+// it is the launch's latency that counts, and ranks up to 48 run two at 512 channels too (28 layers, us, two
+// / one at 512 channels / two at 256: rank 32, 1000 tokens 32 / 36 / 34, 2000 tokens 52 / 56 / 56 and on
+// operands not in any cache 71 / 76 / 82; rank 48, 2000 tokens 58 / 65 / 59, 73 / 82 / 84).
+constexpr int wgs_per_cu(int nhg, int rank, bool cached) {
+  const int kch = (rank + 31) / 32;
+  if (waves_for(nhg, kch) == 8) return 1;
+  return nhg == 4 && kch <= 2 && !(cached && rank <= 48) ? 1 : 2;
+}
+// Both branches' output (twice n_jobs products of rows x width) fits the 256 MB memory-side cache.
+constexpr bool output_cached(int64_t rows, int64_t n_jobs, int width) {
+  return rows * n_jobs * width * 2 <= int64_t{128} << 20;
 }
 constexpr int kDRows = kRopeMinRows;  // in-half offsets d = 0..15
 
@@ -355,21 +364,23 @@ hipError_t launch_decode(int rank, const GemmParams& p, int grid_size, size_t ld
 // that fits the LDS reads the codes least often and keeps each row's stores together, but its tiles
 // are large: a launch with few of them ends in a round that leaves CUs idle.  So the chunk with the
 // least rounds x (elements a CU takes per round) wins, each halving of the chunk counted as 1.25
-// times the work.  Keys and values at the 8B shape (28 layers, rank 128), 512 / 256 / 128 channels,
+// times the work, 1.35 above rank 128 (rank 256, 700 tokens x 28 layers, 256 / 128 channels: 55 / 55 us, on
+// operands not in any cache 73 / 77).  Keys and values at the 8B shape (28 layers, rank 128), 512 / 256 / 128 channels,
 // us: 40 tokens 27 / 19 / 15, 333 tokens 37 / 29 / 29, 700 tokens 38 / 40 / 40, 1100 tokens
 // 60 / 44 / 50, 2000 tokens 76 / 95 / 103, 8192 tokens 286 / 329 / 366.  Ranks up to 64 hold only one
 // workgroup of 4 waves per CU at 512 channels, which pays once the stores go to HBM: while both
-// branches' output fits the 256 MB memory-side cache they start at 256 (rank 64, 512 / 256 channels,
-// us: 333 tokens 26 / 24, 1000 tokens 41 / 36, 2000 tokens 63 / 58, 8192 tokens 239 / 284).
+// branches' output fits the memory-side cache they start at 256 (rank 64, 512 / 256 channels,
+// us: 333 tokens 26 / 24, 1000 tokens 41 / 36, 2000 tokens 63 / 58, 8192 tokens 239 / 284), ranks up to 48
+// at 512 with two workgroups (wgs_per_cu).
 int decode_channel_groups(int rank, int basis_width, int64_t rows, int64_t n_jobs) {
   int nhg = basis_width % 512 == 0 ? 4 : (basis_width % 256 == 0 ? 2 : 1);
-  const bool cached = rows * n_jobs * basis_width * 2 <= int64_t{128} << 20;
-  if (nhg == 4 && (rank > 128 || (rank <= 64 && cached))) nhg = 2;
+  const bool cached = output_cached(rows, n_jobs, basis_width);
+  if (nhg == 4 && (rank > 128 || (rank <= 64 && rank > 48 && cached))) nhg = 2;
   constexpr int64_t kCus = 256;
   double best_cost = 0.0, weight = 1.0;
   int best = nhg;
-  for (int g = nhg; g >= 1; g /= 2, weight *= 1.25) {
-    const int64_t tr = decode_tile_rows(g, rank), per_cu = wgs_per_cu(g, (rank + 31) / 32);
+  for (int g = nhg; g >= 1; g /= 2, weight *= rank > 128 ? 1.35 : 1.25) {
+    const int64_t tr = decode_tile_rows(g, rank), per_cu = wgs_per_cu(g, rank, cached);
     const int64_t tiles = (rows + tr - 1) / tr * n_jobs * (basis_width / (128 * g));
     const int64_t rounds = (tiles + kCus * per_cu - 1) / (kCus * per_cu);
     const double cost = weight * static_cast<double>(rounds * per_cu * tr * g);
@@ -430,7 +441,7 @@ hipError_t launch_decode_bf16(int nhg, const GemmParams& p, hipStream_t stream, 
   const hipError_t e = compute_units(&cus);
   if (e != hipSuccess) return e;
   const int waves = waves_for(nhg, kch);
-  const int per_cu = wgs_per_cu(nhg, kch);
+  const int per_cu = wgs_per_cu(nhg, rank, output_cached(p.m, p.n_jobs, p.jobs[0].n));
   const int n_nc = p.jobs[0].n / cn;
   const int64_t tile_rows = 32 * waves;
   const int64_t row_tiles = (p.m + tile_rows - 1) / tile_rows * p.n_jobs;

@@ -155,7 +155,7 @@ SMALL_ALIGN = Workload("small_align_bf16", 3, 512, 2, 128, (300, 77, 650), (64, 
 # Many short Reuse layers: more row tiles than the decode's one round of workgroups, so shares run
 # across layer boundaries (the basis is restaged mid-share) and every layer ends in a partial tile;
 # ranks 128 (512-channel chunks) and 256 (256-channel chunks).
-SMALL_MANY_LAYERS = Workload("small_many_layers_bf16", 72, 256, 8, 128, (300, 340),
+SMALL_MANY_LAYERS = Workload("small_many_layers_bf16", 72, 256, 8, 128, (510, 590),
                              (128,) * 48 + (256,) * 24, (), 5e5, "bf16")
 # Offline Reuse fit (paired producer/consumer calibration caches): ragged batch with start positions,
 # w = D = 128 (one 256 x 256 Gram of three upper tiles, several row slices with a ragged tail);

@@ -55,11 +55,12 @@ def test_fold_tiles(heads, head_dim, d_model, hidden, layers):
                     wl.name)
 
 
-# Reuse decode at 8 KV heads of 128 (w = 1024): chunks of 128, 256 and 512 channels for rank 128, of
-# 128 and 256 for rank 256, of 256 and 512 for ranks 32 and 64.
+# Reuse decode at 8 KV heads of 128 (w = 1024): chunks of 128, 256 and 512 channels for ranks up to 128
+# (512 at rank 32 with two workgroups per CU and with one), of 128 and 256 for rank 256;
+# test_launch_rules.test_decode_chunks names the chunk of each.
 @pytest.mark.parametrize("rank,tokens,layers", [
-    (128, 40, 2), (128, 1999, 7), (128, 8192, 4), (256, 333, 2), (256, 1100, 2), (64, 500, 3),
-    (32, 31000, 2), (64, 31000, 2)])
+    (128, 40, 2), (128, 1999, 7), (128, 8192, 4), (256, 333, 2), (256, 5000, 2), (64, 500, 3),
+    (64, 31000, 2), (64, 40000, 2), (32, 9000, 4), (32, 31000, 2), (32, 40000, 2)])
 def test_decode_chunks(rank, tokens, layers):
     wl = W.Workload(f"chunks_{rank}_{tokens}", layers, 256, 8, 128, (tokens - 7, 7),
                     (rank,) * layers, (), 5e5, "bf16")

@@ -41,3 +41,15 @@ def generic_shape(op, bf16, m, jobs):
     (ENCODE_KV, False, 64, [(64, 512)] * 16, K32X32), (ENCODE_KV, True, 4099, [(128, 1024)] * 16, K128X64)])
 def test_generic_shape(op, bf16, tokens, jobs, want):
     assert generic_shape(op, bf16, tokens, jobs) == want
+
+
+# (rank, tokens, layers): the cases of test_gpu_tiles at w = 1024, and 28 layers of an 8-head model
+@pytest.mark.parametrize("rank,tokens,layers,want", [
+    (128, 40, 2, 1), (128, 1999, 7, 2), (128, 8192, 4, 4), (256, 333, 2, 1), (256, 5000, 2, 2), (64, 500, 3, 1),
+    (64, 31000, 2, 2), (64, 40000, 2, 4), (32, 9000, 4, 2), (32, 31000, 2, 4), (32, 40000, 2, 4),
+    (16, 65700, 1, 4), (48, 65700, 1, 4), (112, 65700, 1, 4), (128, 1100, 48, 4), (256, 1100, 24, 2),
+    (32, 1000, 28, 4), (48, 2000, 28, 4), (64, 2000, 28, 2), (32, 333, 28, 2), (128, 2000, 28, 4), (256, 700, 28, 2)])
+def test_decode_chunks(rank, tokens, layers, want):
+    fn = _rule("_ZN3scd21decode_channel_groupsEiill", ctypes.c_int, ctypes.c_int, ctypes.c_int, ctypes.c_int64,
+               ctypes.c_int64)
+    assert fn(rank, 1024, tokens, layers) == want
