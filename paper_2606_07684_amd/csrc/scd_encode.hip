@@ -335,6 +335,10 @@ __global__ __launch_bounds__(kResThreads, 2) void encode_kv_bf16_kernel(GemmPara
   if (DEROPE && lds_batch) stage_batch(p, lbatch, tid, kResThreads);
 
   constexpr int kNo = DEROPE ? DH / 32 : 1;      // 16-wide offsets per half head
+  // Two sets of input registers (loads one chunk ahead) where three and the factors are more than 256
+  // registers: with three, rank 128 keys spilled 61 (w = 512, 24 layers: 4000 tokens 102 us, two sets 78;
+  // 32,768 tokens 635, two sets 502).
+  constexpr bool kTwoSets = DEROPE && (DH == 128 ? RB >= 3 : RB == 4 && MU);
   for (int64_t t = first; t < last;) {
     const int j = static_cast<int>(t / per_job);
     const int64_t t1 = last < (j + 1) * per_job ? last : (j + 1) * per_job;
@@ -344,8 +348,8 @@ __global__ __launch_bounds__(kResThreads, 2) void encode_kv_bf16_kernel(GemmPara
     const uint16_t* E = static_cast<const uint16_t*>(job.b) + static_cast<int64_t>(code0) * K;
     uint16_t* Z = static_cast<uint16_t*>(job.c);
 
-    // Loads run two chunks ahead of use, across the wave's tiles (t + wave, t + wave + 8, ...).  Past
-    // the last tile they re-read the wave's first one; rows past the end read row 0.
+    // Loads run two chunks (or one, kTwoSets) ahead of use, across the wave's tiles (t + wave, t + wave
+    // + 8, ...).  Past the last tile they re-read the wave's first one; rows past the end read row 0.
     int64_t lt = t + wave;  // tile and chunk of the next load
     int lc = 0;
     const uint16_t* xrow;
@@ -367,7 +371,7 @@ __global__ __launch_bounds__(kResThreads, 2) void encode_kv_bf16_kernel(GemmPara
     uint4 x0[8], x1[8], x2[8];
     if (t != first) lds_barrier();  // every wave is done with the previous job's weights
     load_x(x0);
-    load_x(x1);
+    if constexpr (!kTwoSets) load_x(x1);
     // the encoder -> LDS: chunk c of code row rho (permuted so that a lane ends with 16 consecutive
     // codes of one row), piece q at q ^ (rho & 7); rows past R repeat row 0 and are never stored
     for (int s = wave * 64; s < nchunks * CB * 16; s += kResThreads) {
@@ -425,12 +429,14 @@ __global__ __launch_bounds__(kResThreads, 2) void encode_kv_bf16_kernel(GemmPara
       if constexpr (DEROPE) {
         const int64_t row = (tile - job0) * 32 + (lane & 31);
         const int pos = row < M ? (lds_batch ? row_position_lds(p, lbatch, row) : row_position(p, row)) : 0;
-        const float2* cs_row = p.rope + static_cast<int64_t>(pos) * (DH / 2);
+        int off = 8 * h;  // opaque: hoisted out of the loop, the address took two registers too many
+        asm volatile("" : "+v"(off));
+        const float2* cs_row = p.rope + static_cast<int64_t>(pos) * (DH / 2) + off;
 #pragma unroll
         for (int o = 0; o < kNo; ++o)
 #pragma unroll
           for (int e = 0; e < 8; e += 2) {
-            const float4 v = *reinterpret_cast<const float4*>(cs_row + 16 * o + 8 * h + e);
+            const float4 v = *reinterpret_cast<const float4*>(cs_row + 16 * o + e);
             cs_c[o][e] = v.x;
             cs_s[o][e] = v.y;
             cs_c[o][e + 1] = v.z;
@@ -529,11 +535,17 @@ __global__ __launch_bounds__(kResThreads, 2) void encode_kv_bf16_kernel(GemmPara
       clear();
     };
     while (ct < t1) {
-      step(x0, x2);
-      if (ct >= t1) break;
-      step(x1, x0);
-      if (ct >= t1) break;
-      step(x2, x1);
+      if constexpr (kTwoSets) {
+        step(x0, x1);
+        if (ct >= t1) break;
+        step(x1, x0);
+      } else {
+        step(x0, x2);
+        if (ct >= t1) break;
+        step(x1, x0);
+        if (ct >= t1) break;
+        step(x2, x1);
+      }
     }
     t = t1;
   }
