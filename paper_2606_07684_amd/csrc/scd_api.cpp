@@ -362,8 +362,8 @@ scd_status_t scd_encode(const scd_model_t* model, const scd_batch_t* batch,
   }
   const scd::GemmParams kv_base = base_params(model, batch, T * g, g, rope_table, max_position);
   const scd::GemmParams h_base = base_params(model, batch, T, 1, rope_table, max_position);
-  // one launch per (rank, branch kind, offset present): each is its own kernel instance.  Rows whose
-  // encoder fits the LDS run with it resident, the others stream it (encode_resident).
+  // one launch per (rank, branch kind, offset present): each is its own kernel instance, with the encoder
+  // resident in LDS or streamed (encode_resident)
   auto by_kind = [](const scd::GemmJob& j) {
     const bool mu = (j.flags & scd::kVecIn) != 0 && j.vec != nullptr;
     return j.n * 4 + ((j.flags & scd::kDeropeIn) != 0 ? 2 : 0) + (mu ? 1 : 0);

@@ -621,18 +621,32 @@ static int resident_blocks(int k, int rank) {
   return rank <= 32 ? 1 : rank <= 64 || k > 512 ? 2 : rank <= 96 ? 3 : 4;
 }
 
-// Resident where one workgroup's LDS holds the encoder of every code, so that the rows are read once:
-// keys and values, us streamed / resident: w = 512, rank 96, 32,768 tokens x 24 layers 706 / 617;
-// w = 128 (heads' shared basis), ranks 64 and 32, 8192 tokens x 32 layers 442 / 344; w = 1024, rank 64,
-// 32,768 tokens 1046 / 1020.  Split over workgroups the rows are read once per 64 codes, which loses
-// for large launches (w = 1024, rank 128, 8192 tokens: 315 / 330) and still wins while the launch is
-// one tile per wave and bound by latency (rank 128, 40 tokens 49 / 29, 333 tokens 57 / 35).
+// Where one workgroup's LDS holds the encoder of every code the rows are read once, but a workgroup takes the
+// whole CU and starts with its encoder.  So the kernel pays where the streamed kernel's chain of weight copies
+// is what counts (a launch of few 32-row tiles a wave, of 256 x 8 waves) and where its products are (ranks
+// above 64, long launches); in between, and for few codes, the streamed kernel's several workgroups per CU
+// keep more loads in flight, above all on operands that are in no cache.  Keys and values, us streamed /
+// resident, then the same on operands in no cache (in brackets: tiles a wave of one launch):
+//   w = 1024, rank 64, 14 layers: 1000 tokens (0.22) 42 / 34, 56 / 51; 2000 (0.43) 43 / 42, 67 / 76; 16,384
+//   (3.5) 239 / 244, 282 / 299
+//   w = 512, 24 layers: rank 64, 1000 tokens (0.38) 32 / 30, 46 / 46; 4000 (1.5) 60 / 64, 105 / 112; 20,000
+//   (7.3) 268 / 275, 297 / 317; rank 128, 4000 tokens 80 / 73, 118 / 123; 8192 (3) 159 / 143, 184 / 178;
+//   20,000 329 / 314, 348 / 350
+//   w = 256, 24 layers, rank 128: 4000 tokens (1.5) 51 / 52, 73 / 83; 16,384 (6) 173 / 160, 192 / 195
+//   w = 128 (8 heads' shared basis), 16 layers: rank 64, 100 tokens (0.2) 17 / 19, 22 / 24; 1000 (2) 32 / 34,
+//   48 / 55; 8192 (16) 208 / 199, 227 / 232; rank 32, 8192 tokens 176 / 155, 193 / 192; rank 128 286 / 268,
+//   303 / 291
+// Split over workgroups the rows are read once per 64 codes, which loses for large launches (w = 1024, rank
+// 128, 8192 tokens: 315 / 330) and still wins while the launch is one tile per wave and bound by latency
+// (rank 128, 40 tokens 49 / 29, 333 tokens 57 / 35).
 bool encode_resident(int k, int rank, int64_t rows, int64_t n_jobs) {
   const int rb = resident_blocks(k, rank);
   if (resident_lds(rb, k) + sizeof(LdsBatch) > 160 * 1024) return false;
   const int n_split = (rank + 32 * rb - 1) / (32 * rb);
-  const int64_t wgs = ((rows + 31) / 32 + kResWaves - 1) / kResWaves;
-  return n_split == 1 || wgs * n_jobs * n_split <= kCus;
+  const int64_t per_job = (rows + 31) / 32, waves = kCus * kResWaves, tiles = per_job * n_jobs;
+  if (n_split > 1) return (per_job + kResWaves - 1) / kResWaves * n_jobs * n_split <= kCus;
+  if (k == 128) return tiles >= 8 * waves;
+  return 8 * tiles <= 3 * waves || (rank > 64 && (k >= 512 || tiles >= 2 * waves));
 }
 
 hipError_t launch_encode_kv_bf16(GemmParams p, hipStream_t stream) {

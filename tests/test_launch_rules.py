@@ -53,3 +53,18 @@ def test_decode_chunks(rank, tokens, layers, want):
     fn = _rule("_ZN3scd21decode_channel_groupsEiill", ctypes.c_int, ctypes.c_int, ctypes.c_int, ctypes.c_int64,
                ctypes.c_int64)
     assert fn(rank, 1024, tokens, layers) == want
+
+
+# (w, rank, rows, layers): the cases of test_gpu_tiles.test_encode_shapes, and both sides of each line
+@pytest.mark.parametrize("w,rank,rows,layers,want", [
+    (1024, 256, 303, 1, True), (1024, 128, 5000, 2, True), (256, 64, 9100, 8, False), (256, 96, 9001, 8, False),
+    (512, 128, 700, 1, True), (512, 128, 40000, 2, True), (512, 96, 30100, 3, True), (256, 96, 33000, 4, True),
+    (128, 32, 131080, 4, True), (128, 64, 131080, 4, True), (128, 128, 23992, 1, False),
+    (128, 64, 800, 16, False), (128, 64, 65536, 28, True),
+    (1024, 64, 1500, 14, True), (1024, 64, 2000, 14, False), (512, 64, 1000, 24, True), (512, 64, 4000, 24, False),
+    (512, 96, 4000, 24, True), (256, 128, 4000, 24, False), (256, 128, 16384, 24, True),
+    (1024, 128, 333, 24, True), (1024, 128, 8192, 28, False)])
+def test_encode_resident(w, rank, rows, layers, want):
+    fn = _rule("_ZN3scd15encode_residentEiill", ctypes.c_bool, ctypes.c_int, ctypes.c_int, ctypes.c_int64,
+               ctypes.c_int64)
+    assert fn(w, rank, rows, layers) == want
