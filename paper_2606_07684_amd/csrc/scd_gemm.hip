@@ -213,7 +213,12 @@ __global__ __launch_bounds__(WM * WK * 64, 2) void gemm_nt_kernel(GemmParams p) 
 
   struct Step {
     uint4 x[FM][2], w[FN][2];
-    float4 cs[kEnc ? FM : 1][kEnc ? VL / 2 : 1];
+  };
+  // Rotation factors: loaded with the step's operands, or, where a second set is too many registers (51 of
+  // them spilled), once the step before has used its own.
+  constexpr bool kOneCs = BF16 && FN == 4 && WK > 1;
+  struct Factors {
+    float4 v[kEnc ? FM : 1][kEnc ? VL / 2 : 1];
   };
   // This lane's contraction columns of step i: two blocks, or with deRoPE a block of first halves and
   // their partners.  Both operands take the same columns, so the order does not matter.
@@ -228,6 +233,8 @@ __global__ __launch_bounds__(WM * WK * 64, 2) void gemm_nt_kernel(GemmParams p) 
       c1 = c0 + KB;
     }
   };
+  // steps wk, wk + WK, ...; each step's operands are loaded during the one before
+  const int steps = (K + 2 * KB - 1) / (2 * KB);
   auto load = [&](int i, Step& s) {
     int c0, c1;
     cols(i, c0, c1);
@@ -237,18 +244,26 @@ __global__ __launch_bounds__(WM * WK * 64, 2) void gemm_nt_kernel(GemmParams p) 
     for (int a = 0; a < FM; ++a) {
       s.x[a][0] = *reinterpret_cast<const uint4*>(xrow[a] + d0);
       s.x[a][1] = *reinterpret_cast<const uint4*>(xrow[a] + d1);
-      if constexpr (kEnc) {
-        if (derope) {
-          const float4* cs = reinterpret_cast<const float4*>(csrow[a] + (d0 & hmask));
-#pragma unroll
-          for (int e = 0; e < VL / 2; ++e) s.cs[a][e] = cs[e];
-        }
-      }
     }
 #pragma unroll
     for (int b = 0; b < FN; ++b) {
       s.w[b][0] = *reinterpret_cast<const uint4*>(wrow[b] + d0);
       s.w[b][1] = *reinterpret_cast<const uint4*>(wrow[b] + d1);
+    }
+  };
+
+  auto load_cs = [&](int i, Factors& cs) {
+    if constexpr (kEnc) {
+      if (derope && i < steps) {
+        int c0, c1;
+        cols(i, c0, c1);
+#pragma unroll
+        for (int a = 0; a < FM; ++a) {
+          const float4* q = reinterpret_cast<const float4*>(csrow[a] + ((c0 < K ? c0 : 0) & hmask));
+#pragma unroll
+          for (int e = 0; e < VL / 2; ++e) cs.v[a][e] = q[e];
+        }
+      }
     }
   };
 
@@ -258,7 +273,7 @@ __global__ __launch_bounds__(WM * WK * 64, 2) void gemm_nt_kernel(GemmParams p) 
 #pragma unroll
     for (int b = 0; b < FN; ++b) acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-  auto compute = [&](int i, Step& s) {
+  auto compute = [&](int i, Step& s, Factors& cs) {
     int c[2];
     cols(i, c[0], c[1]);
     if constexpr (kEnc) {
@@ -282,12 +297,12 @@ __global__ __launch_bounds__(WM * WK * 64, 2) void gemm_nt_kernel(GemmParams p) 
           EL::unpack(s.x[a][0], u);
           EL::unpack(s.x[a][1], v);
           if (derope) {
-            const float* cs = reinterpret_cast<const float*>(s.cs[a]);
+            const float* f = reinterpret_cast<const float*>(cs.v[a]);
 #pragma unroll
             for (int e = 0; e < VL; ++e) {
               const float uu = u[e], vv = v[e];
-              u[e] = uu * cs[2 * e] + vv * cs[2 * e + 1];
-              v[e] = vv * cs[2 * e] - uu * cs[2 * e + 1];
+              u[e] = uu * f[2 * e] + vv * f[2 * e + 1];
+              v[e] = vv * f[2 * e] - uu * f[2 * e + 1];
             }
           }
 #pragma unroll
@@ -298,6 +313,7 @@ __global__ __launch_bounds__(WM * WK * 64, 2) void gemm_nt_kernel(GemmParams p) 
           s.x[a][0] = EL::pack(u);
           s.x[a][1] = EL::pack(v);
         }
+        if constexpr (kOneCs) load_cs(i + WK, cs);
       }
     }
 #pragma unroll
@@ -330,18 +346,24 @@ __global__ __launch_bounds__(WM * WK * 64, 2) void gemm_nt_kernel(GemmParams p) 
     }
   };
 
-  // steps wk, wk + WK, ...; each step's operands are loaded during the one before
-  const int steps = (K + 2 * KB - 1) / (2 * KB);
   {
     Step s0, s1;
+    Factors f0, f1;
+    Factors& g1 = kOneCs ? f0 : f1;
+    auto ahead = [&](int i, Step& st, Factors& cs) {
+      if (i >= steps) return;
+      load(i, st);
+      if constexpr (!kOneCs) load_cs(i, cs);
+    };
     int i = wk;
-    if (i < steps) load(i, s0);
+    ahead(i, s0, f0);
+    if constexpr (kOneCs) load_cs(i, f0);
     for (; i < steps; i += 2 * WK) {
-      if (i + WK < steps) load(i + WK, s1);
-      compute(i, s0);
+      ahead(i + WK, s1, g1);
+      compute(i, s0, f0);
       if (i + WK >= steps) break;
-      if (i + 2 * WK < steps) load(i + 2 * WK, s0);
-      compute(i + WK, s1);
+      ahead(i + 2 * WK, s0, f0);
+      compute(i + WK, s1, g1);
     }
   }
 

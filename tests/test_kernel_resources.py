@@ -57,7 +57,8 @@ def spills():
 # The most registers an instance of each kernel family may spill.
 @pytest.mark.parametrize("kernel,most", [
     ("reuse_decode_bf16_kernel", 2), ("patch_align_act_bf16_kernel", 0),
-    ("encode_kv_bf16_kernel", 0), ("encode_bf16_kernel", 0)])
+    ("encode_kv_bf16_kernel", 0), ("encode_bf16_kernel", 0),
+    ("gemm_nt_kernel", 2), ("gemm_staged_bf16_kernel", 0)])
 def test_spilled_registers(spills, kernel, most):
     got = {n: v for n, v in spills.items() if re.search(r"\d%s" % kernel, n)}
     assert got
