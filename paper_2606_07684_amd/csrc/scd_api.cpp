@@ -112,7 +112,7 @@ scd_status_t opt_ptr(const void* const* arr, int layer, const char* name, const 
     if (s_ != SCD_OK) return s_;       \
   } while (0)
 
-// Packs jobs into launches of at most kMaxJobs jobs each.
+// Packs jobs into launches (launch_jobs).
 class JobPacker {
  public:
   JobPacker(const scd::GemmParams& base, int bm, int bn) : base_(base), bm_(bm), bn_(bn) {}
@@ -120,12 +120,13 @@ class JobPacker {
   std::vector<scd::GemmParams> build() const {
     std::vector<scd::GemmParams> out;
     const int64_t mt = (base_.m + bm_ - 1) / bm_;
-    for (size_t s = 0; s < jobs_.size(); s += scd::kMaxJobs) {
+    for (size_t s = 0; s < jobs_.size();) {
       scd::GemmParams p = base_;
       p.n_jobs = 0;
       int64_t tiles = 0;
-      for (size_t i = s; i < jobs_.size() && i < s + scd::kMaxJobs; ++i) {
-        scd::GemmJob j = jobs_[i];
+      const size_t end = s + scd::launch_jobs(jobs_.data() + s, jobs_.size() - s, base_.m, bm_, bn_);
+      for (; s < end; ++s) {
+        scd::GemmJob j = jobs_[s];
         j.tile_begin = static_cast<int32_t>(tiles);
         tiles += mt * ((j.n + bn_ - 1) / bn_);
         p.jobs[p.n_jobs++] = j;
@@ -210,6 +211,17 @@ int64_t kv_width(const scd_model_t* m) {
 }
 
 }  // namespace
+
+size_t scd::launch_jobs(const GemmJob* jobs, size_t n, int64_t m, int bm, int bn) {
+  constexpr int64_t kMaxTiles = ((int64_t{1} << 32) - 1) / 256;
+  int64_t tiles = 0;
+  size_t i = 0;
+  for (; i < n && i < static_cast<size_t>(kMaxJobs); ++i) {
+    tiles += (m + bm - 1) / bm * ((jobs[i].n + bn - 1) / bn);
+    if (i > 0 && tiles > kMaxTiles) break;
+  }
+  return i;
+}
 
 extern "C" {
 

@@ -48,6 +48,10 @@ struct GemmParams {
 };
 static_assert(sizeof(GemmParams) <= 4096, "kernel argument block");
 
+// How many of the first `n` jobs of m rows one launch of bm x bn tiles takes: at most kMaxJobs, and (a first
+// job aside) no more workgroups of 256 threads than a launch may have work-items, 2^32 - 1.
+size_t launch_jobs(const GemmJob* jobs, size_t n, int64_t m, int bm, int bn);
+
 // Workgroup shape of a generic launch, by the rows x columns of C it computes: 4 waves of 32 x 64 or
 // 32 x 32 along the rows, one tile whose 4 or 8 waves split the contraction, or a 128 x 128 tile staged
 // through LDS (the bf16 decode and Patch only).

@@ -68,3 +68,16 @@ def test_encode_resident(w, rank, rows, layers, want):
     fn = _rule("_ZN3scd15encode_residentEiill", ctypes.c_bool, ctypes.c_int, ctypes.c_int, ctypes.c_int64,
                ctypes.c_int64)
     assert fn(w, rank, rows, layers) == want
+
+
+# Jobs per launch: a full table, and where its workgroups of 256 threads would be 2^32 work-items (64 jobs of
+# 1024 columns in 128 x 32 tiles from 1,048,576 rows on), fewer; one job always fits.
+@pytest.mark.parametrize("rows,n,jobs,bm,bn,want", [
+    (8192, 1024, 70, 128, 32, 64), (8192, 1024, 5, 128, 64, 5), (1048448, 1024, 64, 128, 32, 64),
+    (1048576, 1024, 64, 128, 32, 63), (8388608, 1024, 64, 128, 32, 7), (8388608, 1024, 64, 128, 128, 31),
+    (2 ** 31 - 1, 32, 3, 128, 32, 1)])
+def test_launch_jobs(rows, n, jobs, bm, bn, want):
+    arr = (_Job * jobs)(*[_Job(None, None, None, None, n, 64, 0, 0) for _ in range(jobs)])
+    fn = _rule("_ZN3scd11launch_jobsEPKNS_7GemmJobEmlii", ctypes.c_size_t, ctypes.c_void_p, ctypes.c_size_t,
+               ctypes.c_int64, ctypes.c_int, ctypes.c_int)
+    assert fn(arr, jobs, rows, bm, bn) == want
