@@ -49,10 +49,12 @@ namespace {
 using namespace dev;
 
 constexpr int kBK = 64;                     // contraction step
-constexpr int kLDK = kBK;                   // LDS row (bf16 elements): 8 16-byte chunks, swizzled
+[[maybe_unused]] constexpr int kLDK = kBK;  // LDS row (bf16 elements): 8 16-byte chunks, swizzled
 constexpr int kChunks = kBK / 8;            // 16-byte chunks of an operand row's step
 constexpr int kWaves = 4;                   // one wave per SIMD
 constexpr int kThreads = 64 * kWaves;
+
+// (Names that only the device pass of the product's body uses are marked, for the host pass.)
 
 // Geometry of a square tile of TILE channels x TILE tokens (256 or 128) whose copies run AHEAD steps
 // before their use.
@@ -68,18 +70,18 @@ struct Geo {
   static_assert(TILE * 32 * 16 + TILE * 2 <= kRing * kSlot * 2, "epilogue staging fits the ring");
 };
 // Fourth word of a raw buffer resource on gfx9-family parts: 32-bit data format, no swizzle.
-constexpr int kBufferFlags = 0x00020000;
+[[maybe_unused]] constexpr int kBufferFlags = 0x00020000;
 
 // Chunk c of LDS row r sits at chunk position c ^ swz(r).  A swizzle must depend on r % 16 only
 // (fragment reads take it from the lane's row within a 16-row block); for 128-byte rows, r & 7 is
 // conflict-free for the MFMA operand reads (eight lanes of a read hit eight distinct chunk
 // positions of eight rows, all 32 banks once).
-__device__ __forceinline__ int swz(int r) { return r & 7; }
+[[maybe_unused]] __device__ __forceinline__ int swz(int r) { return r & 7; }
 
 // Weight row (within the tile) held by LDS row rho.  Element i of a 16 x 16 MFMA accumulator of
 // lane l is output row 4 (l / 16) + i of its block; with this order, blocks 2p and 2p + 1 of the
 // tile give lane l the channels 32p + 8 (l / 16) + (0..7), eight consecutive ones.
-__device__ __forceinline__ int weight_row_of_lds(int rho) {
+[[maybe_unused]] __device__ __forceinline__ int weight_row_of_lds(int rho) {
   const int m = rho & 15;
   return (rho & ~31) | (8 * (m >> 2) + 4 * ((rho >> 4) & 1) + (m & 3));
 }
@@ -89,16 +91,16 @@ __device__ __forceinline__ int weight_row_of_lds(int rho) {
 // reads (ds_read_b64_tr_b16: 16 lanes read 4 rows x 16 channels and lane i receives channel i of
 // the 4 rows).  Chunk c of row k sits at c ^ kswz(k); the two bits keep apart the rows a read takes
 // from one group of four, the third the groups of neighbouring reads.
-__device__ __forceinline__ int kswz(int k) { return 2 * (k & 3) + ((k >> 3) & 1); }
+[[maybe_unused]] __device__ __forceinline__ int kswz(int k) { return 2 * (k & 3) + ((k >> 3) & 1); }
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) s16x4* lds_s16x4_t;
 
 // s_waitcnt immediates: at most n vector-memory operations outstanding (optionally with every LDS
 // access completed), or every LDS access completed.
-constexpr int vmcnt_imm(int n, bool lds_done = false) {
+[[maybe_unused]] constexpr int vmcnt_imm(int n, bool lds_done = false) {
   return (n & 15) | ((n >> 4) << 14) | (0x7 << 4) | ((lds_done ? 0 : 0xF) << 8);
 }
-constexpr int kLgkmDone = 0xF | (0x3 << 14) | (0x7 << 4);
+[[maybe_unused]] constexpr int kLgkmDone = 0xF | (0x3 << 14) | (0x7 << 4);
 
 // Scheduling groups for one slice of MFMAs, in two halves with a scheduling fence between them (one
 // solver region of all 64 MFMAs, 16 reads and 8 copies of a 256-wide tile is not ordered as asked):
