@@ -393,8 +393,8 @@ __global__ __launch_bounds__(WM * WK * 64, 2) void gemm_nt_kernel(GemmParams p) 
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           const float u = f[b][e], v = f[b + FP][e];
-          f[b][e] = u * co[e] - v * si[e];
-          f[b + FP][e] = v * co[e] + u * si[e];
+          f[b][e] = fmaf(-v, si[e], u * co[e]);  // as the staged kernel rounds
+          f[b + FP][e] = fmaf(u, si[e], v * co[e]);
         }
       }
     }
@@ -571,8 +571,8 @@ __global__ __launch_bounds__(256) void gemm_staged_bf16_kernel(GemmParams p) {
       for (int e = 0; e < 8; ++e) {
         const float2 f = cs[e];
         const float x = u[e], y = v[e];
-        u[e] = x * f.x - y * f.y;
-        v[e] = y * f.x + x * f.y;
+        u[e] = fmaf(-y, f.y, x * f.x);  // as the direct kernel rounds
+        v[e] = fmaf(x, f.y, y * f.x);
       }
       *reinterpret_cast<uint4*>(C + gm * N + n0 + c0) = EL::pack(u);
       *reinterpret_cast<uint4*>(C + gm * N + n0 + c1) = EL::pack(v);
@@ -627,7 +627,7 @@ __global__ void positions_kernel(int32_t* out, int64_t n_tokens, int32_t n_seqs,
 // bf16 outputs wider than a 64-column tile are staged through LDS: decodes from 128 tiles of 128 x 128 on
 // (128x64 / 128x32 / staged: w = 512, rank 32, 8 layers, 64 tokens, 64 tiles, 9.0 / 8.4 / 8.1, 200 tokens 9.3
 // / 9.3 / 9.5, 500 tokens 10.7 / 11.6 / 10.2, 1000 tokens 18 / 19 / 12; w = 1024, rank 256, 4 layers, 64
-// tokens, 64 tiles, split by 8 8.1, staged 10.4), the longer contractions of the Patch above 1024 tiles of
+// tokens, 64 tiles, 128x32 9.3, staged 10.4), the longer contractions of the Patch above 1024 tiles of
 // 32 x 64, four a CU (split by 4 / staged: d_model 4128, 1024 channels, 4 layers, 200 tokens, 896 tiles, 67 /
 // 102, 333 tokens, 1408 tiles, 98 / 102, 500 tokens 130 / 98; d_model 4096, 192 channels, 1000 tokens, 768
 // tiles, 70 / 90, 1400 tokens, 1056 tiles, 112 / 91).
@@ -636,6 +636,8 @@ __global__ void positions_kernel(int32_t* out, int64_t n_tokens, int32_t n_seqs,
 // tokens 966 / 1109; bf16 w = 64, rank 64, 16 heads x 4 layers, 8192 tokens 145 / 173, staged 136; with 32
 // heads x 14 layers 943 / 1121, staged 1006; heads' shared rows of 32, 32 heads x 6 layers, 8192 tokens 251 /
 // 195), 32 x 32 waves below.
+// Decodes take those at every rank: the shapes that do not split the contraction add every sum in the same
+// order, so a decode's bits do not depend on the layers it shares a launch with (the streamed receipt's groups).
 // Longer ones take four 32 x 64 waves along the rows, or one such tile per workgroup whose waves split the
 // contraction, or 32 x 32 tiles split by 8 below one 32 x 64 tile per CU (256 tokens of a d_model of 512 to
 // 4096: a half to a third of the time).  The first two differ by the last round: a CU's share is whole
@@ -659,7 +661,8 @@ GenericShape generic_shape(Op op, bool bf16, const GemmJob* jobs, size_t n_jobs,
   if (bf16 && n > 64 &&
       ((op == Op::kReuseDecode && staged >= 128) || (op == Op::kPatchKV && tiles > 1024)))
     return GenericShape::kStaged;
-  if (k <= 128) return n > 32 && tiles >= 1536 ? GenericShape::k128x64 : GenericShape::k128x32;
+  if (k <= 128 || op == Op::kReuseDecode)
+    return n > 32 && tiles >= 1536 ? GenericShape::k128x64 : GenericShape::k128x32;
   if (tiles < 256) return GenericShape::k32x32;
   const int64_t rows4 = 4 * ((tiles + 1023) / 1024) + 1, split = (tiles + 255) / 256;
   const double cost = bf16 && op == Op::kEncodeKV ? 1.45 : 1.16;

@@ -111,6 +111,25 @@ def test_streamed_receipt_matches_one_call_decode(wl, group, source):
     U.assert_within(errs, U.TOL[wl.dtype], f"streamed {wl.name} group {group}")
 
 
+# The receipt's groups are smaller launches than the one call, on other shapes of the generic kernel (fp32
+# above rank 128; heads of 32 on staged tiles in one call): the caches are the same bits all the same.
+@pytest.mark.parametrize("dtype,heads,head_dim,tokens,ranks", [
+    ("f32", 4, 64, (400,), (192, 256, 192, 144, 256, 192)), ("f32", 8, 128, (33, 7), (256, 16, 208)),
+    ("bf16", 8, 32, (1300, 200), (64, 256, 48, 144, 256, 192, 80, 64))])
+def test_streamed_receipt_is_bit_identical_on_every_shape(dtype, heads, head_dim, tokens, ranks):
+    wl = W.Workload(f"receipt_{dtype}_{head_dim}_{len(ranks)}", len(ranks), 256, heads, head_dim, tokens, ranks,
+                    (), 1e4, dtype, with_mu=True)
+    dev = torch.device("cuda")
+    inp = U.Inputs(wl, dev, encode=False, patch=False)
+    rope = scd.scd_rope_table(U.model_of(wl), wl.max_position)
+    payload = _packed_codes(wl, inp, dev)
+    direct = U.run_gpu(wl, inp, rope, which=("decode",), fill=float("nan"))
+    _, kc, vc = _receive(wl, inp, rope, payload, 1, "device")
+    for l in inp.R:
+        assert _bitwise_equal(kc[l], direct["k_cache"][l]), f"k_cache[{l}]"
+        assert _bitwise_equal(vc[l], direct["v_cache"][l]), f"v_cache[{l}]"
+
+
 def test_streamed_receipt_full_size_from_pinned_host():
     """The receipt at the Llama-3-8B shape from pinned host memory, in the grouping the
     benchmark times; sampled rows against the oracle and every cache against the one-call decode."""
