@@ -8,6 +8,7 @@
 
 #include <cstdarg>
 #include <cstdio>
+#include <set>
 #include <string>
 #include <vector>
 
@@ -439,8 +440,27 @@ scd_status_t check_reuse_decode(const scd_model_t* model, const scd_batch_t* bat
   return SCD_OK;
 }
 
-// Launch half of the Reuse decode, on arguments check_reuse_decode accepted.
-scd_status_t enqueue_reuse_decode(const scd_model_t* model, const scd_batch_t* batch,
+// Whether a model's Reuse decode runs on the bf16 decode kernel, one launch per rank and branch.  Decided for
+// the whole model, so that the streamed receipt's groups take the same kernel as the one call.
+bool decode_by_rank(const scd_model_t* m, const scd_batch_t* b) {
+  if (m->dtype != SCD_BF16 || (m->head_dim != 64 && m->head_dim != 128) || m->basis_width % 128 != 0 ||
+      b->n_seqs > scd::kMaxLdsSeqs)
+    return false;
+  std::set<int> keys, values;
+  int64_t layers = 0;
+  for (int l = 0; l < m->n_layers; ++l) {
+    if (m->is_patch[l]) continue;
+    ++layers;
+    keys.insert(m->rank_k[l]);
+    values.insert(m->rank_v[l]);
+  }
+  return !scd::decode_one_launch(static_cast<int>(keys.size() + values.size()),
+                                 2 * layers * b->n_tokens * kv_width(m) * 2);
+}
+
+// Launch half of the Reuse decode, on arguments check_reuse_decode accepted; by_rank: decode_by_rank of the
+// whole model.
+scd_status_t enqueue_reuse_decode(const scd_model_t* model, const scd_batch_t* batch, bool by_rank,
                                   const void* rope_table, int64_t max_position,
                                   const void* const* z_k, const void* const* z_v,
                                   const void* const* w_dec_k, const void* const* w_dec_v,
@@ -450,8 +470,6 @@ scd_status_t enqueue_reuse_decode(const scd_model_t* model, const scd_batch_t* b
   const int w = model->basis_width;
   const int g = static_cast<int>(kv_width(model) / w);
   const int64_t T = batch->n_tokens;
-  const bool fast = model->dtype == SCD_BF16 && (model->head_dim == 64 || model->head_dim == 128) &&
-                    w % 128 == 0 && batch->n_seqs <= scd::kMaxLdsSeqs;
   std::vector<scd::GemmJob> jobs;
   for (int l = 0; l < model->n_layers; ++l) {
     if (model->is_patch[l]) continue;
@@ -462,7 +480,7 @@ scd_status_t enqueue_reuse_decode(const scd_model_t* model, const scd_batch_t* b
     jobs.push_back({z_v[l], w_dec_v[l], v_cache[l], mv, w, model->rank_v[l], scd::kVecOut, 0});
   }
   const scd::GemmParams base = base_params(model, batch, T * g, g, rope_table, max_position);
-  if (!fast) return run_generic(scd::Op::kReuseDecode, base, jobs, model->dtype, stream);
+  if (!by_rank) return run_generic(scd::Op::kReuseDecode, base, jobs, model->dtype, stream);
   // one launch per (rank, branch): key and value jobs run different kernel instances
   for (const auto& grp : group_by(jobs, [](const scd::GemmJob& j) {
          return j.k * 2 + ((j.flags & scd::kRopeOut) != 0 ? 1 : 0);
@@ -492,8 +510,8 @@ scd_status_t scd_reuse_decode(const scd_model_t* model, const scd_batch_t* batch
   SCD_TRY(check_reuse_decode(model, batch, rope_table, max_position, z_k, z_v, w_dec_k, w_dec_v,
                              mu_k, mu_v, k_cache, v_cache, &any));
   if (!any || batch->n_tokens == 0) return ok();
-  SCD_TRY(enqueue_reuse_decode(model, batch, rope_table, max_position, z_k, z_v, w_dec_k,
-                               w_dec_v, mu_k, mu_v, k_cache, v_cache, stream));
+  SCD_TRY(enqueue_reuse_decode(model, batch, decode_by_rank(model, batch), rope_table, max_position, z_k,
+                               z_v, w_dec_k, w_dec_v, mu_k, mu_v, k_cache, v_cache, stream));
   return ok();
 }
 
@@ -592,6 +610,7 @@ scd_status_t scd_reuse_decode_streamed(const scd_model_t* model, const scd_batch
   if ((e = hipStreamWaitEvent(copy_stream, ready, 0)) != hipSuccess)
     return hip_fail("stream wait", e);
 
+  const bool by_rank = decode_by_rank(model, batch);
   const char* src = static_cast<const char*>(payload_src);
   char* dst = static_cast<char*>(payload_dst);
   for (int l0 = 0; l0 < L; l0 += layers_per_group) {
@@ -617,7 +636,7 @@ scd_status_t scd_reuse_decode_streamed(const scd_model_t* model, const scd_batch
     bool sub_any = false;
     for (int l = l0; l < l1; ++l) sub_any = sub_any || !model->is_patch[l];
     if (!sub_any) continue;
-    SCD_TRY(enqueue_reuse_decode(&sub, batch, rope_table, max_position, zk.data() + l0,
+    SCD_TRY(enqueue_reuse_decode(&sub, batch, by_rank, rope_table, max_position, zk.data() + l0,
                                  zv.data() + l0, w_dec_k + l0, w_dec_v + l0,
                                  mu_k ? mu_k + l0 : nullptr, mu_v ? mu_v + l0 : nullptr,
                                  k_cache + l0, v_cache + l0, stream));

@@ -360,6 +360,16 @@ hipError_t launch_decode(int rank, const GemmParams& p, int grid_size, size_t ld
 
 }  // namespace
 
+// Schedules of several ranks take two launches per rank here, each with its own start and last round; one
+// launch of the generic kernel is slower by about 6 us, a launch's cost, for each 18 MiB it writes past the
+// first two.  16 layers, us by rank / in one launch: 8 KV heads of 128, ranks cycling 64, 128, 192 (6 launches)
+// 200 tokens (13 MB) 43 / 19, 622 tokens (41 MB) 49 / 34, 1500 tokens (98 MB) 72 / 64, 3000 tokens 96 / 116;
+// ranks 16, 48, 96 34 / 16, 38 / 29, 56 / 56, 83 / 102; keys of rank 16 with values of 32 and 96 (3
+// launches) 33 tokens 16 / 12, 300 tokens (20 MB) 19 / 20, 700 tokens 26 / 31; one rank, 48, 200 tokens 14 / 16.
+bool decode_one_launch(int launches, int64_t out_bytes) {
+  return launches > 2 && out_bytes <= (launches - 2) * (int64_t{18} << 20);
+}
+
 // Channels per workgroup (128 nhg) for a launch of n_jobs products of `rows` rows.  The widest chunk
 // that fits the LDS reads the codes least often and keeps each row's stores together, but its tiles
 // are large: a launch with few of them ends in a round that leaves CUs idle.  So the chunk with the

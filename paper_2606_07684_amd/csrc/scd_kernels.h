@@ -106,6 +106,9 @@ hipError_t launch_patch_fold(bool bf16, bool products, const FoldParams& p, hipS
 // Reuse decode on the bf16 path: workgroups own a channel chunk of 128 * nhg and a share of the
 // launch's row tiles (decode_tile_rows(nhg) rows each); basis_width % (128 * nhg) == 0, one rank
 // (% 16 == 0, <= 256) and one branch per launch, head_dim 64 or 128.
+// decode_one_launch: instead, every rank and branch in one launch of the generic kernel, for a decode of
+// `out_bytes` in all that would take `launches`.
+bool decode_one_launch(int launches, int64_t out_bytes);
 int decode_channel_groups(int rank, int basis_width, int64_t rows, int64_t n_jobs);
 int decode_tile_rows(int nhg, int rank);  // rows per tile of the kernel instance
 // align: run the aligner's first product (jobs flagged kSiluOut, rank <= 128, no RoPE) under its

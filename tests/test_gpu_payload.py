@@ -112,10 +112,12 @@ def test_streamed_receipt_matches_one_call_decode(wl, group, source):
 
 
 # The receipt's groups are smaller launches than the one call, on other shapes of the generic kernel (fp32
-# above rank 128; heads of 32 on staged tiles in one call): the caches are the same bits all the same.
+# above rank 128; heads of 32 on staged tiles in one call) or of one rank where the one call has several: the
+# caches are the same bits all the same.
 @pytest.mark.parametrize("dtype,heads,head_dim,tokens,ranks", [
     ("f32", 4, 64, (400,), (192, 256, 192, 144, 256, 192)), ("f32", 8, 128, (33, 7), (256, 16, 208)),
-    ("bf16", 8, 32, (1300, 200), (64, 256, 48, 144, 256, 192, 80, 64))])
+    ("bf16", 8, 32, (1300, 200), (64, 256, 48, 144, 256, 192, 80, 64)),
+    ("bf16", 4, 64, (300, 33), (16, 32, 256, 128)), ("bf16", 4, 128, (20000,), (16, 64, 128))])
 def test_streamed_receipt_is_bit_identical_on_every_shape(dtype, heads, head_dim, tokens, ranks):
     wl = W.Workload(f"receipt_{dtype}_{head_dim}_{len(ranks)}", len(ranks), 256, heads, head_dim, tokens, ranks,
                     (), 1e4, dtype, with_mu=True)

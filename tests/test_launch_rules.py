@@ -81,3 +81,10 @@ def test_launch_jobs(rows, n, jobs, bm, bn, want):
     fn = _rule("_ZN3scd11launch_jobsEPKNS_7GemmJobEmlii", ctypes.c_size_t, ctypes.c_void_p, ctypes.c_size_t,
                ctypes.c_int64, ctypes.c_int, ctypes.c_int)
     assert fn(arr, jobs, rows, bm, bn) == want
+
+
+@pytest.mark.parametrize("launches,mib,want", [
+    (2, 0, False), (2, 1, False), (3, 18, True), (3, 19, False), (6, 72, True), (6, 94, False)])
+def test_decode_one_launch(launches, mib, want):
+    fn = _rule("_ZN3scd17decode_one_launchEil", ctypes.c_bool, ctypes.c_int, ctypes.c_int64)
+    assert fn(launches, mib << 20) == want
