@@ -286,8 +286,8 @@ scd_status_t scd_reuse_decode_streamed(const scd_model_t* model, const scd_batch
  *  - scd_fit_solve takes those sums for N = n_rows rows (n_tokens * g) and solves the fit in fp64
  *    (Householder tridiagonalisation of the centred Gram, bisection and inverse iteration for its
  *    top r eigenpairs, Cholesky ridge solves; each stage one launch over all layers, except the
- *    tridiagonalisation, one launch per column until at most 128 rows remain, and the Cholesky of
- *    sizes above 128, one launch per column), writing w_enc, w_dec and, when
+ *    tridiagonalisation, one launch per column until at most 256 rows remain, and the Cholesky,
+ *    two launches per 64 columns), writing w_enc, w_dec and, when
  *    center = 1, mu_enc and mu_dec in the model's dtype (rounded once).  Needs basis_width <= 1024
  *    and 16 <= rank <= basis_width, rank % 16 == 0, lambda >= 0.  lambda = 0 with a singular
  *    A^T A (fewer independent rows than w) leaves NaN in the layer's outputs.  Eigenvalues within

@@ -5,8 +5,9 @@
 //
 // Work decomposition: a launch covers one branch (keys or values) of every layer of one rank, as
 // one round of workgroups sized to the machine.  A workgroup owns a channel chunk of NHG x 128
-// channels (512 for ranks up to 128: one workgroup of 8 waves per CU, whose basis chunk fills most
-// of the LDS) and a contiguous, balanced share of the launch's row tiles, running across layers.
+// channels (128, 256 or 512, decode_channel_groups; 512 at rank 128 is one workgroup of 8 waves per CU,
+// whose basis chunk fills most of the LDS) and a contiguous, balanced share of the launch's row tiles,
+// running across layers.
 // It copies a layer-branch's basis chunk (CN rows of W_dec, permuted so each MFMA accumulator lane
 // ends with 16 consecutive channels of one row) into padded LDS rows with direct global->LDS
 // loads when its share enters that layer-branch.  Each wave owns 32 rows of a tile: it loads

@@ -795,7 +795,7 @@ __global__ __launch_bounds__(kSolveThreads) void fit_prep_kernel(const FitSolveP
 // round of loads and the rows arrive while the vector part's two barriers pass.  PRE: row entries per
 // lane, n - k - 2 <= 64 PRE.  PAIR: the second of a pair.  write: store the matrix.  Every workgroup repeats the vector part (each thread keeps its own entries
 // in registers).  Bound by launch latency and by streaming the block twice: with
-// the rows loaded after the vector part, four barriers and shuffled sums, each of the 1791 steps at
+// the rows loaded after the vector part, four barriers and shuffled sums, each of the 1792 steps at
 // w = 1024 took about 10 us more (fit of two layers 46.3 ms, then 28.3).
 template <int PRE, int ROWS, int THREADS, bool PAIR>
 __global__ __launch_bounds__(THREADS, 2) void fit_tridiag_kernel(const SolveArgs a, int write) {
@@ -1381,7 +1381,7 @@ __device__ inline bool cluster_of(const double* lam, int r, int j, double ctol, 
 // Inverse iteration, one eigenvector per working thread: the thread keeps its vector and the LU
 // factors of T - sigma I in LDS ([i][thread], THREADS interleaved, so the threads' accesses fall in
 // distinct banks) and copies each finished vector to Y[i][m].  Two instances: 8 threads per workgroup
-// for n <= 256, and one thread per workgroup (82 KiB of LDS) for larger n; the chain of dependent
+// for n <= 256, and one thread per workgroup (114 KiB of LDS) for larger n; the chain of dependent
 // accesses would otherwise wait on global memory at each link.  28 layers x 64 vectors of 256 150 us, 2
 // layers x 128 vectors of 2048 1.1 ms (a division per row in every solve, and the sums in passes of their
 // own: 362 us and 2.9 ms).
